@@ -30,6 +30,11 @@
  *     results to the host synchronise that stream before returning.
  *   - A handle is not thread-safe: calls on one handle must not overlap.
  *     Distinct handles are independent.
+ *   - The fine operator's products in giamg_solve, giamg_solve_noalloc and
+ *     giamg_apply run over the elements (sum factorisation, same operator to
+ *     rounding) where it is large enough (at least 4 M and 0.2 M p^2
+ *     nonzeros, p >= 2), over its CSR rows otherwise.  direct_gathers,
+ *     row_groups and lean_max_nnz choose the form of the CSR products.
  */
 #ifndef GIAMG_H
 #define GIAMG_H

@@ -175,6 +175,28 @@ struct DevCSR {
 void setup_row_blocks(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s);
 void setup_row_blocks32(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s);
 
+// Element form of the fine operator (element.hip): the product by sum
+// factorisation over the elements.  order == 0: not built.
+constexpr int ELEM_COEF = 21;      // trilinear coefficients per element (without the constant)
+struct ElementForm {
+    int order = 0;
+    int64_t ne = 0;
+    double lambda = 0.0;
+    DevBuf<int32_t> map;           // [ne][(order+1)^3] node, -1 = constrained
+    DevBuf<int32_t> nptr, nent;    // per node: its entries of ev, ascending ([n + 1], one per map entry >= 0)
+    DevBuf<double> coef, tabs;     // [ELEM_COEF][ne]; 1-D tables
+    DevBuf<float> coef32, tabs32;  // mixed precision
+    DevBuf<double> ev;             // [ne][(order+1)^3] element results (either precision)
+    bool built() const { return order > 0; }
+    int64_t device_bytes() const {
+        return (int64_t)(map.n + nptr.n + nent.n) * 4 + (int64_t)(coef.n + tabs.n + ev.n) * 8 +
+               (int64_t)(coef32.n + tabs32.n) * 4;
+    }
+};
+void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
+                        int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
+                        hipStream_t s);
+
 // ---- the hierarchy ----------------------------------------------------------
 struct BatchState;                 // batched-solve workspace (batch.hip)
 struct BatchDeleter {
@@ -188,6 +210,7 @@ struct Level {
     DevCSR A, P, R;                // P, R empty on the coarsest level
     DevCSR AP;                     // A P (rows of this level, columns of the next), kept
                                    // from the Galerkin product for the post-smoothing residual
+    ElementForm E;                 // fine level: its products run in this form where built
     DevBuf<double> dinv;
     DevBuf<float> dinv32;
     double lam_hat = 0.0;

@@ -121,7 +121,14 @@ struct SpmvArgs {
     // lean form (DevCSR::lean): nblk blocks of LEAN_THREADS / lanes rows,
     // reading rp / ci / val / v directly
     bool lean = false;
+    const ElementForm* elem = nullptr;   // host only: the product runs in the element form
 };
+
+// Element form: product in two kernels (nblk = element_blocks(n) row blocks
+// for the dot partials).
+int64_t element_blocks(int64_t n);
+template <typename T>
+void launch_element_product(int mode, const SpmvArgs<T>& a, hipStream_t s);
 
 template <typename T>
 void launch_spmv(int mode, const SpmvArgs<T>& a, hipStream_t s);

@@ -162,9 +162,23 @@ SpmvArgs<T> args_of(const DevCSR& M, const T* val) {
     return a;
 }
 
-// Blocks of the product form args_of picks for FP64 values (the number of
-// block partials its DOT and RINIT epilogues write).
-int64_t product_blocks(const DevCSR& M) { return M.lean ? M.lean_nblk : M.gnblk > 0 ? M.gnblk : M.blk.nblk; }
+// Product arguments over a level's operator: the element form where built.
+template <typename T>
+SpmvArgs<T> args_of_level(const Level& L, const T* val) {
+    SpmvArgs<T> a = args_of<T>(L.A, val);
+    if (L.E.built()) {
+        a.elem = &L.E;
+        a.nblk = element_blocks(a.n);
+    }
+    return a;
+}
+
+// Blocks of the product form args_of_level picks for FP64 values (the number
+// of block partials its DOT and RINIT epilogues write).
+int64_t product_blocks(const Level& L) {
+    const DevCSR& M = L.A;
+    return L.E.built() ? element_blocks(M.nrows) : M.lean ? M.lean_nblk : M.gnblk > 0 ? M.gnblk : M.blk.nblk;
+}
 
 // Lean form for the operators with at most max_nnz nonzeros and no row longer
 // than spmv_cap<double>() (their staging tables are released).
@@ -252,7 +266,7 @@ double power_estimate(Handle& H, Level& L) {
     launch_power_start(n, v.get(), H.stream);
     double lam = 0.0;
     for (int it = 0; it < H.opts.power_iters; ++it) {
-        SpmvArgs<double> a = args_of<double>(L.A, L.A.val.get());
+        SpmvArgs<double> a = args_of_level<double>(L, L.A.val.get());
         a.v = v.get(); a.y = w.get(); a.dinv = L.dinv.get();
         launch_spmv(SPMV_DINV, a, H.stream);
         const double ww = std::sqrt(device_dot(H, n, w.get(), w.get()));
@@ -288,6 +302,21 @@ void alloc_level_vectors(Level& L, bool mixed) {
 }  // namespace
 
 void noalloc_scratch_init();
+
+// Whether the fine operator's products run in the element form (element.hip):
+// where reading the assembled rows takes longer than the two kernels' own
+// latency, which grows with the order.  Measured (fine FP64 Chebyshev step,
+// element form / CSR): 8^3 p = 4 (6.4 M nonzeros) 14 / 20 us, 16^3 p = 4
+// (49 M) 26 / 116, 32^3 p = 4 (424 M) 123 / 943, 40^3 p = 2 53 / 78,
+// 13^3 p = 5 30 / 181, 8^3 p = 8 45 / 547; but 2^3 p = 10 (13 M) 40 / 28 and
+// 3^3 p = 8 (12 M) 30 / 29.  The rule looks at the operator alone, so the
+// product forms of the CSR arrays (staged, direct, lean, grouped) all leave
+// the same results behind.
+static bool use_element_form(const Handle& H) {
+    const int64_t p = H.porder, nl = (p + 1) * (p + 1) * (p + 1);
+    return p >= 2 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 200000 * p * p) &&
+           H.n_elem * nl < (int64_t(1) << 31);
+}
 
 void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     noalloc_scratch_init();
@@ -332,6 +361,10 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
             HostCSR A0 = assemble_fine(H.corners, l2g, ne, H.porder, n, H.lambda, H.constrained, o.basis);
             upload_csr(A0, L.A, H.stream, false);
         }
+    }
+    if (use_element_form(H)) {
+        Level& L = H.levels.back();
+        build_element_form(L.E, H.corners, l2g, ne, H.porder, n, H.lambda, H.constrained, o.basis, mixed, H.stream);
     }
     H.setup_ms[0] = ms_since(t0);
     // p-levels
@@ -452,6 +485,7 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     int64_t maxn = 1, maxblk = 1;
     for (auto& L : H.levels) {
         maxn = std::max(maxn, L.n);
+        if (L.E.built()) maxblk = std::max(maxblk, element_blocks(L.n));
         for (const DevCSR* M : {&L.A, &L.P, &L.R, &L.AP})
             maxblk = std::max({maxblk, M->blk.nblk, M->blk32.nblk, M->gnblk, M->lean_nblk});
     }
@@ -516,7 +550,7 @@ int64_t handle_device_bytes(const Handle& H) {
     };
     int64_t b = 0;
     for (const Level& L : H.levels) {
-        b += csr(L.A) + csr(L.P) + csr(L.R) + csr(L.AP);
+        b += csr(L.A) + csr(L.P) + csr(L.R) + csr(L.AP) + L.E.device_bytes();
         b += (int64_t)(L.dinv.n + L.f.n + L.x.n + L.r.n + L.d0.n + L.d1.n + L.t.n) * 8;
         b += (int64_t)(L.dinv32.n + L.f32.n + L.x32.n + L.r32.n + L.d032.n + L.d132.n + L.t32.n) * 4;
     }
@@ -560,7 +594,7 @@ template <> struct LV<float> {
 
 template <typename T>
 SpmvArgs<T> args_A(const Level& L) {
-    SpmvArgs<T> a = args_of<T>(L.A, LV<T>::A(L));
+    SpmvArgs<T> a = args_of_level<T>(L, LV<T>::A(L));
     a.dinv = LV<T>::dinv(L);
     return a;
 }
@@ -583,6 +617,11 @@ double spmv_bytes(int mode, const SpmvArgs<T>& a) {
         case SPMV_DINV: rows = 2; break;              // dinv, y
         case SPMV_RINIT: rows = 2; break;             // f, y
         case SPMV_RCHEB0: rows = 4; break;            // dinv, y, r, d_0
+    }
+    if (a.elem != nullptr) {   // element map, coefficients, element results out and in, node lists, vectors
+        const ElementForm& E = *a.elem;
+        return 4.0 * E.map.n + ELEM_COEF * vb * E.ne + 2.0 * vb * E.map.n + 4.0 * (E.nptr.n + E.nent.n) +
+               vb * a.ncols + rows * vb * a.n;
     }
     if (a.gblk != nullptr)   // grouped: slots per entry, block records, row list, group table
         return vb * a.nnz + 2.0 * a.gentries + 8.0 * a.gnruns + (4.0 + 32.0) * (a.nblk + 1) + 4.0 * a.n +
@@ -853,7 +892,10 @@ void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false) {
     }
     Phase ph(H, GIAMG_PHASE_SMOOTH);
     Phase ph0(H, l == 0 ? GIAMG_PHASE_FIRST_SMOOTH : -1);
-    smooth<T>(H, L, f, x, false, LV<T>::t(L), LV<T>::x(C));
+    if (L.E.built())   // A x costs less than (A P) e there
+        smooth<T>(H, L, f, x, false);
+    else
+        smooth<T>(H, L, f, x, false, LV<T>::t(L), LV<T>::x(C));
 }
 
 // z = V-cycle(r).  init_done: the fine level's smoother init was fused into
@@ -919,11 +961,11 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
     const Level& L0 = H.levels[0];
     const bool flexible = H.opts.precision == GIAMG_PREC_MIXED;
     hipStream_t s = H.stream;
-    const int64_t gs = product_blocks(L0.A), gv = vec_blocks(n);
+    const int64_t gs = product_blocks(L0), gv = vec_blocks(n);
     // initial: a zero guess (flagged on the device) skips the product; at
     // exit the true residual of the solution is always formed
     auto rinit = [&](double* out, bool initial) {
-        SpmvArgs<double> a = args_of<double>(L0.A, L0.A.val.get());
+        SpmvArgs<double> a = args_of_level<double>(L0, L0.A.val.get());
         a.v = x; a.f = b; a.y = out; a.partial = w.partial;
         if (initial) a.vnz = w.scal + S_XNZ;
         run_spmv(H, SPMV_RINIT, a);
@@ -995,7 +1037,7 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
                 H.prof.half = 1;
                 {
                     Phase ph(H, GIAMG_PHASE_CG_MATVEC);
-                    SpmvArgs<double> a = args_of<double>(L0.A, L0.A.val.get());
+                    SpmvArgs<double> a = args_of_level<double>(L0, L0.A.val.get());
                     a.v = w.p; a.y = w.q; a.partial = w.partial;
                     H.bytes += (flexible ? 56.0 : 48.0) * n;
                     run_spmv(H, SPMV_DOT, a);
