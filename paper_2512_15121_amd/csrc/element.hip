@@ -15,8 +15,13 @@
 //
 // Why: the assembled rows hold (p + 2)^3 nonzeros of 10 to 12 bytes per node,
 // read once per product: 4.4 GB at 32^3, p = 4, 0.62 ms at the rate of a plain
-// read stream.  The element form reads the element map, the corners and the
-// vectors (about 0.15 GB there) and is bound by the vector ALUs and LDS.
+// read stream and 0.94 ms measured.  The element form reads the element map,
+// the corners and the vectors (about 0.15 GB there).  Its first kernel takes
+// 60 us there in FP64 and 36 us in FP32 (990 vector instructions per wave, half
+// of the vector ALUs' time in FP64 at three waves per SIMD, 83 % of it in FP32
+// at five; with full tables instead of the even and odd parts 91 and 40 us:
+// the tables then spilled from the scalar registers), the second 20 to 28 us
+// (its vectors at about 6 TB/s).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -38,30 +43,34 @@ struct ElemArgs {
     const T* v = nullptr;
     T* ev = nullptr;                 // [ne][nl]
     const T* coef = nullptr;         // [ELEM_COEF][ne] trilinear coefficients
-    const T* tabs = nullptr;         // L [n1][nq], D [n1][nq], Gauss points [nq], weights [nq]
-    T lambda = 0;
+    const T* tabs = nullptr;         // 1-D tables (element_tables)
+    T lambda = 0, ps = 1, pt = -1;   // pair transform of the inner positions (element_tables)
     const int* stop = nullptr;
     const double* vnz = nullptr;     // when set and zero, v is +0: nothing to do
 };
 
+// Every multiply-add is written out, so each instance of the kernel gives the
+// same bits (see the contract pragma at each function).
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double recip(double d) {
     // reciprocal estimate and two Newton steps (1 ulp)
     double r = __builtin_amdgcn_rcp(d);
-    r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
-    return __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+    r = mad(mad(-d, r, 1.0), r, r);
+    return mad(mad(-d, r, 1.0), r, r);
 }
 __device__ __forceinline__ float recip(float d) {
     const float r = __builtin_amdgcn_rcpf(d);
-    return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+    return mad(mad(-d, r, 1.0f), r, r);
 }
 
 // Thread counts and elements per block.  The quadrature step takes (p + 2)^2
 // lanes per element: narrow blocks are the whole waves one element needs (or
 // several elements in one wave), wide blocks fill 256 threads with elements.
 // Wide where that fills more lanes (p = 3, 4, 5, 7, 8) and the mesh has a wide
-// block for every CU; measured (product of the fine operator, FP64, wide /
-// narrow): 32^3 p = 4 115.6 / 154.6 us, 12^3 p = 7 51.2 / 74.8, 13^3 p = 5
-// 23.1 / 28.7; with fewer elements 8^3 p = 4 16.3 / 13.2; 40^3 p = 2 48.8 / 44.8.
+// block for every CU.  Measured with the full tables (product, FP64, wide /
+// narrow): 32^3 p = 4 116 / 155 us, 12^3 p = 7 51 / 75, 13^3 p = 5 23 / 29; with
+// fewer elements 8^3 p = 4 16 / 13; 40^3 p = 2 49 / 45.
 constexpr int64_t ELEM_WIDE_LANES = 65536;   // 256 lanes on each of 256 CUs
 constexpr bool elem_wide_pays(int p) { return p == 3 || p == 4 || p == 5 || p == 7 || p == 8; }
 template <int P>
@@ -72,208 +81,388 @@ constexpr int elem_threads(bool wide) {
 template <int P>
 constexpr int elem_per_block(bool wide) { return elem_threads<P>(wide) / ((P + 2) * (P + 2)); }
 
+// 1-D contractions in even and odd parts.  A line of N nodal values u becomes
+// N / 2 pairs (e, o) of position k and its mirror N - 1 - k (and the middle
+// value, which is even); the values at the Gauss points q and Q - 1 - q are
+// then (even part) +- (odd part), and likewise for the derivative, whose even
+// part comes from the odd coefficients.  This halves the multiply-adds of both
+// tables, and one q's entries (2 N numbers: Le, Lo, De, Do) are all a step
+// needs at a time, so they stay in scalar registers.
+template <typename T, int N>
+struct Line {
+    static constexpr int H = (N + 1) / 2, O = N / 2;
+    T e[H], o[O > 0 ? O : 1];
+};
+template <typename T, int N>
+__device__ __forceinline__ void to_parity(const T* u, Line<T, N>& l, T ps, T pt) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+        const T a = u[k], b = u[N - 1 - k];
+        if (k == 0) {
+            l.e[0] = a + b;
+            l.o[0] = a - b;
+        } else {
+            l.e[k] = mad(ps, b, a);
+            l.o[k] = mad(pt, b, ps * a);
+        }
+    }
+    if constexpr (N % 2) l.e[N / 2] = u[N / 2];
+}
+template <typename T, int N>
+__device__ __forceinline__ void from_parity(const Line<T, N>& l, T* u, T ps, T pt) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) {
+        if (k == 0) {
+            u[0] = l.e[0] + l.o[0];
+            u[N - 1] = l.e[0] - l.o[0];
+        } else {
+            u[k] = mad(ps, l.o[k], l.e[k]);
+            u[N - 1 - k] = mad(pt, l.o[k], ps * l.e[k]);
+        }
+    }
+    if constexpr (N % 2) u[N / 2] = l.e[N / 2];
+}
+// The table entries of one Gauss point pair: [H] Le, [O] Lo, [H] De, [O] Do.
+// In the constant address space: uniform loads into scalar registers.
+template <typename T>
+using const_ptr = const T __attribute__((address_space(4)))*;
+template <typename T, int N>
+struct Rec {
+    const_ptr<T> p;
+    __device__ __forceinline__ T le(int k) const { return p[k]; }
+    __device__ __forceinline__ T lo(int k) const { return p[(N + 1) / 2 + k]; }
+    __device__ __forceinline__ T de(int k) const { return p[N + k]; }
+    __device__ __forceinline__ T dod(int k) const { return p[N + (N + 1) / 2 + k]; }
+};
+template <typename T, int N>
+__device__ __forceinline__ T even_l(const Rec<T, N>& r, const Line<T, N>& l) {
+    T s = r.le(0) * l.e[0];
+#pragma unroll
+    for (int k = 1; k < (N + 1) / 2; ++k) s = mad(r.le(k), l.e[k], s);
+    return s;
+}
+template <typename T, int N>
+__device__ __forceinline__ T odd_l(const Rec<T, N>& r, const Line<T, N>& l) {
+    T s = r.lo(0) * l.o[0];
+#pragma unroll
+    for (int k = 1; k < N / 2; ++k) s = mad(r.lo(k), l.o[k], s);
+    return s;
+}
+template <typename T, int N>   // derivative: even in q
+__device__ __forceinline__ T even_d(const Rec<T, N>& r, const Line<T, N>& l) {
+    T s = r.dod(0) * l.o[0];
+#pragma unroll
+    for (int k = 1; k < N / 2; ++k) s = mad(r.dod(k), l.o[k], s);
+    return s;
+}
+template <typename T, int N>   // derivative: odd in q
+__device__ __forceinline__ T odd_d(const Rec<T, N>& r, const Line<T, N>& l) {
+    T s = r.de(0) * l.e[0];
+#pragma unroll
+    for (int k = 1; k < (N + 1) / 2; ++k) s = mad(r.de(k), l.e[k], s);
+    return s;
+}
+// Transposes: a Gauss pair's even and odd parts into the coefficients.
+template <typename T, int N>
+__device__ __forceinline__ void add_l(const Rec<T, N>& r, T ev, T od, Line<T, N>& l) {
+#pragma unroll
+    for (int k = 0; k < (N + 1) / 2; ++k) l.e[k] = mad(r.le(k), ev, l.e[k]);
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) l.o[k] = mad(r.lo(k), od, l.o[k]);
+}
+template <typename T, int N>
+__device__ __forceinline__ void add_d(const Rec<T, N>& r, T ev, T od, Line<T, N>& l) {
+#pragma unroll
+    for (int k = 0; k < (N + 1) / 2; ++k) l.e[k] = mad(r.de(k), od, l.e[k]);
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) l.o[k] = mad(r.dod(k), ev, l.o[k]);
+}
+template <typename T, int N>
+__device__ __forceinline__ void clear(Line<T, N>& l) {
+#pragma unroll
+    for (int k = 0; k < (N + 1) / 2; ++k) l.e[k] = T(0);
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k) l.o[k] = T(0);
+}
+// The same pointer, opaque to the compiler: the table entries of one step are
+// loaded again in the next instead of being held (and spilled) across it.
+template <typename T>
+__device__ __forceinline__ const_ptr<T> fresh(const T* p) {
+    asm volatile("" : "+s"(p));
+    return (const_ptr<T>)(uintptr_t)p;
+}
+
 template <typename T, int P, bool WIDE>
 __global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs<T> a) {
+#pragma clang fp contract(off)
     if (a.stop != nullptr && *a.stop != 0) return;
     if (a.vnz != nullptr && *a.vnz == 0.0) return;
     constexpr int N = P + 1, Q = P + 2, N2 = N * N, NL = N2 * N, Q2 = Q * Q;
-    constexpr int NT = elem_threads<P>(WIDE), EPB = elem_per_block<P>(WIDE);
-    constexpr int SA = 2 * Q * N2;     // [2][qz][i][j]
-    constexpr int SB = 3 * N * Q2;     // [3][i][qy][qz]; first and last the element's nodal values
-    constexpr int ITER = (EPB * NL + NT - 1) / NT;
-    __shared__ T sA[EPB * SA];
-    __shared__ T sB[EPB * SB];
+    constexpr int H = (Q + 1) / 2;                 // Gauss pairs, the middle point one of its own
+    constexpr int NT = elem_threads<P>(WIDE), V = elem_per_block<P>(WIDE);
+    constexpr int ITER = (V * NL + NT - 1) / NT;
+    constexpr int UNROLL = 2 * N * H * (int)sizeof(T) <= 240 ? H : 1;   // one step's tables in 60 scalar registers
+    // one region, element fastest: nodal values [i][j][k], then [2][qz][i][j],
+    // then [3][i][qy][qz], and back; every step has at most one line per
+    // thread, reads it, waits, and writes its results over the others' inputs
+    __shared__ T sh[V * 3 * N * Q2];
     const int tid = threadIdx.x;
-    const int64_t e0 = xcd_block(blockIdx.x, gridDim.x) * EPB;
-    const int cnt = (int)min((int64_t)EPB, a.ne - e0) * NL;
-    const T* __restrict__ L = a.tabs;
-    const T* __restrict__ D = a.tabs + N * Q;
-    const T* __restrict__ gq = a.tabs + 2 * N * Q;
-    const T* __restrict__ wq = gq + Q;
+    const int v = tid % V, line = tid / V;
+    const int64_t e0 = xcd_block(blockIdx.x, gridDim.x) * V;
+    const int cnt = (int)min((int64_t)V, a.ne - e0) * NL;
+    const T ps = a.ps, pt = a.pt;
     // gather
     {
         const int32_t* __restrict__ map = a.map + e0 * NL;
-        const T* __restrict__ v = a.v;
+        const T* __restrict__ vec = a.v;
         int32_t g[ITER];
         T x[ITER];
 #pragma unroll
         for (int it = 0; it < ITER; ++it) g[it] = map[min(tid + it * NT, cnt - 1)];
 #pragma unroll
-        for (int it = 0; it < ITER; ++it) x[it] = v[max(g[it], 0)];
+        for (int it = 0; it < ITER; ++it) x[it] = vec[max(g[it], 0)];
 #pragma unroll
         for (int it = 0; it < ITER; ++it) {
             const int t = tid + it * NT;
-            if (t < EPB * NL) sB[(t / NL) * SB + t % NL] = g[it] >= 0 ? x[it] : T(0);
+            if (t < V * NL) sh[(t % NL) * V + t / NL] = g[it] >= 0 ? x[it] : T(0);
         }
     }
+    const int64_t e = min(e0 + v, a.ne - 1);
+    T c[ELEM_COEF];   // the element's geometry, used at the quadrature points
+#pragma unroll
+    for (int m = 0; m < ELEM_COEF; ++m) c[m] = a.coef[m * a.ne + e];
     __syncthreads();
     // z: nodal lines to Gauss points, values and derivatives
-    for (int t = tid; t < EPB * N2; t += NT) {
-        const int el = t / N2, ij = t % N2;
+    {
+        const const_ptr<T> tab = fresh(a.tabs);
         T u[N];
+        Line<T, N> l;
+        if (line < N2) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) u[k] = sB[el * SB + ij * N + k];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            T s0 = L[q] * u[0], s1 = D[q] * u[0];
-#pragma unroll
-            for (int k = 1; k < N; ++k) {
-                s0 += L[k * Q + q] * u[k];
-                s1 += D[k * Q + q] * u[k];
+            for (int k = 0; k < N; ++k) u[k] = sh[(line * N + k) * V + v];
+        }
+        to_parity<T, N>(u, l, ps, pt);
+        __syncthreads();
+        if (line < N2) {
+#pragma unroll UNROLL
+            for (int q = 0; q < H; ++q) {
+                const Rec<T, N> r{tab + q * 2 * N};
+                const T ve = even_l(r, l), vo = odd_l(r, l), de = even_d(r, l), dd = odd_d(r, l);
+                sh[(q * N2 + line) * V + v] = ve + vo;
+                sh[((Q + q) * N2 + line) * V + v] = de + dd;
+                if (Q % 2 == 0 || q < H - 1) {
+                    sh[((Q - 1 - q) * N2 + line) * V + v] = ve - vo;
+                    sh[((2 * Q - 1 - q) * N2 + line) * V + v] = de - dd;
+                }
             }
-            sA[el * SA + q * N2 + ij] = s0;
-            sA[el * SA + (Q + q) * N2 + ij] = s1;
         }
     }
     __syncthreads();
-    // y
-    for (int t = tid; t < EPB * N * Q; t += NT) {
-        const int el = t / (N * Q), r = t % (N * Q), qz = r / N, i = r % N;
-        T a0[N], a1[N];
+    // y: lines (qz, i)
+    const int li = line % N, lq = line / N;
+    {
+        const const_ptr<T> tab = fresh(a.tabs);
+        T u[N];
+        Line<T, N> l0, l1;
+        if (line < N * Q) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            a0[j] = sA[el * SA + r * N + j];
-            a1[j] = sA[el * SA + Q * N2 + r * N + j];
+            for (int j = 0; j < N; ++j) u[j] = sh[(line * N + j) * V + v];
+            to_parity<T, N>(u, l0, ps, pt);
+#pragma unroll
+            for (int j = 0; j < N; ++j) u[j] = sh[(Q * N2 + line * N + j) * V + v];
+            to_parity<T, N>(u, l1, ps, pt);
         }
-        T* out = sB + el * SB + i * Q2 + qz;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            T s0 = L[q] * a0[0], s1 = D[q] * a0[0], s2 = L[q] * a1[0];
-#pragma unroll
-            for (int j = 1; j < N; ++j) {
-                s0 += L[j * Q + q] * a0[j];
-                s1 += D[j * Q + q] * a0[j];
-                s2 += L[j * Q + q] * a1[j];
+        __syncthreads();
+        if (line < N * Q) {
+            T* out = sh + (li * Q2 + lq) * V + v;
+#pragma unroll UNROLL
+            for (int q = 0; q < H; ++q) {
+                const Rec<T, N> r{tab + q * 2 * N};
+                const T ve = even_l(r, l0), vo = odd_l(r, l0), de = even_d(r, l0), dd = odd_d(r, l0);
+                const T ze = even_l(r, l1), zo = odd_l(r, l1);
+                out[q * Q * V] = ve + vo;
+                out[(N * Q2 + q * Q) * V] = de + dd;
+                out[(2 * N * Q2 + q * Q) * V] = ze + zo;
+                if (Q % 2 == 0 || q < H - 1) {
+                    out[(Q - 1 - q) * Q * V] = ve - vo;
+                    out[(N * Q2 + (Q - 1 - q) * Q) * V] = de - dd;
+                    out[(2 * N * Q2 + (Q - 1 - q) * Q) * V] = ze - zo;
+                }
             }
-            out[q * Q] = s0;
-            out[N * Q2 + q * Q] = s1;
-            out[2 * N * Q2 + q * Q] = s2;
         }
     }
     __syncthreads();
     // x, the quadrature points of one x line per thread, and x back
-    if (tid < EPB * Q2) {
-        const int el = tid / Q2, r = tid % Q2;
-        const int64_t e = min(e0 + el, a.ne - 1);
-        T c[ELEM_COEF];
-#pragma unroll
-        for (int m = 0; m < ELEM_COEF; ++m) c[m] = a.coef[m * a.ne + e];
-        const T eta = gq[r / Q], zeta = gq[r % Q];
-        const T wyz = wq[r / Q] * wq[r % Q];
-        // columns of the Jacobian: dx/dxi is fixed on the line, the others are linear in xi
+    if (line < Q2) {
+        const const_ptr<T> tab = fresh(a.tabs);
+        const const_ptr<T> gq = tab + 2 * N * H, wq = gq + Q;
+        const T* __restrict__ lgq = a.tabs + 2 * N * H;   // per lane
+        const T eta = lgq[line / Q], zeta = lgq[line % Q];
+        const T wyz = lgq[Q + line / Q] * lgq[Q + line % Q];
+        // Columns of the Jacobian: ax = dx/dxi is fixed on the line, b = dx/deta
+        // and d = dx/dzeta are linear in xi.  gx = b x d, gy = d x ax,
+        // gz = ax x b are the reference gradients times the determinant.
         T ax[3], b0[3], b1[3], d0[3], d1[3];
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
             // c: xi, eta, zeta, xi eta, xi zeta, eta zeta, xi eta zeta
-            ax[m] = c[m] + c[9 + m] * eta + (c[12 + m] + c[18 + m] * eta) * zeta;
-            b0[m] = c[3 + m] + c[15 + m] * zeta;
-            b1[m] = c[9 + m] + c[18 + m] * zeta;
-            d0[m] = c[6 + m] + c[15 + m] * eta;
-            d1[m] = c[12 + m] + c[18 + m] * eta;
+            ax[m] = mad(mad(c[18 + m], eta, c[12 + m]), zeta, mad(c[9 + m], eta, c[m]));
+            b0[m] = mad(c[15 + m], zeta, c[3 + m]);
+            b1[m] = mad(c[18 + m], zeta, c[9 + m]);
+            d0[m] = mad(c[15 + m], eta, c[6 + m]);
+            d1[m] = mad(c[18 + m], eta, c[12 + m]);
         }
-        T* col = sB + el * SB + r;
-        T u0[N], u1[N], u2[N], o0[N], o1[N], o2[N];
+        T g0[3], g1[3], g2[3], y0[3], y1[3], z0[3], z1[3];
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            u0[i] = col[i * Q2];
-            u1[i] = col[(N + i) * Q2];
-            u2[i] = col[(2 * N + i) * Q2];
-            o0[i] = o1[i] = o2[i] = T(0);
+        for (int m = 0; m < 3; ++m) {
+            const int m1 = (m + 1) % 3, m2 = (m + 2) % 3;
+            g0[m] = mad(b0[m1], d0[m2], -(b0[m2] * d0[m1]));
+            g1[m] = mad(b0[m1], d1[m2], -(b0[m2] * d1[m1])) + mad(b1[m1], d0[m2], -(b1[m2] * d0[m1]));
+            g2[m] = mad(b1[m1], d1[m2], -(b1[m2] * d1[m1]));
+            y0[m] = mad(d0[m1], ax[m2], -(d0[m2] * ax[m1]));
+            y1[m] = mad(d1[m1], ax[m2], -(d1[m2] * ax[m1]));
+            z0[m] = mad(ax[m1], b0[m2], -(ax[m2] * b0[m1]));
+            z1[m] = mad(ax[m1], b1[m2], -(ax[m2] * b1[m1]));
         }
+        const T t0 = mad(ax[2], g0[2], mad(ax[1], g0[1], ax[0] * g0[0]));
+        const T t1 = mad(ax[2], g1[2], mad(ax[1], g1[1], ax[0] * g1[0]));
+        const T t2 = mad(ax[2], g2[2], mad(ax[1], g2[1], ax[0] * g2[0]));
+        T* col = sh + line * V + v;
+        Line<T, N> u0, u1, u2, o0, o1, o2;
+        {
+            T u[N];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            T val = L[q] * u0[0], ux = D[q] * u0[0], uy = L[q] * u1[0], uz = L[q] * u2[0];
+            for (int i = 0; i < N; ++i) u[i] = col[i * Q2 * V];
+            to_parity<T, N>(u, u0, ps, pt);
 #pragma unroll
-            for (int i = 1; i < N; ++i) {
-                val += L[i * Q + q] * u0[i];
-                ux += D[i * Q + q] * u0[i];
-                uy += L[i * Q + q] * u1[i];
-                uz += L[i * Q + q] * u2[i];
-            }
-            const T xi = gq[q];
-            T b[3], d[3], gx[3], gy[3], gz[3], V[3];
+            for (int i = 0; i < N; ++i) u[i] = col[(N + i) * Q2 * V];
+            to_parity<T, N>(u, u1, ps, pt);
+#pragma unroll
+            for (int i = 0; i < N; ++i) u[i] = col[(2 * N + i) * Q2 * V];
+            to_parity<T, N>(u, u2, ps, pt);
+        }
+        clear(o0);
+        clear(o1);
+        clear(o2);
+#pragma unroll UNROLL
+        for (int q = 0; q < H; ++q) {
+            const Rec<T, N> r{tab + q * 2 * N};
+            const T xi = gq[q], w = wq[q] * wyz;
+            const bool pair = Q % 2 == 0 || q < H - 1;
+            const T ve = even_l(r, u0), vo = odd_l(r, u0);
+            const T xe = even_d(r, u0), xo = odd_d(r, u0);
+            const T ye = even_l(r, u1), yo = odd_l(r, u1);
+            const T ze = even_l(r, u2), zo = odd_l(r, u2);
+            const T te = mad(t2, xi * xi, t0), to = t1 * xi;
+            T ge[3], go[3];
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-                b[m] = b0[m] + b1[m] * xi;
-                d[m] = d0[m] + d1[m] * xi;
+                ge[m] = mad(g2[m], xi * xi, g0[m]);
+                go[m] = g1[m] * xi;
             }
+            T f[2][4];
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int m1 = (m + 1) % 3, m2 = (m + 2) % 3;
-                gx[m] = b[m1] * d[m2] - b[m2] * d[m1];
-                gy[m] = d[m1] * ax[m2] - d[m2] * ax[m1];
-                gz[m] = ax[m1] * b[m2] - ax[m2] * b[m1];
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && !pair) {
+                    f[1][0] = f[1][1] = f[1][2] = f[1][3] = T(0);
+                    continue;
+                }
+                const T x = h == 0 ? xi : -xi;
+                T gx[3], gy[3], gz[3], W[3];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    gx[m] = h == 0 ? ge[m] + go[m] : ge[m] - go[m];
+                    gy[m] = mad(y1[m], x, y0[m]);
+                    gz[m] = mad(z1[m], x, z0[m]);
+                }
+                const T det = h == 0 ? te + to : te - to;
+                const T ux = h == 0 ? xe + xo : xe - xo, uy = h == 0 ? ye + yo : ye - yo;
+                const T uz = h == 0 ? ze + zo : ze - zo, val = h == 0 ? ve + vo : ve - vo;
+                const T s = w * recip(det);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) W[m] = s * mad(gz[m], uz, mad(gy[m], uy, gx[m] * ux));
+                f[h][0] = mad(gx[2], W[2], mad(gx[1], W[1], gx[0] * W[0]));
+                f[h][1] = mad(gy[2], W[2], mad(gy[1], W[1], gy[0] * W[0]));
+                f[h][2] = mad(gz[2], W[2], mad(gz[1], W[1], gz[0] * W[0]));
+                f[h][3] = (a.lambda * w) * (det * val);
             }
-            const T det = ax[0] * gx[0] + ax[1] * gx[1] + ax[2] * gx[2];
-            const T w = wq[q] * wyz;
-            const T s = w * recip(det);
-#pragma unroll
-            for (int m = 0; m < 3; ++m) V[m] = s * (gx[m] * ux + gy[m] * uy + gz[m] * uz);
-            const T fx = gx[0] * V[0] + gx[1] * V[1] + gx[2] * V[2];
-            const T fy = gy[0] * V[0] + gy[1] * V[1] + gy[2] * V[2];
-            const T fz = gz[0] * V[0] + gz[1] * V[1] + gz[2] * V[2];
-            const T fm = a.lambda * w * det * val;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                o0[i] += D[i * Q + q] * fx;
-                o0[i] += L[i * Q + q] * fm;
-                o1[i] += L[i * Q + q] * fy;
-                o2[i] += L[i * Q + q] * fz;
-            }
+            add_d(r, f[0][0] + f[1][0], f[0][0] - f[1][0], o0);
+            add_l(r, f[0][3] + f[1][3], f[0][3] - f[1][3], o0);
+            add_l(r, f[0][1] + f[1][1], f[0][1] - f[1][1], o1);
+            add_l(r, f[0][2] + f[1][2], f[0][2] - f[1][2], o2);
         }
+        {
+            T u[N];
+            from_parity<T, N>(o0, u, ps, pt);
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-            col[i * Q2] = o0[i];
-            col[(N + i) * Q2] = o1[i];
-            col[(2 * N + i) * Q2] = o2[i];
+            for (int i = 0; i < N; ++i) col[i * Q2 * V] = u[i];
+            from_parity<T, N>(o1, u, ps, pt);
+#pragma unroll
+            for (int i = 0; i < N; ++i) col[(N + i) * Q2 * V] = u[i];
+            from_parity<T, N>(o2, u, ps, pt);
+#pragma unroll
+            for (int i = 0; i < N; ++i) col[(2 * N + i) * Q2 * V] = u[i];
         }
     }
     __syncthreads();
     // y back
-    for (int t = tid; t < EPB * N * Q; t += NT) {
-        const int el = t / (N * Q), r = t % (N * Q), qz = r / N, i = r % N;
-        const T* in = sB + el * SB + i * Q2 + qz;
-        T c0[Q], c1[Q], c2[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            c0[q] = in[q * Q];
-            c1[q] = in[N * Q2 + q * Q];
-            c2[q] = in[2 * N * Q2 + q * Q];
-        }
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            T s0 = L[j * Q] * c0[0], s1 = L[j * Q] * c2[0];
-            s0 += D[j * Q] * c1[0];
-#pragma unroll
-            for (int q = 1; q < Q; ++q) {
-                s0 += L[j * Q + q] * c0[q];
-                s0 += D[j * Q + q] * c1[q];
-                s1 += L[j * Q + q] * c2[q];
+    {
+        const const_ptr<T> tab = fresh(a.tabs);
+        Line<T, N> l0, l1;
+        clear(l0);
+        clear(l1);
+        if (line < N * Q) {
+            const T* in = sh + (li * Q2 + lq) * V + v;
+#pragma unroll UNROLL
+            for (int q = 0; q < H; ++q) {
+                const Rec<T, N> r{tab + q * 2 * N};
+                const bool pair = Q % 2 == 0 || q < H - 1;
+                const T a0 = in[q * Q * V], a1 = in[(N * Q2 + q * Q) * V], a2 = in[(2 * N * Q2 + q * Q) * V];
+                const T b0 = pair ? in[(Q - 1 - q) * Q * V] : T(0);
+                const T b1 = pair ? in[(N * Q2 + (Q - 1 - q) * Q) * V] : T(0);
+                const T b2 = pair ? in[(2 * N * Q2 + (Q - 1 - q) * Q) * V] : T(0);
+                add_l(r, a0 + b0, a0 - b0, l0);
+                add_d(r, a1 + b1, a1 - b1, l0);
+                add_l(r, a2 + b2, a2 - b2, l1);
             }
-            sA[el * SA + r * N + j] = s0;
-            sA[el * SA + Q * N2 + r * N + j] = s1;
+        }
+        __syncthreads();
+        if (line < N * Q) {
+            T u[N];
+            from_parity<T, N>(l0, u, ps, pt);
+#pragma unroll
+            for (int j = 0; j < N; ++j) sh[(line * N + j) * V + v] = u[j];
+            from_parity<T, N>(l1, u, ps, pt);
+#pragma unroll
+            for (int j = 0; j < N; ++j) sh[(Q * N2 + line * N + j) * V + v] = u[j];
         }
     }
     __syncthreads();
     // z back
-    for (int t = tid; t < EPB * N2; t += NT) {
-        const int el = t / N2, ij = t % N2;
-        T d0[Q], d1[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            d0[q] = sA[el * SA + q * N2 + ij];
-            d1[q] = sA[el * SA + (Q + q) * N2 + ij];
-        }
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            T s = L[k * Q] * d0[0];
-            s += D[k * Q] * d1[0];
-#pragma unroll
-            for (int q = 1; q < Q; ++q) {
-                s += L[k * Q + q] * d0[q];
-                s += D[k * Q + q] * d1[q];
+    {
+        const const_ptr<T> tab = fresh(a.tabs);
+        Line<T, N> l;
+        clear(l);
+        if (line < N2) {
+#pragma unroll UNROLL
+            for (int q = 0; q < H; ++q) {
+                const Rec<T, N> r{tab + q * 2 * N};
+                const bool pair = Q % 2 == 0 || q < H - 1;
+                const T a0 = sh[(q * N2 + line) * V + v], a1 = sh[((Q + q) * N2 + line) * V + v];
+                const T b0 = pair ? sh[((Q - 1 - q) * N2 + line) * V + v] : T(0);
+                const T b1 = pair ? sh[((2 * Q - 1 - q) * N2 + line) * V + v] : T(0);
+                add_l(r, a0 + b0, a0 - b0, l);
+                add_d(r, a1 + b1, a1 - b1, l);
             }
-            sB[el * SB + ij * N + k] = s;
+        }
+        __syncthreads();
+        if (line < N2) {
+            T u[N];
+            from_parity<T, N>(l, u, ps, pt);
+#pragma unroll
+            for (int k = 0; k < N; ++k) sh[(line * N + k) * V + v] = u[k];
         }
     }
     __syncthreads();
@@ -281,7 +470,7 @@ __global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs
 #pragma unroll
     for (int it = 0; it < ITER; ++it) {
         const int t = tid + it * NT;
-        if (t < cnt) ev[t] = sB[(t / NL) * SB + t % NL];
+        if (t < cnt) ev[t] = sh[(t % NL) * V + t / NL];
     }
 }
 
@@ -403,6 +592,7 @@ void launch_element_product(int mode, const SpmvArgs<T>& args, hipStream_t s) {
     ElemArgs<T> e;
     e.ne = E.ne; e.map = E.map.get(); e.v = a.v; e.ev = reinterpret_cast<T*>(E.ev.get());
     e.coef = form_coef<T>(E); e.tabs = form_tabs<T>(E); e.lambda = (T)E.lambda;
+    e.ps = (T)E.ps; e.pt = (T)E.pt;
     e.stop = a.stop;
     e.vnz = mode == SPMV_RINIT ? a.vnz : nullptr;
     if (e.coef == nullptr || e.tabs == nullptr) throw Error(GIAMG_EINVAL, "element form without this precision");
@@ -431,9 +621,33 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     E.order = p;
     E.ne = ne;
     E.lambda = lambda;
+    // Local positions of the kernel: the nodal basis keeps its order (position k
+    // mirrors N - 1 - k).  The modal basis puts its two vertex modes at the ends
+    // and its bubbles (even bubble m = 2, 4, ... at k, odd one at N - 1 - k)
+    // inside: they are even or odd by themselves, so the pair transform of the
+    // inner positions is the identity there (ps = 0, pt = 1).
+    std::vector<int> pos(n1);   // position -> 1-D basis index
+    for (int k = 0; k < n1; ++k) pos[k] = k;
+    if (basis == GIAMG_BASIS_MODAL) {
+        pos[0] = 0;
+        pos[n1 - 1] = 1;
+        for (int k = 1; 2 * k <= p; ++k) pos[k] = 2 * k;
+        for (int k = 1; 2 * k + 1 <= p; ++k) pos[n1 - 1 - k] = 2 * k + 1;
+        E.ps = 0.0;
+        E.pt = 1.0;
+    }
     std::vector<int32_t> map((size_t)m);
-    parallel_for(m, 1 << 16, [&](int64_t b, int64_t e) {
-        for (int64_t i = b; i < e; ++i) map[i] = cons[l2g[i]] ? -1 : l2g[i];
+    parallel_for(ne, 1 << 10, [&](int64_t b, int64_t en) {
+        for (int64_t e = b; e < en; ++e) {
+            const int32_t* g = l2g + e * n1 * n1 * n1;
+            int32_t* o = map.data() + e * n1 * n1 * n1;
+            for (int i = 0; i < n1; ++i)
+                for (int j = 0; j < n1; ++j)
+                    for (int k = 0; k < n1; ++k) {
+                        const int32_t node = g[(pos[i] * n1 + pos[j]) * n1 + pos[k]];
+                        o[(i * n1 + j) * n1 + k] = cons[node] ? -1 : node;
+                    }
+        }
     });
     E.map.alloc(m);
     GIAMG_HIP(hipMemcpyAsync(E.map.get(), map.data(), m * sizeof(int32_t), hipMemcpyHostToDevice, s));
@@ -456,9 +670,27 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     GIAMG_HIP(hipMemcpyAsync(E.coef.get(), coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice, s));
     std::vector<double> L, D, g, w;
     reference_tables(p, basis, L, D, g, w);
-    std::vector<double> tabs(L);
-    for (const auto* v : {&D, &g, &w}) tabs.insert(tabs.end(), v->begin(), v->end());
-    GIAMG_REQUIRE((int)tabs.size() == 2 * n1 * nq + 2 * nq, "unexpected size of the 1-D tables");
+    // per Gauss pair q, Q - 1 - q: even and odd parts of the values (Le from the
+    // even, Lo from the odd coefficients) and derivatives (De: odd in q, Do: even)
+    std::vector<double> tabs;
+    const int hq = (nq + 1) / 2, hn = (n1 + 1) / 2, on = n1 / 2;
+    auto part = [&](const std::vector<double>& M, int k, int q, double parity, double mirror) {
+        const bool pairs = basis != GIAMG_BASIS_MODAL || k == 0;
+        auto sym = [&](int i) {   // average of the two points' values with the part's symmetry in q
+            return 0.5 * (M[i * nq + q] + mirror * M[i * nq + nq - 1 - q]);
+        };
+        if (k == n1 - 1 - k) return sym(pos[k]);
+        if (!pairs) return sym(parity > 0 ? pos[k] : pos[n1 - 1 - k]);
+        return 0.5 * (sym(pos[k]) + parity * sym(pos[n1 - 1 - k]));
+    };
+    for (int q = 0; q < hq; ++q) {
+        for (int k = 0; k < hn; ++k) tabs.push_back(part(L, k, q, 1.0, 1.0));
+        for (int k = 0; k < on; ++k) tabs.push_back(part(L, k, q, -1.0, -1.0));
+        for (int k = 0; k < hn; ++k) tabs.push_back(part(D, k, q, 1.0, -1.0));
+        for (int k = 0; k < on; ++k) tabs.push_back(part(D, k, q, -1.0, 1.0));
+    }
+    for (const auto* v : {&g, &w}) tabs.insert(tabs.end(), v->begin(), v->end());
+    GIAMG_REQUIRE((int)tabs.size() == 2 * n1 * hq + 2 * nq, "unexpected size of the 1-D tables");
     E.tabs.alloc(tabs.size());
     GIAMG_HIP(hipMemcpyAsync(E.tabs.get(), tabs.data(), tabs.size() * sizeof(double), hipMemcpyHostToDevice, s));
     if (mixed) {

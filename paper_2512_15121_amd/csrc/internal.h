@@ -182,6 +182,7 @@ struct ElementForm {
     int order = 0;
     int64_t ne = 0;
     double lambda = 0.0;
+    double ps = 1.0, pt = -1.0;    // pair transform of the inner 1-D positions (build_element_form)
     DevBuf<int32_t> map;           // [ne][(order+1)^3] node, -1 = constrained
     DevBuf<int32_t> nptr, nent;    // per node: its entries of ev, ascending ([n + 1], one per map entry >= 0)
     DevBuf<double> coef, tabs;     // [ELEM_COEF][ne]; 1-D tables

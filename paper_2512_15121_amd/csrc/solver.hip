@@ -306,15 +306,15 @@ void noalloc_scratch_init();
 // Whether the fine operator's products run in the element form (element.hip):
 // where reading the assembled rows takes longer than the two kernels' own
 // latency, which grows with the order.  Measured (fine FP64 Chebyshev step,
-// element form / CSR): 8^3 p = 4 (6.4 M nonzeros) 14 / 20 us, 16^3 p = 4
-// (49 M) 26 / 116, 32^3 p = 4 (424 M) 123 / 943, 40^3 p = 2 53 / 78,
-// 13^3 p = 5 30 / 181, 8^3 p = 8 45 / 547; but 2^3 p = 10 (13 M) 40 / 28 and
-// 3^3 p = 8 (12 M) 30 / 29.  The rule looks at the operator alone, so the
-// product forms of the CSR arrays (staged, direct, lean, grouped) all leave
-// the same results behind.
+// element form / CSR): 9^3 p = 4 (10 M nonzeros) 12 / 24 us, 16^3 p = 4 (49 M)
+// 20 / 116, 32^3 p = 4 (424 M) 92 / 943, 21^3 p = 2 (4 M) 15 / 16, 40^3 p = 2
+// 49 / 78, 7^3 p = 5 14 / 31, 8^3 p = 8 21 / 547; a form's least time is 11 us at
+// p = 2 to 18 us at p = 10, a CSR step of 4 M nonzeros takes about 13 us.  The
+// rule looks at the operator alone, so the product forms of the CSR arrays
+// (staged, direct, lean, grouped) all leave the same results behind.
 static bool use_element_form(const Handle& H) {
     const int64_t p = H.porder, nl = (p + 1) * (p + 1) * (p + 1);
-    return p >= 2 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 200000 * p * p) &&
+    return p >= 2 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
            H.n_elem * nl < (int64_t(1) << 31);
 }
 

@@ -17,7 +17,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 # (n, p, basis, bc): one per order, above the size from which the form is used
-# (0.2 M p^2 and 4 M nonzeros); element counts that leave the last block of
+# (0.15 M p^2 and 4 M nonzeros); element counts that leave the last block of
 # several elements ragged, few and many elements per order, both block shapes
 CASES = [(21, 2, "nodal", "dirichlet"), (13, 3, "nodal", "pin"), (17, 3, "modal", "dirichlet"),
          (9, 4, "nodal", "dirichlet"), (9, 4, "modal", "pin"), (13, 4, "nodal", "dirichlet"),
