@@ -22,6 +22,7 @@
 #include <memory>
 
 #include "kernels.h"
+#include "row_epilogue.h"
 
 namespace giamg {
 
@@ -32,54 +33,6 @@ constexpr int DOT_ROWS = 256;       // rows per column-dot block (fixed)
 constexpr int MAX_K = 1024;
 constexpr int CHUNK = 4;            // graph replays between host checks
 constexpr int GROUP_MAX = 8;        // rows per row group of the group kernel
-
-template <typename T>
-struct SpmmArgs {
-    const int64_t* rp = nullptr;
-    const int32_t* ci = nullptr;
-    const T* val = nullptr;
-    int64_t n = 0;
-    int k = 1;
-    const T* v = nullptr;      // gathered block [ncols][k]
-    T* y = nullptr;
-    const T* f = nullptr;
-    const T* dinv = nullptr;   // per row
-    T* r = nullptr;
-    T* x = nullptr;
-    T c1 = 0, c2 = 0, inv_theta = 0, omega = 0;
-    int flags = 0;
-    const int* run = nullptr;  // skip all work when *run == 0
-    const int32_t* gptr = nullptr;   // row groups (spmm_group_kernel only)
-    const int32_t* grows = nullptr;
-    int64_t ngroups = 0;
-};
-
-// Row-local tail of a block product: acc = (A v)[row][col].
-template <typename T, int MODE>
-__device__ __forceinline__ void spmm_epilogue(const SpmmArgs<T>& a, int64_t row, int64_t col, T acc) {
-    const int64_t idx = row * a.k + col;
-    if constexpr (MODE == SPMV_PLAIN) {
-        a.y[idx] = acc;
-    } else if constexpr (MODE == SPMV_RESID) {
-        a.y[idx] = a.f[idx] - acc;
-    } else if constexpr (MODE == SPMV_ADD) {
-        a.y[idx] += acc;
-    } else if constexpr (MODE == SPMV_CHEB_INIT) {
-        const T res = a.dinv[row] * (a.f[idx] - acc);
-        a.r[idx] = res;
-        a.y[idx] = res * a.inv_theta;
-    } else if constexpr (MODE == SPMV_CHEB_STEP) {
-        const T rr = a.r[idx] - a.dinv[row] * acc;
-        const T dold = a.v[idx];
-        const T dn = a.c1 * dold + a.c2 * rr;
-        a.r[idx] = rr;
-        a.y[idx] = dn;
-        const T inc = (a.flags & CHEB_LAST) ? dold + dn : dold;
-        a.x[idx] = ((a.flags & CHEB_ASSIGN) ? T(0) : a.x[idx]) + inc;
-    } else if constexpr (MODE == SPMV_JACOBI) {
-        a.y[idx] = a.v[idx] + a.omega * a.dinv[row] * (a.f[idx] - acc);
-    }
-}
 
 // One wavefront covers RPW = 64 / KT rows; KT lanes per row take KT columns.
 template <typename T, int MODE, int KT, int WPB>
@@ -763,6 +716,8 @@ struct BatchState {
     std::vector<BatchLevel> lv;
     DevBuf<double> R, Z, P, Q, Rold;
     DevBuf<double> partial;   // [2][k][dot blocks] column-dot partials
+    bool elem = false;        // the fine products run in the element form
+    DevBuf<double> ev;        // its element results, per map entry and column (either precision)
     DevBuf<ColState> st;
     DevBuf<int> run;
     std::map<std::string, Tile> tiles;   // tuned tile per operator and precision
@@ -900,9 +855,29 @@ void with_groups(BatchCtx& c, const DevCSR& M, const std::string& key, Tile t, S
 template <typename T>
 Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 
+// Whether the block products of the fine operator run in the element form,
+// for every k or for none (a column's bits do not depend on the batch): from
+// p = 5, where the form is faster whatever k.  Measured (whole batched solves,
+// element form / CSR block products): 10^3 p = 5 k = 1 7.4 / 59 ms, k = 8 9.9 /
+// 46, k = 64 30 / 34 (mixed) and 45 / 50 (FP64); 8^3 p = 6 k = 48 13 / 23, k = 64
+// 21 / 36; 4^3 p = 6 k = 2 3.8 / 12.  At p = 4 the rows are a third as long and
+// 64 columns share each nonzero: 16^3 k = 64 43 / 27 (k = 8 still 4.9 / 12).
+bool block_element_form(const Handle& H) {
+    const int64_t nl = (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1);
+    return H.porder >= 5 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
+}
+
 template <typename T>
 void spmm(BatchCtx& c, int mode, const DevCSR& M, SpmmArgs<T> a, const std::string& key,
           double rowvecs) {
+    if (c.B.elem && &M == &c.H.levels[0].A) {
+        const ElementForm& E = c.H.levels[0].E;
+        if (c.count_bytes)
+            c.H.bytes += 4.0 * (2.0 * E.map.n + E.nptr.n) + ELEM_COEF * sizeof(T) * E.ne +
+                         sizeof(T) * (2.0 * E.map.n * c.k + (double)M.ncols * c.k + rowvecs * M.nrows * c.k);
+        launch_element_block<T>(mode, a, E, c.B.ev.get(), c.s());
+        return;
+    }
     const Tile t = tile_for<T>(c, M, key);
     if (c.count_bytes) c.H.bytes += spmm_bytes(M, c.k, sizeof(T), rowvecs);
     with_groups<T>(c, M, key, t, a);
@@ -991,7 +966,7 @@ void bsmooth(BatchCtx& c, size_t l, const T* f, T* x, bool zero_start, const T* 
                                                                     (T)(1.0 / theta), deg == 1, c.run);
         }
     } else {
-        const bool ap = e != nullptr;
+        const bool ap = e != nullptr && !(l == 0 && c.B.elem);   // A x costs less there
         const DevCSR& M = ap ? L.AP : L.A;
         SpmmArgs<T> a = bargs<T>(M, ap ? BL<T>::AP(L) : BL<T>::A(L), k, c.run);
         a.v = ap ? e : x; a.f = ap ? t : f; a.r = r; a.y = d[0]; a.dinv = BL<T>::dinv(L);
@@ -1194,6 +1169,11 @@ std::unique_ptr<BatchState> make_state(Handle& H, int k) {
         }
         B->lv.push_back(std::move(W));
     }
+    if (block_element_form(H)) {
+        ensure_element_form(H);
+        B->elem = true;
+        B->ev.alloc(H.levels[0].E.map.n * (size_t)k);
+    }
     const size_t tot = (size_t)H.n_nodes * k;
     B->R.alloc(tot); B->P.alloc(tot); B->Q.alloc(tot);
     if (!B->mixed) B->Z.alloc(tot);   // mixed precision: z stays in level 0's x32
@@ -1246,11 +1226,12 @@ void tune_all(Handle& H, BatchState& B, int k) {
     for (size_t l = 0; l < H.levels.size(); ++l) {
         Level& L = H.levels[l];
         const std::string sl = std::to_string(l);
-        tile_for<double>(t, L.A, "A" + sl);
+        const bool elem = l == 0 && B.elem;
+        if (!elem) tile_for<double>(t, L.A, "A" + sl);
         if (l + 1 == H.levels.size()) continue;
-        const bool ap = H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV;
+        const bool ap = H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV && !elem;
         if (B.mixed) {
-            tile_for<float>(t, L.A, "A" + sl);
+            if (!elem) tile_for<float>(t, L.A, "A" + sl);
             tile_for<float>(t, L.R, "R" + sl);
             tile_for<float>(t, L.P, "P" + sl);
             if (ap) tile_for<float>(t, L.AP, "AP" + sl);
@@ -1577,7 +1558,7 @@ int64_t session_device_bytes(const Session* S) {
     for (const auto& l : B.lv)
         b += (int64_t)(l.f.n + l.x.n + l.r.n + l.d0.n + l.d1.n + l.t.n) * 8 +
              (int64_t)(l.f32.n + l.x32.n + l.r32.n + l.d032.n + l.d132.n + l.t32.n) * 4;
-    b += (int64_t)(B.R.n + B.Z.n + B.P.n + B.Q.n + B.Rold.n + B.partial.n) * 8;
+    b += (int64_t)(B.R.n + B.Z.n + B.P.n + B.Q.n + B.Rold.n + B.partial.n + B.ev.n) * 8;
     b += (int64_t)(S->Bm.n + S->X.n) * 8;
     return b;
 }

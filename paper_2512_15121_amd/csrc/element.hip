@@ -45,7 +45,9 @@ struct ElemArgs {
     const T* coef = nullptr;         // [ELEM_COEF][ne] trilinear coefficients
     const T* tabs = nullptr;         // 1-D tables (element_tables)
     T lambda = 0, ps = 1, pt = -1;   // pair transform of the inner positions (element_tables)
+    int k = 1;                       // columns of v ([n][k]) and ev ([ne][nl][k])
     const int* stop = nullptr;
+    const int* run = nullptr;        // when set and zero, nothing to do
     const double* vnz = nullptr;     // when set and zero, v is +0: nothing to do
 };
 
@@ -194,14 +196,18 @@ __device__ __forceinline__ const_ptr<T> fresh(const T* p) {
     return (const_ptr<T>)(uintptr_t)p;
 }
 
-template <typename T, int P, bool WIDE>
-__global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs<T> a) {
+// A block of NT threads works on V elements side by side.  COLS: block vectors
+// of a.k columns, the V elements are (element, column) pairs, column fastest.
+template <typename T, int P, int NT, int V, bool COLS>
+__global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
 #pragma clang fp contract(off)
+    if (a.run != nullptr && *a.run == 0) return;
     if (a.stop != nullptr && *a.stop != 0) return;
     if (a.vnz != nullptr && *a.vnz == 0.0) return;
     constexpr int N = P + 1, Q = P + 2, N2 = N * N, NL = N2 * N, Q2 = Q * Q;
     constexpr int H = (Q + 1) / 2;                 // Gauss pairs, the middle point one of its own
-    constexpr int NT = elem_threads<P>(WIDE), V = elem_per_block<P>(WIDE);
+    static_assert(V * Q2 <= NT, "block shape");
+    constexpr int LINES = NT / V, CITER = (NL + LINES - 1) / LINES;   // COLS: nodal values per thread
     constexpr int ITER = (V * NL + NT - 1) / NT;
     constexpr int UNROLL = 2 * N * H * (int)sizeof(T) <= 240 ? H : 1;   // one step's tables in 60 scalar registers
     // one region, element fastest: nodal values [i][j][k], then [2][qz][i][j],
@@ -210,12 +216,30 @@ __global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs
     __shared__ T sh[V * 3 * N * Q2];
     const int tid = threadIdx.x;
     const int v = tid % V, line = tid / V;
-    const int64_t e0 = xcd_block(blockIdx.x, gridDim.x) * V;
-    const int cnt = (int)min((int64_t)V, a.ne - e0) * NL;
+    const int64_t first = xcd_block(blockIdx.x, gridDim.x) * V;   // element, or pair
+    const int64_t total = COLS ? a.ne * a.k : a.ne;
+    const int64_t mine = min(first + v, total - 1);
+    const int64_t e = COLS ? (total <= (int64_t)UINT32_MAX ? (uint32_t)mine / (uint32_t)a.k : mine / a.k) : mine;
+    const int64_t col0 = COLS ? mine - e * a.k : 0;
+    const int cnt = (int)min((int64_t)V, total - first) * NL;
     const T ps = a.ps, pt = a.pt;
     // gather
-    {
-        const int32_t* __restrict__ map = a.map + e0 * NL;
+    if constexpr (COLS) {
+        const int32_t* __restrict__ map = a.map + e * NL;
+        const T* __restrict__ vec = a.v + col0;
+        int32_t g[CITER];
+        T x[CITER];
+#pragma unroll
+        for (int it = 0; it < CITER; ++it) g[it] = map[min(line + it * LINES, NL - 1)];
+#pragma unroll
+        for (int it = 0; it < CITER; ++it) x[it] = vec[(int64_t)max(g[it], 0) * a.k];
+#pragma unroll
+        for (int it = 0; it < CITER; ++it) {
+            const int loc = line + it * LINES;
+            if (line < LINES && loc < NL) sh[loc * V + v] = g[it] >= 0 ? x[it] : T(0);
+        }
+    } else {
+        const int32_t* __restrict__ map = a.map + first * NL;
         const T* __restrict__ vec = a.v;
         int32_t g[ITER];
         T x[ITER];
@@ -229,7 +253,6 @@ __global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs
             if (t < V * NL) sh[(t % NL) * V + t / NL] = g[it] >= 0 ? x[it] : T(0);
         }
     }
-    const int64_t e = min(e0 + v, a.ne - 1);
     T c[ELEM_COEF];   // the element's geometry, used at the quadrature points
 #pragma unroll
     for (int m = 0; m < ELEM_COEF; ++m) c[m] = a.coef[m * a.ne + e];
@@ -466,11 +489,20 @@ __global__ void __launch_bounds__(elem_threads<P>(WIDE)) element_kernel(ElemArgs
         }
     }
     __syncthreads();
-    T* __restrict__ ev = a.ev + e0 * NL;
+    if constexpr (COLS) {
+        T* __restrict__ ev = a.ev + e * NL * a.k + col0;
 #pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-        const int t = tid + it * NT;
-        if (t < cnt) ev[t] = sh[(t % NL) * V + t / NL];
+        for (int it = 0; it < CITER; ++it) {
+            const int loc = line + it * LINES;
+            if (line < LINES && loc < NL && first + v < total) ev[(int64_t)loc * a.k] = sh[loc * V + v];
+        }
+    } else {
+        T* __restrict__ ev = a.ev + first * NL;
+#pragma unroll
+        for (int it = 0; it < ITER; ++it) {
+            const int t = tid + it * NT;
+            if (t < cnt) ev[t] = sh[(t % NL) * V + t / NL];
+        }
     }
 }
 
@@ -509,12 +541,19 @@ __global__ void __launch_bounds__(NODE_THREADS) element_node_kernel(SpmvArgs<T> 
 
 template <typename T, int P, bool WIDE>
 void launch_element_kernel(const ElemArgs<T>& a, hipEvent_t ev_start, hipStream_t s) {
-    constexpr int EPB = elem_per_block<P>(WIDE);
-    const dim3 grid((unsigned)((a.ne + EPB - 1) / EPB)), block(elem_threads<P>(WIDE));
+    constexpr int EPB = elem_per_block<P>(WIDE), NT = elem_threads<P>(WIDE);
+    const dim3 grid((unsigned)((a.ne + EPB - 1) / EPB)), block(NT);
     if (ev_start != nullptr)
-        hipExtLaunchKernelGGL((element_kernel<T, P, WIDE>), grid, block, 0, s, ev_start, nullptr, 0, a);
+        hipExtLaunchKernelGGL((element_kernel<T, P, NT, EPB, false>), grid, block, 0, s, ev_start, nullptr, 0, a);
     else
-        element_kernel<T, P, WIDE><<<grid, block, 0, s>>>(a);
+        element_kernel<T, P, NT, EPB, false><<<grid, block, 0, s>>>(a);
+}
+
+template <typename T, int P>
+void launch_element_columns(const ElemArgs<T>& a, hipStream_t s) {
+    constexpr int NT = P <= 9 ? 256 : 192, V = NT / ((P + 2) * (P + 2));
+    const int64_t pairs = a.ne * a.k;
+    element_kernel<T, P, NT, V, true><<<(unsigned)((pairs + V - 1) / V), NT, 0, s>>>(a);
 }
 
 template <typename T>
@@ -536,6 +575,47 @@ void launch_element_order(int p, const ElemArgs<T>& a, hipEvent_t ev_start, hipS
     }
 #undef GIAMG_ELEM
     GIAMG_HIP(hipGetLastError());
+}
+
+template <typename T>
+void launch_element_block_order(int p, const ElemArgs<T>& a, hipStream_t s) {
+    if (a.k == 1) {
+        launch_element_order<T>(p, a, nullptr, s);
+        return;
+    }
+#define GIAMG_ELEM(P) \
+    case P: launch_element_columns<T, P>(a, s); break;
+    switch (p) {
+        GIAMG_ELEM(5) GIAMG_ELEM(6) GIAMG_ELEM(7) GIAMG_ELEM(8) GIAMG_ELEM(9) GIAMG_ELEM(10)
+        default: throw Error(GIAMG_EINVAL, "element form of an unsupported order");
+    }
+#undef GIAMG_ELEM
+    GIAMG_HIP(hipGetLastError());
+}
+
+// The node step over k columns: one thread per node and column.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(NODE_THREADS) element_node_block_kernel(SpmmArgs<T> a,
+                                                                          const int32_t* __restrict__ ptr,
+                                                                          const int32_t* __restrict__ ent,
+                                                                          const T* __restrict__ ev) {
+    if (a.run != nullptr && *a.run == 0) return;
+    const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t idx = lb * NODE_THREADS + threadIdx.x;
+    if (idx >= a.n * a.k) return;
+    const int64_t row = idx <= (int64_t)UINT32_MAX ? (uint32_t)idx / (uint32_t)a.k : idx / a.k;
+    const int col = (int)(idx - row * a.k);
+    const int32_t s = ptr[row], e = ptr[row + 1];
+    T y = 0;
+    for (int32_t j = s; j < e; ++j) y += ev[(int64_t)ent[j] * a.k + col];
+    if (s == e) y = a.v[idx];
+    spmm_epilogue<T, MODE>(a, row, col, y);
+}
+
+template <typename T, int MODE>
+void launch_node_block(const SpmmArgs<T>& a, const ElementForm& E, const T* ev, hipStream_t s) {
+    const unsigned grid = (unsigned)((a.n * a.k + NODE_THREADS - 1) / NODE_THREADS);
+    element_node_block_kernel<T, MODE><<<grid, NODE_THREADS, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
 }
 
 template <typename T, int MODE>
@@ -610,6 +690,28 @@ void launch_element_product(int mode, const SpmvArgs<T>& args, hipStream_t s) {
     }
     GIAMG_HIP(hipGetLastError());
 }
+template <typename T>
+void launch_element_block(int mode, const SpmmArgs<T>& a, const ElementForm& E, double* ev, hipStream_t s) {
+    ElemArgs<T> e;
+    e.ne = E.ne; e.map = E.map.get(); e.v = a.v; e.ev = reinterpret_cast<T*>(ev);
+    e.coef = form_coef<T>(E); e.tabs = form_tabs<T>(E); e.lambda = (T)E.lambda;
+    e.ps = (T)E.ps; e.pt = (T)E.pt;
+    e.k = a.k; e.run = a.run;
+    if (e.coef == nullptr || e.tabs == nullptr) throw Error(GIAMG_EINVAL, "element form without this precision");
+    launch_element_block_order<T>(E.order, e, s);
+    switch (mode) {
+        case SPMV_PLAIN: launch_node_block<T, SPMV_PLAIN>(a, E, e.ev, s); break;
+        case SPMV_RESID: launch_node_block<T, SPMV_RESID>(a, E, e.ev, s); break;
+        case SPMV_CHEB_INIT: launch_node_block<T, SPMV_CHEB_INIT>(a, E, e.ev, s); break;
+        case SPMV_CHEB_STEP: launch_node_block<T, SPMV_CHEB_STEP>(a, E, e.ev, s); break;
+        case SPMV_JACOBI: launch_node_block<T, SPMV_JACOBI>(a, E, e.ev, s); break;
+        default: throw Error(GIAMG_EINVAL, "unknown block product mode of the element form");
+    }
+    GIAMG_HIP(hipGetLastError());
+}
+template void launch_element_block<double>(int, const SpmmArgs<double>&, const ElementForm&, double*, hipStream_t);
+template void launch_element_block<float>(int, const SpmmArgs<float>&, const ElementForm&, double*, hipStream_t);
+
 template void launch_element_product<double>(int, const SpmvArgs<double>&, hipStream_t);
 template void launch_element_product<float>(int, const SpmvArgs<float>&, hipStream_t);
 
@@ -715,7 +817,6 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     node_place_kernel<<<setup_grid(m), 256, 0, s>>>(m, E.map.get(), E.nptr.get(), counts.get(), E.nent.get());
     node_sort_kernel<<<setup_grid(n), 256, 0, s>>>(n, E.nptr.get(), E.nent.get());
     GIAMG_HIP(hipGetLastError());
-    E.ev.alloc((size_t)m);
     GIAMG_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
 }
 

@@ -176,7 +176,9 @@ void setup_row_blocks(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s);
 void setup_row_blocks32(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s);
 
 // Element form of the fine operator (element.hip): the product by sum
-// factorisation over the elements.  order == 0: not built.
+// factorisation over the elements.  order == 0: not built.  Read only once
+// built, except ev (the single-vector products' work array; block products
+// bring their own).
 constexpr int ELEM_COEF = 21;      // trilinear coefficients per element (without the constant)
 struct ElementForm {
     int order = 0;
@@ -211,7 +213,8 @@ struct Level {
     DevCSR A, P, R;                // P, R empty on the coarsest level
     DevCSR AP;                     // A P (rows of this level, columns of the next), kept
                                    // from the Galerkin product for the post-smoothing residual
-    ElementForm E;                 // fine level: its products run in this form where built
+    ElementForm E;                 // fine level: element form, where the products use it
+    bool elem_products = false;    // the single-vector products run in the element form
     DevBuf<double> dinv;
     DevBuf<float> dinv32;
     double lam_hat = 0.0;
@@ -274,6 +277,9 @@ struct Handle {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     ~Handle();
 };
+
+// Build the fine level's element form if it is not there (solver.hip).
+void ensure_element_form(Handle& H);
 
 // ---- host setup (setup_host.cpp) -------------------------------------------
 void gll_points(int p, std::vector<double>& x, std::vector<double>& w);

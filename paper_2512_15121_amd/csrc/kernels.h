@@ -124,11 +124,37 @@ struct SpmvArgs {
     const ElementForm* elem = nullptr;   // host only: the product runs in the element form
 };
 
+// Arguments of a block product over k columns (block vectors row-major [n][k]).
+template <typename T>
+struct SpmmArgs {
+    const int64_t* rp = nullptr;
+    const int32_t* ci = nullptr;
+    const T* val = nullptr;
+    int64_t n = 0;
+    int k = 1;
+    const T* v = nullptr;      // gathered block [ncols][k]
+    T* y = nullptr;
+    const T* f = nullptr;
+    const T* dinv = nullptr;   // per row
+    T* r = nullptr;
+    T* x = nullptr;
+    T c1 = 0, c2 = 0, inv_theta = 0, omega = 0;
+    int flags = 0;
+    const int* run = nullptr;  // skip all work when *run == 0
+    const int32_t* gptr = nullptr;   // row groups (spmm_group_kernel only)
+    const int32_t* grows = nullptr;
+    int64_t ngroups = 0;
+};
+
 // Element form: product in two kernels (nblk = element_blocks(n) row blocks
 // for the dot partials).
 int64_t element_blocks(int64_t n);
 template <typename T>
 void launch_element_product(int mode, const SpmvArgs<T>& a, hipStream_t s);
+// The block product over k columns; ev holds an element result per map entry
+// and column.  A column's bits do not depend on k.
+template <typename T>
+void launch_element_block(int mode, const SpmmArgs<T>& a, const ElementForm& E, double* ev, hipStream_t s);
 
 template <typename T>
 void launch_spmv(int mode, const SpmvArgs<T>& a, hipStream_t s);

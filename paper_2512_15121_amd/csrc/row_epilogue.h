@@ -152,4 +152,31 @@ __device__ __forceinline__ void block_sum_to0(double* red, int tid, double& a, d
 template <int MODE>
 constexpr int n_partials() { return MODE == SPMV_RINIT ? 2 : 1; }
 
+// Row-local tail of a block product: acc = (A v)[row][col].
+template <typename T, int MODE>
+__device__ __forceinline__ void spmm_epilogue(const SpmmArgs<T>& a, int64_t row, int64_t col, T acc) {
+    const int64_t idx = row * a.k + col;
+    if constexpr (MODE == SPMV_PLAIN) {
+        a.y[idx] = acc;
+    } else if constexpr (MODE == SPMV_RESID) {
+        a.y[idx] = a.f[idx] - acc;
+    } else if constexpr (MODE == SPMV_ADD) {
+        a.y[idx] += acc;
+    } else if constexpr (MODE == SPMV_CHEB_INIT) {
+        const T res = a.dinv[row] * (a.f[idx] - acc);
+        a.r[idx] = res;
+        a.y[idx] = res * a.inv_theta;
+    } else if constexpr (MODE == SPMV_CHEB_STEP) {
+        const T rr = a.r[idx] - a.dinv[row] * acc;
+        const T dold = a.v[idx];
+        const T dn = a.c1 * dold + a.c2 * rr;
+        a.r[idx] = rr;
+        a.y[idx] = dn;
+        const T inc = (a.flags & CHEB_LAST) ? dold + dn : dold;
+        a.x[idx] = ((a.flags & CHEB_ASSIGN) ? T(0) : a.x[idx]) + inc;
+    } else if constexpr (MODE == SPMV_JACOBI) {
+        a.y[idx] = a.v[idx] + a.omega * a.dinv[row] * (a.f[idx] - acc);
+    }
+}
+
 }  // namespace giamg

@@ -166,7 +166,7 @@ SpmvArgs<T> args_of(const DevCSR& M, const T* val) {
 template <typename T>
 SpmvArgs<T> args_of_level(const Level& L, const T* val) {
     SpmvArgs<T> a = args_of<T>(L.A, val);
-    if (L.E.built()) {
+    if (L.elem_products) {
         a.elem = &L.E;
         a.nblk = element_blocks(a.n);
     }
@@ -177,7 +177,7 @@ SpmvArgs<T> args_of_level(const Level& L, const T* val) {
 // of block partials its DOT and RINIT epilogues write).
 int64_t product_blocks(const Level& L) {
     const DevCSR& M = L.A;
-    return L.E.built() ? element_blocks(M.nrows) : M.lean ? M.lean_nblk : M.gnblk > 0 ? M.gnblk : M.blk.nblk;
+    return L.elem_products ? element_blocks(M.nrows) : M.lean ? M.lean_nblk : M.gnblk > 0 ? M.gnblk : M.blk.nblk;
 }
 
 // Lean form for the operators with at most max_nnz nonzeros and no row longer
@@ -314,8 +314,17 @@ void noalloc_scratch_init();
 // (staged, direct, lean, grouped) all leave the same results behind.
 static bool use_element_form(const Handle& H) {
     const int64_t p = H.porder, nl = (p + 1) * (p + 1) * (p + 1);
-    return p >= 2 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
+    return p >= 2 && p <= 10 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
            H.n_elem * nl < (int64_t(1) << 31);
+}
+
+void ensure_element_form(Handle& H) {
+    Level& L = H.levels[0];
+    if (L.E.built()) return;
+    ElementForm E;
+    build_element_form(E, H.corners, H.l2g.data(), H.n_elem, H.porder, H.n_nodes, H.lambda, H.constrained,
+                       H.opts.basis, H.opts.precision == GIAMG_PREC_MIXED, H.stream);
+    L.E = std::move(E);
 }
 
 void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
@@ -364,7 +373,9 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     }
     if (use_element_form(H)) {
         Level& L = H.levels.back();
-        build_element_form(L.E, H.corners, l2g, ne, H.porder, n, H.lambda, H.constrained, o.basis, mixed, H.stream);
+        ensure_element_form(H);
+        L.E.ev.alloc(L.E.map.n);
+        L.elem_products = true;
     }
     H.setup_ms[0] = ms_since(t0);
     // p-levels
@@ -485,7 +496,7 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     int64_t maxn = 1, maxblk = 1;
     for (auto& L : H.levels) {
         maxn = std::max(maxn, L.n);
-        if (L.E.built()) maxblk = std::max(maxblk, element_blocks(L.n));
+        if (L.elem_products) maxblk = std::max(maxblk, element_blocks(L.n));
         for (const DevCSR* M : {&L.A, &L.P, &L.R, &L.AP})
             maxblk = std::max({maxblk, M->blk.nblk, M->blk32.nblk, M->gnblk, M->lean_nblk});
     }
@@ -892,7 +903,7 @@ void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false) {
     }
     Phase ph(H, GIAMG_PHASE_SMOOTH);
     Phase ph0(H, l == 0 ? GIAMG_PHASE_FIRST_SMOOTH : -1);
-    if (L.E.built())   // A x costs less than (A P) e there
+    if (L.elem_products)   // A x costs less than (A P) e there
         smooth<T>(H, L, f, x, false);
     else
         smooth<T>(H, L, f, x, false, LV<T>::t(L), LV<T>::x(C));

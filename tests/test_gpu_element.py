@@ -55,3 +55,31 @@ def test_element_products_match_assembled_rows(n, p, basis, bc):
         s.apply("residual", 0, ft, xt, out=z, fp32=fp32)
         assert torch.equal(y, z)                             # the same bits every time
     s.close()
+
+
+# (n, p, basis, precision): every order of the block products' element form
+BATCHES = [(4, 5, "nodal", "mixed"), (3, 6, "modal", "fp64"), (3, 7, "nodal", "mixed"), (2, 8, "nodal", "fp64"),
+           (2, 9, "nodal", "mixed"), (2, 10, "nodal", "fp64")]
+
+
+@pytest.mark.parametrize("n,p,basis,precision", BATCHES)
+def test_element_block_columns_alone_and_together(n, p, basis, precision):
+    """A column gives the same bits alone (a block of whole elements), among
+    2 and among 70 (blocks of (element, column) pairs that cross elements and
+    end ragged), and agrees with the single solve of the same system: both
+    stop at a relative residual of 1e-10 of the same operator, 1e-8 apart at
+    most."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=6, basis=basis)
+    s = Solver(m.coords, m.l2g, p, 2.0, Options(precision=precision, basis=basis))
+    B = torch.from_numpy(synth.normal_rhs(m.n_nodes * 70, 8).reshape(m.n_nodes, 70)).to("cuda:0")
+    X, infos = s.solve_batch(B)
+    assert all(i.status == 0 and i.true_relres < 1e-9 for i in infos)
+    for cols in ((0,), (41,), (69, 3)):
+        Xc, ic = s.solve_batch(B[:, list(cols)].contiguous())
+        for j, c in enumerate(cols):
+            assert ic[j].iters == infos[c].iters and torch.equal(Xc[:, j], X[:, c]), (cols, c)
+    x, _ = s.solve(B[:, 41].contiguous())
+    assert torch.linalg.norm(x - X[:, 41]) <= 1e-8 * torch.linalg.norm(x)
+    s.close()
