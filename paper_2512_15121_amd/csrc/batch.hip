@@ -864,7 +864,7 @@ Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 // 64 columns share each nonzero: 16^3 k = 64 43 / 27 (k = 8 still 4.9 / 12).
 bool block_element_form(const Handle& H) {
     const int64_t nl = (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1);
-    return H.porder >= 5 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
+    return element_form_allowed(H) && H.porder >= 5 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
 }
 
 template <typename T>

@@ -281,6 +281,16 @@ struct Handle {
 // Build the fine level's element form if it is not there (solver.hip).
 void ensure_element_form(Handle& H);
 
+// Whether products of the fine operator may run in the element form.  Not in
+// mixed precision with one pinned node: there the constant is held by that node
+// alone, and the rounding of the FP32 cycle, not its convergence, decides how far
+// the solution is shifted (any other rounding, of the FP64 products too, moves
+// it by 1e-10 to 2e-8 of itself at a tolerance of 1e-10).  These handles keep the
+// assembled rows, and with them their solutions to the last bit.
+inline bool element_form_allowed(const Handle& H) {
+    return !(H.opts.precision == GIAMG_PREC_MIXED && H.opts.bc == GIAMG_BC_PIN);
+}
+
 // ---- host setup (setup_host.cpp) -------------------------------------------
 void gll_points(int p, std::vector<double>& x, std::vector<double>& w);
 void gauss_points(int m, std::vector<double>& x, std::vector<double>& w);

@@ -314,7 +314,7 @@ void noalloc_scratch_init();
 // (staged, direct, lean, grouped) all leave the same results behind.
 static bool use_element_form(const Handle& H) {
     const int64_t p = H.porder, nl = (p + 1) * (p + 1) * (p + 1);
-    return p >= 2 && p <= 10 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
+    return element_form_allowed(H) && p >= 2 && p <= 10 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
            H.n_elem * nl < (int64_t(1) << 31);
 }
 

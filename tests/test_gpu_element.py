@@ -31,7 +31,9 @@ def test_element_products_match_assembled_rows(n, p, basis, bc):
     import torch
     from paper_2512_15121_amd import Options, Solver
     m = synth.hex_mesh(n, p, perturb=0.1, seed=5, basis=basis)
-    s = Solver(m.coords, m.l2g, p, 2.0, Options(precision="mixed", basis=basis, bc=bc))
+    # mixed handles with a pinned node keep the assembled rows (the constant's mode)
+    precision = "fp64" if bc == "pin" else "mixed"
+    s = Solver(m.coords, m.l2g, p, 2.0, Options(precision=precision, basis=basis, bc=bc))
     _, by = s.time_kernel("spmv", 0, 1)
     d = s.level(0)
     assert by < 8 * d["nnz_A"], "the product reads the assembled values"
@@ -40,6 +42,8 @@ def test_element_products_match_assembled_rows(n, p, basis, bc):
     rng = np.random.default_rng(7)
     x, f = rng.standard_normal(d["rows"]), rng.standard_normal(d["rows"])
     for dt, eps, fp32 in ((torch.float64, 2.0 ** -53, False), (torch.float32, 2.0 ** -24, True)):
+        if fp32 and precision != "mixed":
+            continue
         xt, ft = (torch.from_numpy(v).to(dt).to("cuda:0") for v in (x, f))
         xh, fh = xt.double().cpu().numpy(), ft.double().cpu().numpy()
         bound = (6 * (p + 2) + 40) * 64 * eps * np.max(abs(A) @ np.abs(xh))
@@ -83,3 +87,22 @@ def test_element_block_columns_alone_and_together(n, p, basis, precision):
     x, _ = s.solve(B[:, 41].contiguous())
     assert torch.linalg.norm(x - X[:, 41]) <= 1e-8 * torch.linalg.norm(x)
     s.close()
+
+
+def test_pinned_mixed_handles_keep_the_assembled_rows():
+    """One pinned node holds the constant of a pure Neumann problem: in mixed
+    precision the FP32 cycle's rounding decides the solution's shift, so single
+    and batched products of such handles stay with the assembled rows, whose
+    bits direct_gathers = 1 and the forced block shapes share."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(8, 5, perturb=0.1, seed=5)
+    B = torch.from_numpy(synth.pinned_normal_batch(m.n_nodes, 3, 9)).to("cuda:0")
+    x, X = [], []
+    for kw in ({}, {"direct_gathers": True, "batch_kernel": "lanes"}):
+        s = Solver(m.coords, m.l2g, 5, 0.0, Options(precision="mixed", bc="pin", **kw))
+        assert s.time_kernel("spmv", 0, 1)[1] >= 8 * s.level(0)["nnz_A"]
+        x.append(s.solve(B[:, 1].contiguous())[0])
+        X.append(s.solve_batch(B)[0])
+        s.close()
+    assert torch.equal(x[0], x[1]) and torch.equal(X[0], X[1])
