@@ -855,16 +855,18 @@ void with_groups(BatchCtx& c, const DevCSR& M, const std::string& key, Tile t, S
 template <typename T>
 Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 
-// Whether the block products of the fine operator run in the element form,
-// for every k or for none (a column's bits do not depend on the batch): from
-// p = 5, where the form is faster whatever k.  Measured (whole batched solves,
-// element form / CSR block products): 10^3 p = 5 k = 1 7.4 / 59 ms, k = 8 9.9 /
-// 46, k = 64 30 / 34 (mixed) and 45 / 50 (FP64); 8^3 p = 6 k = 48 13 / 23, k = 64
-// 21 / 36; 4^3 p = 6 k = 2 3.8 / 12.  At p = 4 the rows are a third as long and
-// 64 columns share each nonzero: 16^3 k = 64 43 / 27 (k = 8 still 4.9 / 12).
+// Whether the block products of the fine operator run in the element form, for
+// every k or for none (a column's bits do not depend on the batch): by matrix
+// instructions on the elements' matrices up to p = 4, by sum factorisation from
+// p = 5, where an element's matrix outgrows what it saves.  Measured (whole
+// batched solves, element form / CSR block products, mixed precision): 20^3 p = 3
+// k = 64 15.6 / 19.1 ms, k = 8 6.6 / 14.8, k = 1 5.5 / 13; 16^3 p = 4 k = 64 20.5 / 26.9,
+// 11^3 p = 4 k = 8 4.8 / 12.2; 16^3 p = 2 k = 64 4.4 / 4.6, k = 16 3.1 / 3.7; 10^3 p = 5
+// k = 64 30 / 34, k = 8 9.9 / 46; 8^3 p = 6 k = 48 13 / 23.  Sum factorisation at p = 4
+// loses at k = 64 (16^3: 43 ms).
 bool block_element_form(const Handle& H) {
     const int64_t nl = (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1);
-    return element_form_allowed(H) && H.porder >= 5 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
+    return element_form_allowed(H) && H.porder >= 2 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
 }
 
 template <typename T>
@@ -1171,6 +1173,7 @@ std::unique_ptr<BatchState> make_state(Handle& H, int k) {
     }
     if (block_element_form(H)) {
         ensure_element_form(H);
+        if (H.porder <= 4) build_element_matrices(H.levels[0].E, B->mixed, H.stream);
         B->elem = true;
         B->ev.alloc(H.levels[0].E.map.n * (size_t)k);
     }

@@ -36,6 +36,17 @@ namespace {
 
 constexpr int NODE_THREADS = 256;
 
+// Rows (and columns) of an element's matrix in the dense form: (p + 1)^3 to whole tiles of 16.
+constexpr int dense_rows(int p) { return ((p + 1) * (p + 1) * (p + 1) + 15) / 16 * 16; }
+// Where entry (i, j) of an nlp x nlp element matrix lies in its tiles: column
+// step t, row tile r, lane 16 g + row, column b of the lane's KB.
+template <typename T>
+__host__ __device__ constexpr int element_tile(int nlp, int i, int j) {
+    const int kb = 16 / (int)sizeof(T);
+    const int t = j / (4 * kb), g = j / kb % 4, b = j % kb;
+    return ((t * (nlp / 16) + i / 16) * 64 + g * 16 + i % 16) * kb + b;
+}
+
 template <typename T>
 struct ElemArgs {
     int64_t ne = 0;
@@ -49,6 +60,8 @@ struct ElemArgs {
     const int* stop = nullptr;
     const int* run = nullptr;        // when set and zero, nothing to do
     const double* vnz = nullptr;     // when set and zero, v is +0: nothing to do
+    double* mat = nullptr;           // UNIT: element matrices in tiles
+    float* mat32 = nullptr;
 };
 
 // Every multiply-add is written out, so each instance of the kernel gives the
@@ -198,7 +211,10 @@ __device__ __forceinline__ const_ptr<T> fresh(const T* p) {
 
 // A block of NT threads works on V elements side by side.  COLS: block vectors
 // of a.k columns, the V elements are (element, column) pairs, column fastest.
-template <typename T, int P, int NT, int V, bool COLS>
+// UNIT (FP64, a.k = nl): the columns are the element's unit vectors and the
+// results, the columns of its matrix, go to the tiles of both precisions
+// (element_tile) instead of ev.
+template <typename T, int P, int NT, int V, bool COLS, bool UNIT = false>
 __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
 #pragma clang fp contract(off)
     if (a.run != nullptr && *a.run == 0) return;
@@ -229,10 +245,18 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
         const T* __restrict__ vec = a.v + col0;
         int32_t g[CITER];
         T x[CITER];
+        if constexpr (UNIT) {
 #pragma unroll
-        for (int it = 0; it < CITER; ++it) g[it] = map[min(line + it * LINES, NL - 1)];
+            for (int it = 0; it < CITER; ++it) {
+                g[it] = 0;
+                x[it] = line + it * LINES == (int)col0 ? T(1) : T(0);
+            }
+        } else {
 #pragma unroll
-        for (int it = 0; it < CITER; ++it) x[it] = vec[(int64_t)max(g[it], 0) * a.k];
+            for (int it = 0; it < CITER; ++it) g[it] = map[min(line + it * LINES, NL - 1)];
+#pragma unroll
+            for (int it = 0; it < CITER; ++it) x[it] = vec[(int64_t)max(g[it], 0) * a.k];
+        }
 #pragma unroll
         for (int it = 0; it < CITER; ++it) {
             const int loc = line + it * LINES;
@@ -489,7 +513,19 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
         }
     }
     __syncthreads();
-    if constexpr (COLS) {
+    if constexpr (UNIT) {
+        constexpr int NLP = dense_rows(P);
+#pragma unroll
+        for (int it = 0; it < CITER; ++it) {
+            const int loc = line + it * LINES;
+            if (line < LINES && loc < NL && first + v < total) {
+                const T x = sh[loc * V + v];
+                a.mat[e * NLP * NLP + element_tile<double>(NLP, loc, (int)col0)] = x;
+                if (a.mat32 != nullptr)
+                    a.mat32[e * NLP * NLP + element_tile<float>(NLP, loc, (int)col0)] = (float)x;
+            }
+        }
+    } else if constexpr (COLS) {
         T* __restrict__ ev = a.ev + e * NL * a.k + col0;
 #pragma unroll
         for (int it = 0; it < CITER; ++it) {
@@ -593,29 +629,255 @@ void launch_element_block_order(int p, const ElemArgs<T>& a, hipStream_t s) {
     GIAMG_HIP(hipGetLastError());
 }
 
-// The node step over k columns: one thread per node and column.
-template <typename T, int MODE>
+// ---------------------------------------------------------------------------
+// Dense form of the block products (p <= 4): an element's matrix, stored once,
+// times its nodal values of 16 columns by matrix instructions.  The matrix is
+// cut into tiles of 16 rows and four lane groups of KB columns, in the order the
+// instruction's left operand wants: lane 16 g + r of a tile holds row r and
+// columns KB g .. KB g + KB - 1 in one 16-byte load (KB = 2 in FP64, 4 in FP32),
+// and instruction b of the tile sums over the columns KB g + b of the four
+// groups.  The right operand's lane 16 g + c holds column c of the same nodes.
+// RS: waves that share the rows of one element and 16 columns (few columns);
+// the block's four waves cover 4 / RS tiles of 16 columns.  Every result is the
+// same sum in the same order whatever k, so a column's bits do not depend on it.
+// With RS = 1 the waves share the matrix through LDS in chunks of 16 KB, the next
+// one on its way from memory meanwhile; with RS > 1 each wave reads its own rows.
+//
+// Measured at k = 64: 20^3 p = 3 (0.26 GB of FP64 matrices and as much of results)
+// 113 us FP64 and 69 us FP32, 16^3 p = 4 194 and 108 us; every wave reading the
+// whole matrix by itself 139, 89 and 215 us.  The CSR block products, which
+// gather a row of the block vector per nonzero group, take 319, 143-185, about
+// 580 and 260 us (their epilogues included; the node step below adds 55 to 170).
+// At k = 8, 11^3 p = 4 FP64 (170 MB of matrices): 30 us, the CSR form 240.
+// ---------------------------------------------------------------------------
+template <typename T> struct Mfma;
+template <> struct Mfma<double> {
+    typedef double vec __attribute__((ext_vector_type(4)));
+    typedef double load __attribute__((ext_vector_type(2)));
+    static constexpr int KB = 2;
+    static __device__ __forceinline__ vec mul(double x, double y, vec c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int i) { return g + 4 * i; }   // of result register i
+};
+template <> struct Mfma<float> {
+    typedef float vec __attribute__((ext_vector_type(4)));
+    typedef float load __attribute__((ext_vector_type(4)));
+    static constexpr int KB = 4;
+    static __device__ __forceinline__ vec mul(float x, float y, vec c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int i) { return 4 * g + i; }
+};
+
+template <typename T, int P, int RS>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))) element_dense_kernel(ElemArgs<T> a, const T* __restrict__ mats) {
+    if (a.run != nullptr && *a.run == 0) return;
+    typedef Mfma<T> M;
+    constexpr int NL = (P + 1) * (P + 1) * (P + 1), NLP = dense_rows(P), KB = M::KB;
+    constexpr int RT = NLP / 16, TK = NLP / (4 * KB), RPW = RT / RS;
+    static_assert(RT % RS == 0 && 4 % RS == 0, "row tiles per wave");
+    const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+    const int c = lane % 16, g = lane / 16, r0 = (w % RS) * RPW;
+    const int64_t e = xcd_block(blockIdx.x, gridDim.x);
+    const int c0 = ((int)blockIdx.y * (4 / RS) + w / RS) * 16;
+    if (RS > 1 && c0 >= a.k) return;   // a whole wave without columns
+    const int32_t* __restrict__ map = a.map + e * NL;
+    const T* __restrict__ vec = a.v + min(c0 + c, a.k - 1);
+    const typename M::load* __restrict__ tiles =
+        reinterpret_cast<const typename M::load*>(mats + e * NLP * NLP) + r0 * WAVE + lane;
+    // RS > 1: this step's tiles and the next one's; RS == 1: the block's next
+    // chunk of TS steps, one 16-byte piece of it per thread and register
+    constexpr int TS = TK < 16 / RT ? TK : 16 / RT, PIECES = TS * RT * WAVE / 256;
+    typename M::load m[2][RS > 1 ? RPW : 1], next[RS > 1 ? 1 : PIECES];
+    __shared__ typename M::load chunk[RS > 1 ? 1 : 2][RS > 1 ? 1 : TS * RT * WAVE];
+    if constexpr (RS > 1) {
+#pragma unroll
+        for (int r = 0; r < RPW; ++r) m[0][r] = tiles[r * WAVE];
+    } else {
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) next[u] = tiles[(int)threadIdx.x - lane + u * 256];
+    }
+    T x[TK][KB];
+    int32_t node[TK][KB];
+#pragma unroll
+    for (int t = 0; t < TK; ++t)
+#pragma unroll
+        for (int b = 0; b < KB; ++b) node[t][b] = map[min((4 * t + g) * KB + b, NL - 1)];
+#pragma unroll
+    for (int t = 0; t < TK; ++t)
+#pragma unroll
+        for (int b = 0; b < KB; ++b) x[t][b] = vec[(int64_t)max(node[t][b], 0) * a.k];
+#pragma unroll
+    for (int t = 0; t < TK; ++t)
+#pragma unroll
+        for (int b = 0; b < KB; ++b)   // constrained nodes and padding: zero
+            if (node[t][b] < 0 || (4 * t + g) * KB + b >= NL) x[t][b] = T(0);
+    typename M::vec acc[RPW];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) acc[r] = typename M::vec{0, 0, 0, 0};
+    if constexpr (RS > 1) {
+#pragma unroll
+        for (int t = 0; t < TK; ++t) {
+            if (t + 1 < TK) {
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) m[(t + 1) & 1][r] = tiles[((t + 1) * RT + r) * WAVE];
+            }
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) acc[r] = M::mul(m[t & 1][r][b], x[t][b], acc[r]);
+        }
+    } else {
+#pragma unroll
+        for (int t0 = 0; t0 < TK; t0 += TS) {
+            typename M::load* buf = chunk[(t0 / TS) & 1];
+#pragma unroll
+            for (int u = 0; u < PIECES; ++u) buf[threadIdx.x + u * 256] = next[u];
+            __syncthreads();   // also: the buffer of the step after next is free
+            if (t0 + TS < TK) {
+#pragma unroll
+                for (int u = 0; u < PIECES; ++u)
+                    next[u] = tiles[(int)threadIdx.x - lane + (t0 + TS) * RT * WAVE + u * 256];
+            }
+#pragma unroll
+            for (int t = 0; t < TS; ++t) {
+                typename M::load s[RPW];
+#pragma unroll
+                for (int r = 0; r < RPW; ++r) s[r] = buf[(t * RT + r) * WAVE + lane];
+#pragma unroll
+                for (int b = 0; b < KB; ++b)
+#pragma unroll
+                    for (int r = 0; r < RPW; ++r) acc[r] = M::mul(s[r][b], x[t0 + t][b], acc[r]);
+            }
+        }
+    }
+    if (c0 + c < a.k) {
+        T* __restrict__ ev = a.ev + e * NL * a.k + c0 + c;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (r0 + r) * 16 + M::row(g, i);
+                if (row < NL) ev[(int64_t)row * a.k] = acc[r][i];
+            }
+    }
+}
+
+template <typename T, int P, int RS>
+void launch_dense(const ElemArgs<T>& a, const T* mats, hipStream_t s) {
+    const dim3 grid((unsigned)a.ne, (unsigned)((a.k + 64 / RS - 1) / (64 / RS)));
+    element_dense_kernel<T, P, RS><<<grid, 256, 0, s>>>(a, mats);
+}
+
+template <typename T>
+void launch_dense_order(int p, const ElemArgs<T>& a, const T* mats, hipStream_t s) {
+#define GIAMG_DENSE(P)                                                          \
+    case P:                                                                     \
+        if (a.k <= 16 && dense_rows(P) >= 64) launch_dense<T, P, dense_rows(P) >= 64 ? 4 : 2>(a, mats, s); \
+        else if (a.k <= 32) launch_dense<T, P, 2>(a, mats, s);                  \
+        else launch_dense<T, P, 1>(a, mats, s);                                 \
+        break;
+    switch (p) {
+        GIAMG_DENSE(2) GIAMG_DENSE(3) GIAMG_DENSE(4)
+        default: throw Error(GIAMG_EINVAL, "dense element form of an unsupported order");
+    }
+#undef GIAMG_DENSE
+    GIAMG_HIP(hipGetLastError());
+}
+
+template <int P>
+void launch_unit(const ElemArgs<double>& a, hipStream_t s) {
+    constexpr int NT = 256, V = NT / ((P + 2) * (P + 2));
+    const int64_t pairs = a.ne * a.k;
+    element_kernel<double, P, NT, V, true, true><<<(unsigned)((pairs + V - 1) / V), NT, 0, s>>>(a);
+}
+
+// The node step over k columns: one thread per node and VW columns, which it
+// loads and stores as one vector (16 bytes, or 1 column where k or a pointer
+// does not allow it).  Bound by its vectors: the FP32 Chebyshev step of 20^3
+// p = 3 at k = 64 moves 0.48 GB in 81 us (5.9 TB/s); with one column per thread,
+// 165 us, the dependent loads of the node lists bound it.
+template <typename T, int VW>
+struct alignas(VW * sizeof(T)) ColVec {
+    T c[VW];
+};
+template <typename T, int MODE, int VW>
 __global__ void __launch_bounds__(NODE_THREADS) element_node_block_kernel(SpmmArgs<T> a,
                                                                           const int32_t* __restrict__ ptr,
                                                                           const int32_t* __restrict__ ent,
                                                                           const T* __restrict__ ev) {
+#pragma clang fp contract(off)
     if (a.run != nullptr && *a.run == 0) return;
+    typedef ColVec<T, VW> Vec;
     const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
     const int64_t idx = lb * NODE_THREADS + threadIdx.x;
-    if (idx >= a.n * a.k) return;
-    const int64_t row = idx <= (int64_t)UINT32_MAX ? (uint32_t)idx / (uint32_t)a.k : idx / a.k;
-    const int col = (int)(idx - row * a.k);
+    const int kv = a.k / VW;
+    if (idx >= a.n * kv) return;
+    const int64_t row = idx <= (int64_t)UINT32_MAX ? (uint32_t)idx / (uint32_t)kv : idx / kv;
+    const int cv = (int)(idx - row * kv);
     const int32_t s = ptr[row], e = ptr[row + 1];
-    T y = 0;
-    for (int32_t j = s; j < e; ++j) y += ev[(int64_t)ent[j] * a.k + col];
-    if (s == e) y = a.v[idx];
-    spmm_epilogue<T, MODE>(a, row, col, y);
+    // row-local operands, loaded ahead of the sum
+    Vec f, r, v, x, y;
+    T dinv = 0;
+    auto at = [&](const T* p) { return reinterpret_cast<const Vec*>(p)[idx]; };
+    auto put = [&](T* p, const Vec& u) { reinterpret_cast<Vec*>(p)[idx] = u; };
+    if constexpr (MODE == SPMV_RESID || MODE == SPMV_CHEB_INIT || MODE == SPMV_JACOBI) f = at(a.f);
+    if constexpr (MODE == SPMV_CHEB_INIT || MODE == SPMV_CHEB_STEP || MODE == SPMV_JACOBI) dinv = a.dinv[row];
+    if constexpr (MODE == SPMV_CHEB_STEP || MODE == SPMV_JACOBI) v = at(a.v);
+    if constexpr (MODE == SPMV_CHEB_STEP) {
+        r = at(a.r);
+        if (!(a.flags & CHEB_ASSIGN)) x = at(a.x);
+    }
+    const Vec* __restrict__ el = reinterpret_cast<const Vec*>(ev) + cv;
+#pragma unroll
+    for (int i = 0; i < VW; ++i) y.c[i] = T(0);
+    for (int32_t j = s; j < e; ++j) {
+        const Vec t = el[(int64_t)ent[j] * kv];
+#pragma unroll
+        for (int i = 0; i < VW; ++i) y.c[i] += t.c[i];
+    }
+    if (s == e) y = at(a.v);   // constrained: identity row
+    Vec o, o2;
+#pragma unroll
+    for (int i = 0; i < VW; ++i) {
+        if constexpr (MODE == SPMV_PLAIN) {
+            o.c[i] = y.c[i];
+        } else if constexpr (MODE == SPMV_RESID) {
+            o.c[i] = f.c[i] - y.c[i];
+        } else if constexpr (MODE == SPMV_CHEB_INIT) {
+            o2.c[i] = dinv * (f.c[i] - y.c[i]);
+            o.c[i] = o2.c[i] * a.inv_theta;
+        } else if constexpr (MODE == SPMV_CHEB_STEP) {
+            r.c[i] = mad(-dinv, y.c[i], r.c[i]);
+            o.c[i] = mad(a.c1, v.c[i], a.c2 * r.c[i]);
+            const T inc = (a.flags & CHEB_LAST) ? v.c[i] + o.c[i] : v.c[i];
+            x.c[i] = ((a.flags & CHEB_ASSIGN) ? T(0) : x.c[i]) + inc;
+        } else if constexpr (MODE == SPMV_JACOBI) {
+            o.c[i] = mad(a.omega * dinv, f.c[i] - y.c[i], v.c[i]);
+        }
+    }
+    put(a.y, o);
+    if constexpr (MODE == SPMV_CHEB_INIT) put(a.r, o2);
+    if constexpr (MODE == SPMV_CHEB_STEP) {
+        put(a.r, r);
+        put(a.x, x);
+    }
 }
 
 template <typename T, int MODE>
 void launch_node_block(const SpmmArgs<T>& a, const ElementForm& E, const T* ev, hipStream_t s) {
-    const unsigned grid = (unsigned)((a.n * a.k + NODE_THREADS - 1) / NODE_THREADS);
-    element_node_block_kernel<T, MODE><<<grid, NODE_THREADS, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
+    constexpr int VW = 16 / (int)sizeof(T);
+    uintptr_t bits = 0;
+    for (const void* p : {(const void*)a.v, (const void*)a.y, (const void*)a.f, (const void*)a.r, (const void*)a.x,
+                          (const void*)ev})
+        bits |= reinterpret_cast<uintptr_t>(p);
+    const int vw = a.k % VW == 0 && bits % 16 == 0 ? VW : 1;
+    const unsigned grid = (unsigned)((a.n * (a.k / vw) + NODE_THREADS - 1) / NODE_THREADS);
+    if (vw == VW)
+        element_node_block_kernel<T, MODE, VW><<<grid, NODE_THREADS, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
+    else
+        element_node_block_kernel<T, MODE, 1><<<grid, NODE_THREADS, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
 }
 
 template <typename T, int MODE>
@@ -698,7 +960,13 @@ void launch_element_block(int mode, const SpmmArgs<T>& a, const ElementForm& E, 
     e.ps = (T)E.ps; e.pt = (T)E.pt;
     e.k = a.k; e.run = a.run;
     if (e.coef == nullptr || e.tabs == nullptr) throw Error(GIAMG_EINVAL, "element form without this precision");
-    launch_element_block_order<T>(E.order, e, s);
+    if (E.mat.get() != nullptr) {
+        const T* mats = nullptr;
+        if constexpr (sizeof(T) == 8) mats = E.mat.get(); else mats = E.mat32.get();
+        launch_dense_order<T>(E.order, e, mats, s);
+    } else {
+        launch_element_block_order<T>(E.order, e, s);
+    }
     switch (mode) {
         case SPMV_PLAIN: launch_node_block<T, SPMV_PLAIN>(a, E, e.ev, s); break;
         case SPMV_RESID: launch_node_block<T, SPMV_RESID>(a, E, e.ev, s); break;
@@ -714,6 +982,32 @@ template void launch_element_block<float>(int, const SpmmArgs<float>&, const Ele
 
 template void launch_element_product<double>(int, const SpmvArgs<double>&, hipStream_t);
 template void launch_element_product<float>(int, const SpmvArgs<float>&, hipStream_t);
+
+void build_element_matrices(ElementForm& E, bool mixed, hipStream_t s) {
+    if (E.mat.get() != nullptr) return;
+    GIAMG_REQUIRE(E.order >= 2 && E.order <= 4, "dense element form of an unsupported order");
+    const int64_t nl = (E.order + 1) * (E.order + 1) * (E.order + 1), nlp = dense_rows(E.order);
+    DevBuf<double> mat((size_t)(E.ne * nlp * nlp));
+    DevBuf<float> mat32;
+    GIAMG_HIP(hipMemsetAsync(mat.get(), 0, mat.n * sizeof(double), s));   // padding
+    if (mixed) {
+        mat32.alloc(mat.n);
+        GIAMG_HIP(hipMemsetAsync(mat32.get(), 0, mat32.n * sizeof(float), s));
+    }
+    ElemArgs<double> a;
+    a.ne = E.ne; a.map = E.map.get(); a.coef = E.coef.get(); a.tabs = E.tabs.get(); a.lambda = E.lambda;
+    a.ps = E.ps; a.pt = E.pt;
+    a.k = (int)nl; a.mat = mat.get(); a.mat32 = mat32.get();
+    switch (E.order) {
+        case 2: launch_unit<2>(a, s); break;
+        case 3: launch_unit<3>(a, s); break;
+        default: launch_unit<4>(a, s); break;
+    }
+    GIAMG_HIP(hipGetLastError());
+    GIAMG_HIP(hipStreamSynchronize(s));
+    E.mat = std::move(mat);
+    E.mat32 = std::move(mat32);
+}
 
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,

@@ -190,15 +190,19 @@ struct ElementForm {
     DevBuf<double> coef, tabs;     // [ELEM_COEF][ne]; 1-D tables
     DevBuf<float> coef32, tabs32;  // mixed precision
     DevBuf<double> ev;             // [ne][(order+1)^3] element results (either precision)
+    DevBuf<double> mat;            // element matrices in tiles (block products, order <= 4)
+    DevBuf<float> mat32;
     bool built() const { return order > 0; }
     int64_t device_bytes() const {
-        return (int64_t)(map.n + nptr.n + nent.n) * 4 + (int64_t)(coef.n + tabs.n + ev.n) * 8 +
-               (int64_t)(coef32.n + tabs32.n) * 4;
+        return (int64_t)(map.n + nptr.n + nent.n) * 4 + (int64_t)(coef.n + tabs.n + ev.n + mat.n) * 8 +
+               (int64_t)(coef32.n + tabs32.n + mat32.n) * 4;
     }
 };
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
                         hipStream_t s);
+// The matrices of every element (order <= 4), FP32 copies with mixed.
+void build_element_matrices(ElementForm& E, bool mixed, hipStream_t s);
 
 // ---- the hierarchy ----------------------------------------------------------
 struct BatchState;                 // batched-solve workspace (batch.hip)
@@ -280,7 +284,6 @@ struct Handle {
 
 // Build the fine level's element form if it is not there (solver.hip).
 void ensure_element_form(Handle& H);
-
 // Whether products of the fine operator may run in the element form.  Not in
 // mixed precision with one pinned node: there the constant is held by that node
 // alone, and the rounding of the FP32 cycle, not its convergence, decides how far

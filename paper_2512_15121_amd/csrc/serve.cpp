@@ -133,13 +133,17 @@ struct Server {
 
     // Device bytes of a problem's group: measured after its first setup,
     // before that an estimate (mean row length (p+2)^3 on hexahedral meshes;
-    // coarse levels, transfers and work vectors add ~25 %).
+    // coarse levels, transfers and work vectors add ~25 %; then the element
+    // form's results per slot and, up to p = 4, the elements' matrices).
     int64_t need(const Problem& P) const {
         if (P.known_bytes >= 0) return P.known_bytes;
         const double rows = (double)P.n_nodes;
         const double nnz = rows * (P.p + 2.0) * (P.p + 2.0) * (P.p + 2.0);
         const double vb = P.opts.precision == GIAMG_PREC_MIXED ? 16.0 : 12.0;
-        return (int64_t)(1.25 * (vb * nnz + 150.0 * rows + 80.0 * rows * o.slots));
+        const double nl = (P.p + 1.0) * (P.p + 1.0) * (P.p + 1.0);
+        const double mats = P.p <= 4 ? (nl + 5.0) * (nl + 5.0) * (vb - 4.0) : 0.0;   // FP64, FP32 copy if mixed
+        return (int64_t)(1.25 * (vb * nnz + 150.0 * rows + 80.0 * rows * o.slots) +
+                         (double)P.n_elem * (8.0 * nl * o.slots + mats));
     }
 
     void setup_main() {

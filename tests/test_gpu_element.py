@@ -61,16 +61,19 @@ def test_element_products_match_assembled_rows(n, p, basis, bc):
     s.close()
 
 
-# (n, p, basis, precision): every order of the block products' element form
-BATCHES = [(4, 5, "nodal", "mixed"), (3, 6, "modal", "fp64"), (3, 7, "nodal", "mixed"), (2, 8, "nodal", "fp64"),
+# (n, p, basis, precision): every order of the block products' element form (matrix
+# instructions up to p = 4, sum factorisation above)
+BATCHES = [(5, 2, "nodal", "mixed"), (4, 2, "modal", "fp64"), (3, 3, "nodal", "mixed"), (4, 3, "nodal", "fp64"),
+           (4, 4, "nodal", "mixed"), (3, 4, "modal", "fp64"), (4, 5, "nodal", "mixed"), (3, 6, "modal", "fp64"), (3, 7, "nodal", "mixed"), (2, 8, "nodal", "fp64"),
            (2, 9, "nodal", "mixed"), (2, 10, "nodal", "fp64")]
 
 
 @pytest.mark.parametrize("n,p,basis,precision", BATCHES)
 def test_element_block_columns_alone_and_together(n, p, basis, precision):
-    """A column gives the same bits alone (a block of whole elements), among
-    2 and among 70 (blocks of (element, column) pairs that cross elements and
-    end ragged), and agrees with the single solve of the same system: both
+    """A column gives the same bits alone, among 2, 20 and 70 (each split of rows
+    and columns over waves, tiles of 16 and 64 columns that end ragged, blocks
+    of (element, column) pairs that cross elements; vectors of one and of four
+    columns in the node step), and agrees with the single solve of the same system: both
     stop at a relative residual of 1e-10 of the same operator, 1e-8 apart at
     most."""
     import torch
@@ -80,7 +83,7 @@ def test_element_block_columns_alone_and_together(n, p, basis, precision):
     B = torch.from_numpy(synth.normal_rhs(m.n_nodes * 70, 8).reshape(m.n_nodes, 70)).to("cuda:0")
     X, infos = s.solve_batch(B)
     assert all(i.status == 0 and i.true_relres < 1e-9 for i in infos)
-    for cols in ((0,), (41,), (69, 3)):
+    for cols in ((0,), (41,), (69, 3), tuple(range(45, 65))):
         Xc, ic = s.solve_batch(B[:, list(cols)].contiguous())
         for j, c in enumerate(cols):
             assert ic[j].iters == infos[c].iters and torch.equal(Xc[:, j], X[:, c]), (cols, c)
