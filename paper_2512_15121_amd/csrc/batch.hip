@@ -368,34 +368,66 @@ __global__ void bconvert_kernel(int64_t total, const Tin* __restrict__ a, Tout* 
         b[i] = accumulate ? (Tout)(b[i] + (Tout)a[i]) : (Tout)a[i];
 }
 
-// Y = inv F for the dense coarsest inverse, FP64 accumulation, one row per
-// wave.  Each row sums over j in ascending order; the loads of COARSE_U
-// consecutive terms are issued before their multiply-adds, so the loop is
-// not one L2 round trip per term.
-constexpr int COARSE_U = 8;
+// Y = inv F for the dense coarsest inverse, FP64 accumulation.  A block forms 16
+// rows of 8 columns, one sum per thread; 256 terms of the sums at a time go
+// through LDS (the inverse is symmetric: rows r0 .. r0 + 15 of its column j are 16
+// neighbours of row j), the next ones on their way meanwhile, so a block waits
+// for memory once in 256 terms.  Each sum runs over j in ascending order, one
+// multiply-add per term.  1000 rows at k = 8: 18 us; one wave per row with
+// the columns on its lanes took 49 to 64 us (8 lanes of 64 at work).
+constexpr int CO_ROWS = 16, CO_COLS = 8, CO_TERMS = 256, CO_THREADS = CO_ROWS * CO_COLS;
 template <typename T>
-__global__ void __launch_bounds__(BW) bcoarse_kernel(int64_t n, int k, const double* __restrict__ inv,
-                                                     const T* __restrict__ f, T* __restrict__ y,
-                                                     const int* run) {
+__global__ void __launch_bounds__(CO_THREADS) bcoarse_kernel(int64_t n, int k, const double* __restrict__ inv,
+                                                             const T* __restrict__ f, T* __restrict__ y,
+                                                             const int* run) {
     if (run && *run == 0) return;
-    const int64_t row = blockIdx.x;
-    const double* __restrict__ ir = inv + row * n;
-    for (int64_t col = threadIdx.x; col < k; col += blockDim.x) {
-        double acc = 0.0;
-        int64_t j = 0;
-        for (; j + COARSE_U <= n; j += COARSE_U) {
-            double fv[COARSE_U], iv[COARSE_U];
+    __shared__ double si[CO_TERMS * CO_ROWS];
+    __shared__ double sf[CO_TERMS * CO_COLS];
+    constexpr int NI = CO_TERMS * CO_ROWS / CO_THREADS, NF = CO_TERMS * CO_COLS / CO_THREADS;
+    const int tid = threadIdx.x, c = tid % CO_COLS, r = tid / CO_COLS;
+    const int64_t r0 = (int64_t)blockIdx.x * CO_ROWS;
+    const int c0 = (int)blockIdx.y * CO_COLS;
+    double pi[NI];
+    T pf[NF];
+    auto fetch = [&](int64_t j0) {   // clamped: rows, columns and terms past the end are never used
 #pragma unroll
-            for (int u = 0; u < COARSE_U; ++u) {
-                fv[u] = (double)f[(j + u) * k + col];
-                iv[u] = ir[j + u];
+        for (int u = 0; u < NI; ++u) {
+            const int t = tid + u * CO_THREADS;
+            pi[u] = inv[min(j0 + t / CO_ROWS, n - 1) * n + min(r0 + t % CO_ROWS, n - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < NF; ++u) {
+            const int t = tid + u * CO_THREADS;
+            pf[u] = f[min(j0 + t / CO_COLS, n - 1) * k + min(c0 + t % CO_COLS, k - 1)];
+        }
+    };
+    double acc = 0.0;
+    fetch(0);
+    for (int64_t j0 = 0; j0 < n; j0 += CO_TERMS) {
+#pragma unroll
+        for (int u = 0; u < NI; ++u) si[tid + u * CO_THREADS] = pi[u];
+#pragma unroll
+        for (int u = 0; u < NF; ++u) sf[tid + u * CO_THREADS] = (double)pf[u];
+        __syncthreads();
+        if (j0 + CO_TERMS < n) fetch(j0 + CO_TERMS);
+        const int m = (int)min((int64_t)CO_TERMS, n - j0);
+        const double* a = si + r;
+        const double* b = sf + c;
+        int j = 0;
+        for (; j + 16 <= m; j += 16) {
+            double av[16], bv[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                av[u] = a[(j + u) * CO_ROWS];
+                bv[u] = b[(j + u) * CO_COLS];
             }
 #pragma unroll
-            for (int u = 0; u < COARSE_U; ++u) acc += iv[u] * fv[u];
+            for (int u = 0; u < 16; ++u) acc = __builtin_fma(av[u], bv[u], acc);
         }
-        for (; j < n; ++j) acc += ir[j] * (double)f[j * k + col];
-        y[row * k + col] = (T)acc;
+        for (; j < m; ++j) acc = __builtin_fma(a[j * CO_ROWS], b[j * CO_COLS], acc);
+        __syncthreads();
     }
+    if (r0 + r < n && c0 + c < k) y[(r0 + r) * k + c0 + c] = (T)acc;
 }
 
 static unsigned bgrid(int64_t total) {
@@ -409,10 +441,79 @@ struct ColState {
 };
 
 // ---- column dot products with a fixed row partition ---------------------------
-// partial[(c*nb + b)] = sum over rows of block b (in order) of a[i][c] * b[i][c]
-// (b FP64, or FP32 widened exactly)
-template <typename TB>
+// partial[c*nb + b] = the dot's share of rows 256 b .. 256 b + 255 of column c: four
+// sums over 64 rows in order, one multiply-add per row, added in order.  A block
+// takes 256 rows of DOT_COLS columns: all its loads are row by row (a wave covers
+// 8 rows of 8 columns) and independent, then one thread per quarter and column
+// adds in order from LDS.  (One thread per column and quarter walking down its 64
+// rows left 8 of 64 lanes at work at k = 8 and waited for every few loads:
+// 91 k rows at k = 8 in 19.6 us and 6.6 so, the update of x and r in 71 and 11.)
+constexpr int DOT_COLS = 8, DOT_PASS = 256 / DOT_COLS, DOT_PASSES = DOT_ROWS / DOT_PASS, DOT_PAD = 8;
+constexpr int DOT_LDS = DOT_ROWS * DOT_COLS + 4 * DOT_PAD;   // quarters shifted by 16 banks
+__device__ __forceinline__ int dot_slot(int row, int c) {
+    return row * DOT_COLS + c + row / (DOT_ROWS / 4) * DOT_PAD;
+}
+// Ordered block sums of u v over the rows in LDS; the caller has synchronised.
+__device__ __forceinline__ void dot_sum(const double* u, const double* v, int rows, int tid, double (*sh)[DOT_COLS],
+                                        int64_t col, int k, double* __restrict__ partial, int64_t nb) {
+    const int c = tid % DOT_COLS, w = tid / DOT_COLS;
+    if (w < 4) {
+        const int m = min(max(rows - w * (DOT_ROWS / 4), 0), DOT_ROWS / 4);
+        double s = 0.0;
+        if (m == DOT_ROWS / 4) {
+#pragma unroll 16
+            for (int i = 0; i < DOT_ROWS / 4; ++i) {
+                const int at = dot_slot(w * (DOT_ROWS / 4) + i, c);
+                s = __builtin_fma(u[at], v[at], s);
+            }
+        } else {
+            for (int i = 0; i < m; ++i) {
+                const int at = dot_slot(w * (DOT_ROWS / 4) + i, c);
+                s = __builtin_fma(u[at], v[at], s);
+            }
+        }
+        sh[w][c] = s;
+    }
+    __syncthreads();
+    if (tid < DOT_COLS && col < k)
+        partial[col * nb + blockIdx.x] = ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
+}
+
+// a.b into partial and, where a2 is set, a2.b into partial2 (b FP64, or FP32
+// widened exactly).
+template <typename TB, bool TWO>
 __global__ void __launch_bounds__(256) bdot_partial_kernel(int64_t n, int k, const double* __restrict__ a,
+                                                           const double* __restrict__ a2,
+                                                           const TB* __restrict__ b,
+                                                           double* __restrict__ partial,
+                                                           double* __restrict__ partial2, int64_t nb,
+                                                           const int* run) {
+    if (run && *run == 0) return;
+    __shared__ double sa[DOT_LDS], sb[DOT_LDS], sa2[TWO ? DOT_LDS : 1];
+    __shared__ double sh[2][4][DOT_COLS];
+    const int tid = threadIdx.x, c = tid % DOT_COLS, r = tid / DOT_COLS;
+    const int64_t col = (int64_t)blockIdx.y * DOT_COLS + c;
+    const int64_t r0 = (int64_t)blockIdx.x * DOT_ROWS;
+    const int rows = (int)min((int64_t)DOT_ROWS, n - r0);
+#pragma unroll
+    for (int u = 0; u < DOT_PASSES; ++u) {
+        const int i = u * DOT_PASS + r;
+        if (i < rows && col < k) {
+            const int64_t idx = (r0 + i) * k + col;
+            sa[dot_slot(i, c)] = a[idx];
+            sb[dot_slot(i, c)] = (double)b[idx];
+            if constexpr (TWO) sa2[dot_slot(i, c)] = a2[idx];
+        }
+    }
+    __syncthreads();
+    dot_sum(sa, sb, rows, tid, sh[0], col, k, partial, nb);
+    if constexpr (TWO) dot_sum(sa2, sb, rows, tid, sh[1], col, k, partial2, nb);
+}
+
+// The same partials with one thread per quarter and column, 64 columns side by
+// side: for wide batches of many rows (wide_columns), whose bandwidth it reaches.
+template <typename TB>
+__global__ void __launch_bounds__(256) bdot_wide_kernel(int64_t n, int k, const double* __restrict__ a,
                                                            const TB* __restrict__ b,
                                                            double* __restrict__ partial, int64_t nb,
                                                            const int* run) {
@@ -424,7 +525,7 @@ __global__ void __launch_bounds__(256) bdot_partial_kernel(int64_t n, int k, con
     double s = 0.0;
     if (col < k) {
         const int64_t r1 = (r0 + DOT_ROWS / 4 < n) ? r0 + DOT_ROWS / 4 : n;
-        for (int64_t i = r0; i < r1; ++i) s += a[i * k + col] * (double)b[i * k + col];
+        for (int64_t i = r0; i < r1; ++i) s = __builtin_fma(a[i * k + col], (double)b[i * k + col], s);
     }
     sh[wave][lane] = s;
     __syncthreads();
@@ -433,9 +534,9 @@ __global__ void __launch_bounds__(256) bdot_partial_kernel(int64_t n, int k, con
 }
 
 // The same partials for two dots that share b: a.b into partial, a2.b into
-// partial2 (each sum in the order of bdot_partial_kernel, so the same bits).
+// partial2 (each sum in the order of bdot_wide_kernel, so the same bits).
 template <typename TB>
-__global__ void __launch_bounds__(256) bdot2_partial_kernel(int64_t n, int k, const double* __restrict__ a,
+__global__ void __launch_bounds__(256) bdot2_wide_kernel(int64_t n, int k, const double* __restrict__ a,
                                                             const double* __restrict__ a2,
                                                             const TB* __restrict__ b,
                                                             double* __restrict__ partial,
@@ -451,8 +552,8 @@ __global__ void __launch_bounds__(256) bdot2_partial_kernel(int64_t n, int k, co
         const int64_t r1 = (r0 + DOT_ROWS / 4 < n) ? r0 + DOT_ROWS / 4 : n;
         for (int64_t i = r0; i < r1; ++i) {
             const double bi = (double)b[i * k + col];
-            s += a[i * k + col] * bi;
-            s2 += a2[i * k + col] * bi;
+            s = __builtin_fma(a[i * k + col], bi, s);
+            s2 = __builtin_fma(a2[i * k + col], bi, s2);
         }
     }
     sh[0][wave][lane] = s;
@@ -469,36 +570,78 @@ __device__ __forceinline__ double* state_field(ColState& s, int which) {
     return which == 0 ? &s.bb : which == 1 ? &s.rr : which == 2 ? &s.rznew : which == 3 ? &s.zrold : &s.pq;
 }
 
-// Column c's dot = fixed-order sum of partial[set][c*nb + 0..nb), stored into
-// field which[set] of its state (only starting columns if only_init); set =
-// blockIdx.y, partial sets nb*k apart.  Each column is summed on its own, so
-// a column's bits do not depend on k.
-__global__ void __launch_bounds__(256) bdot_reduce_kernel(int64_t nb, int k, const double* __restrict__ partial,
-                                                          ColState* st, int which0, int which1, int only_init,
-                                                          const int* run) {
-    if (run && *run == 0) return;
-    __shared__ double sh[256 / BW];
-    const int64_t c = blockIdx.x;
-    const double* __restrict__ p = partial + (int64_t)blockIdx.y * nb * k + c * nb;
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < nb; i += 256) s += p[i];
-#pragma unroll
-    for (int o = BW / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, BW);
-    if (threadIdx.x % BW == 0) sh[threadIdx.x / BW] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = sh[0];
-#pragma unroll
-        for (int w = 1; w < 256 / BW; ++w) t += sh[w];
-        if (!(only_init && !st[c].init)) *state_field(st[c], blockIdx.y == 0 ? which0 : which1) = t;
+// A column that stops: status set, one running column fewer.
+__device__ __forceinline__ void stop_column(ColState& s, int status, int* run) {
+    s.active = 0;
+    s.status = status;
+    atomicSub(run, 1);
+}
+
+// CG scalar updates of one column, applied by the reduction that completes
+// their dots: alpha after p.q, the convergence test after r.r, beta after r.z.
+enum BatchFinish : int { BFIN_NONE = 0, BFIN_ALPHA = 1, BFIN_CHECK = 2, BFIN_BETA = 3, BFIN_BETA_FLEX = 4 };
+__device__ void bcg_finish(int fin, ColState& s, double tol, int maxit, int* run) {
+    if (fin == BFIN_ALPHA) {
+        s.alpha = 0.0;
+        if (!s.active) return;
+        if (!(s.pq > 0.0) || !isfinite(s.pq) || !isfinite(s.rz))
+            stop_column(s, GIAMG_EBREAKDOWN, run);
+        else
+            s.alpha = s.rz / s.pq;
+    } else if (fin == BFIN_CHECK) {
+        if (!s.active) return;
+        s.iters += 1;
+        const double rel = sqrt(s.rr) / sqrt(s.bb);
+        if (!isfinite(rel))
+            stop_column(s, GIAMG_EBREAKDOWN, run);
+        else if (rel < tol)
+            stop_column(s, GIAMG_OK, run);
+        else if (s.iters >= maxit)
+            stop_column(s, GIAMG_ENOTCONV, run);
+    } else if (fin == BFIN_BETA || fin == BFIN_BETA_FLEX) {
+        if (!s.active) return;
+        const double rzn = s.rznew;
+        s.beta = fin == BFIN_BETA_FLEX ? (rzn - s.zrold) / s.rz : rzn / s.rz;
+        s.rz = rzn;
+        if (!isfinite(rzn)) stop_column(s, GIAMG_EBREAKDOWN, run);
     }
 }
 
+// Column c's dots = fixed-order sums of partial[set][c*nb + 0..nb), stored into
+// field which[set] of its state (only starting columns if only_init), sets
+// nb*k apart; then the column's scalar update.  Each column is summed on its
+// own, so a column's bits do not depend on k.  run: the number of running
+// columns (any nonzero value: work to do).
+__global__ void __launch_bounds__(256) bdot_reduce_kernel(int64_t nb, int k, int sets, const double* __restrict__ partial,
+                                                          ColState* st, int which0, int which1, int only_init,
+                                                          int fin, double tol, int maxit, int* run) {
+    if (run && *run == 0) return;
+    __shared__ double sh[256 / BW];
+    const int64_t c = blockIdx.x;
+    for (int set = 0; set < sets; ++set) {
+        const double* __restrict__ p = partial + (int64_t)set * nb * k + c * nb;
+        double s = 0.0;
+        for (int64_t i = threadIdx.x; i < nb; i += 256) s += p[i];
+#pragma unroll
+        for (int o = BW / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, BW);
+        if (threadIdx.x % BW == 0) sh[threadIdx.x / BW] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = sh[0];
+#pragma unroll
+            for (int w = 1; w < 256 / BW; ++w) t += sh[w];
+            if (!(only_init && !st[c].init)) *state_field(st[c], set == 0 ? which0 : which1) = t;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && fin != BFIN_NONE) bcg_finish(fin, st[c], tol, maxit, run);
+}
 
-// Starting columns: decide activity from ||b|| and ||r0||; run = any active.
+
+// Starting columns: decide activity from ||b|| and ||r0||; run = the running columns.
 __global__ void bcg_start_kernel(int k, ColState* st, double tol, int* run) {
-    __shared__ int any;
-    if (threadIdx.x == 0) any = 0;
+    __shared__ int active;
+    if (threadIdx.x == 0) active = 0;
     __syncthreads();
     for (int c = threadIdx.x; c < k; c += blockDim.x) {
         ColState& s = st[c];
@@ -511,20 +654,20 @@ __global__ void bcg_start_kernel(int k, ColState* st, double tol, int* run) {
                 if (!isfinite(s.rr)) { s.active = 0; s.status = GIAMG_EBREAKDOWN; }
             }
         }
-        if (s.active) atomicOr(&any, 1);
+        if (s.active) atomicAdd(&active, 1);
     }
     __syncthreads();
-    if (threadIdx.x == 0) *run = any;
+    if (threadIdx.x == 0) *run = active;
 }
 
 // Finish starting columns: rz = (r, z), clear the flag.
-__global__ void bcg_start_finish_kernel(int k, ColState* st) {
+__global__ void bcg_start_finish_kernel(int k, ColState* st, int* run) {
     for (int c = threadIdx.x; c < k; c += blockDim.x) {
         ColState& s = st[c];
         if (!s.init) continue;
         if (s.active) {
             s.rz = s.rznew;
-            if (!isfinite(s.rz)) { s.active = 0; s.status = GIAMG_EBREAKDOWN; }
+            if (!isfinite(s.rz)) stop_column(s, GIAMG_EBREAKDOWN, run);
         }
         s.init = 0;
     }
@@ -539,22 +682,6 @@ __global__ void bcopy_init_kernel(int64_t n, int k, const double* __restrict__ s
         if (st[i % k].init) dst[i] = src[i];
 }
 
-__global__ void bcg_alpha_kernel(int k, ColState* st, const int* run) {
-    if (*run == 0) return;
-    for (int c = threadIdx.x; c < k; c += blockDim.x) {
-        ColState& s = st[c];
-        if (!s.active) { s.alpha = 0.0; continue; }
-        if (!(s.pq > 0.0) || !isfinite(s.pq) || !isfinite(s.rz)) {
-            s.active = 0;
-            s.status = GIAMG_EBREAKDOWN;
-            s.alpha = 0.0;
-        } else {
-            s.alpha = s.rz / s.pq;
-        }
-    }
-}
-
-// x += alpha p; r_old = r; r -= alpha q   (active columns only)
 // x += alpha p, r_old = r, r -= alpha q for the active columns, and the
 // partials of r.r of every column on the row partition and in the order of
 // bdot_partial_kernel (so the same bits as that kernel run after this one).
@@ -564,6 +691,68 @@ __global__ void bcg_alpha_kernel(int k, ColState* st, const int* run) {
 // operations of bcheb_init0_kernel<TC>, so the same bits).
 template <typename TC>
 __global__ void __launch_bounds__(256) bcg_update_kernel(int64_t n, int k, double* __restrict__ x,
+                                                         double* __restrict__ r, double* __restrict__ rold,
+                                                         const double* __restrict__ p,
+                                                         const double* __restrict__ q,
+                                                         const ColState* __restrict__ st,
+                                                         float* __restrict__ r32,
+                                                         const TC* __restrict__ dinvc, TC* __restrict__ cr,
+                                                         TC* __restrict__ cd, TC inv_theta,
+                                                         double* __restrict__ partial, int64_t nb,
+                                                         const int* run) {
+    if (*run == 0) return;
+    __shared__ double sr[DOT_LDS];
+    __shared__ double sh[4][DOT_COLS];
+    const int tid = threadIdx.x, c = tid % DOT_COLS, rl = tid / DOT_COLS;
+    const int64_t col = (int64_t)blockIdx.y * DOT_COLS + c;
+    const int64_t r0 = (int64_t)blockIdx.x * DOT_ROWS;
+    const int rows = (int)min((int64_t)DOT_ROWS, n - r0);
+    if (col < k) {
+        const bool active = st[col].active != 0;
+        const double alpha = st[col].alpha;
+        constexpr int U = 4;   // passes whose loads are in flight together
+#pragma unroll
+        for (int u0 = 0; u0 < DOT_PASSES; u0 += U) {
+            double rn[U], xv[U], pv[U], qv[U];
+            TC dv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = min((u0 + u) * DOT_PASS + rl, rows - 1);
+                const int64_t idx = (r0 + i) * k + col;
+                rn[u] = r[idx];
+                xv[u] = x[idx];
+                pv[u] = p[idx];
+                qv[u] = q[idx];
+                dv[u] = dinvc ? dinvc[r0 + i] : TC(0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = (u0 + u) * DOT_PASS + rl;
+                if (i >= rows) continue;
+                const int64_t idx = (r0 + i) * k + col;
+                if (active) {
+                    x[idx] = __builtin_fma(alpha, pv[u], xv[u]);
+                    if (rold) rold[idx] = rn[u];
+                    rn[u] = __builtin_fma(-alpha, qv[u], rn[u]);
+                    r[idx] = rn[u];
+                }
+                if (r32) r32[idx] = (float)rn[u];
+                if (dinvc) {
+                    const TC res = dv[u] * (TC)rn[u];
+                    cr[idx] = res;
+                    cd[idx] = res * inv_theta;
+                }
+                sr[dot_slot(i, c)] = rn[u];
+            }
+        }
+    }
+    __syncthreads();
+    dot_sum(sr, sr, rows, tid, sh, col, k, partial, nb);
+}
+
+// The same update on bdot_wide_kernel's threads.
+template <typename TC>
+__global__ void __launch_bounds__(256) bcg_update_wide_kernel(int64_t n, int k, double* __restrict__ x,
                                                          double* __restrict__ r, double* __restrict__ rold,
                                                          const double* __restrict__ p,
                                                          const double* __restrict__ q,
@@ -587,9 +776,9 @@ __global__ void __launch_bounds__(256) bcg_update_kernel(int64_t n, int k, doubl
             const int64_t idx = i * k + col;
             double rn = r[idx];
             if (active) {
-                x[idx] += alpha * p[idx];
+                x[idx] = __builtin_fma(alpha, p[idx], x[idx]);
                 if (rold) rold[idx] = rn;
-                rn = rn - alpha * q[idx];
+                rn = __builtin_fma(-alpha, q[idx], rn);
                 r[idx] = rn;
             }
             if (r32) r32[idx] = (float)rn;
@@ -598,55 +787,13 @@ __global__ void __launch_bounds__(256) bcg_update_kernel(int64_t n, int k, doubl
                 cr[idx] = res;
                 cd[idx] = res * inv_theta;
             }
-            s += rn * rn;
+            s = __builtin_fma(rn, rn, s);
         }
     }
     sh[wave][lane] = s;
     __syncthreads();
     if (wave == 0 && col < k)
         partial[col * nb + blockIdx.x] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
-}
-
-__global__ void bcg_check_kernel(int k, ColState* st, double tol, int maxit, int* run) {
-    __shared__ int any;
-    if (*run == 0) return;
-    if (threadIdx.x == 0) any = 0;
-    __syncthreads();
-    for (int c = threadIdx.x; c < k; c += blockDim.x) {
-        ColState& s = st[c];
-        if (s.active) {
-            s.iters += 1;
-            const double rel = sqrt(s.rr) / sqrt(s.bb);
-            if (!isfinite(rel)) {
-                s.active = 0;
-                s.status = GIAMG_EBREAKDOWN;
-            } else if (rel < tol) {
-                s.active = 0;
-                s.status = GIAMG_OK;
-            } else if (s.iters >= maxit) {
-                s.active = 0;
-                s.status = GIAMG_ENOTCONV;
-            }
-        }
-        if (s.active) atomicOr(&any, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) *run = any;
-}
-
-__global__ void bcg_beta_kernel(int k, ColState* st, int flexible, const int* run) {
-    if (*run == 0) return;
-    for (int c = threadIdx.x; c < k; c += blockDim.x) {
-        ColState& s = st[c];
-        if (!s.active) continue;
-        const double rzn = s.rznew;
-        s.beta = flexible ? (rzn - s.zrold) / s.rz : rzn / s.rz;
-        if (!isfinite(rzn)) {
-            s.active = 0;
-            s.status = GIAMG_EBREAKDOWN;
-        }
-        s.rz = rzn;
-    }
 }
 
 // p = z + beta p (first: p = z), active columns only; z FP64, or the FP32
@@ -1000,7 +1147,8 @@ void bvcycle(BatchCtx& c, size_t l, const T* f, T* x, bool init_done = false) {
     if (l + 1 == H.levels.size()) {
         if (c.count_bytes) H.bytes += 8.0 * H.nc * H.nc + 2.0 * sizeof(T) * H.nc * k;
         if (H.nc > 0)
-            bcoarse_kernel<T><<<(unsigned)H.nc, BW, 0, c.s()>>>(H.nc, k, H.coarse_inv.get(), f, x, c.run);
+            bcoarse_kernel<T><<<dim3((unsigned)((H.nc + CO_ROWS - 1) / CO_ROWS), (unsigned)((k + CO_COLS - 1) / CO_COLS)),
+                                CO_THREADS, 0, c.s()>>>(H.nc, k, H.coarse_inv.get(), f, x, c.run);
         return;
     }
     BatchLevel& W = c.B.lv[l];
@@ -1077,34 +1225,54 @@ void bdirection(BatchCtx& c, const TZ* z, int first) {
 
 int64_t dot_blocks(int64_t n) { return (n + DOT_ROWS - 1) / DOT_ROWS; }
 
-// reduce `sets` partial sets (from B.partial) into the state fields which0, which1
-void breduce(BatchCtx& c, int sets, int which0, int which1, int only_init) {
+// reduce `sets` partial sets (from B.partial) into the state fields which0,
+// which1, then the scalar update `fin` of every column
+void breduce(BatchCtx& c, int sets, int which0, int which1, int only_init, int fin = BFIN_NONE, double tol = 0.0) {
     const int64_t nb = dot_blocks(c.H.n_nodes);
-    bdot_reduce_kernel<<<dim3((unsigned)c.k, (unsigned)sets), 256, 0, c.s()>>>(
-        nb, c.k, c.B.partial.get(), c.B.st.get(), which0, which1, only_init, c.run);
+    bdot_reduce_kernel<<<(unsigned)c.k, 256, 0, c.s()>>>(nb, c.k, sets, c.B.partial.get(), c.B.st.get(), which0, which1,
+                                                         only_init, fin, tol, c.H.opts.maxit,
+                                                         c.run ? c.B.run.get() : nullptr);
+}
+
+// Whether the dots and the update walk 64 columns side by side (the same bits):
+// a block of the wide kernels has a thread per quarter and column, each a serial
+// chain of 64 rows, so it pays where such blocks fill the chip.  Whole mixed
+// batches with 8 columns at a time against 64: 33^3 nodes and k = 64 3.9 and 4.4 ms,
+// 49^3 and k = 32 6.4 and 6.9, 49^3 and k = 64 9.6 and 9.6, 61^3 and k = 32 11.1 and
+// 10.9, 73^3 and k = 32 19.3 and 17.1; 61^3 and k = 16 7.1 and 7.9, 73^3 and k = 16
+// 11.5 and 12.0, 85^3 and k = 8 12.0 and 15.3.
+bool wide_columns(const BatchCtx& c) { return c.k >= 32 && c.H.n_nodes * (int64_t)c.k > 6000000; }
+dim3 dot_grid(const BatchCtx& c) {
+    const int cols = wide_columns(c) ? BW : DOT_COLS;
+    return dim3((unsigned)dot_blocks(c.H.n_nodes), (unsigned)((c.k + cols - 1) / cols));
 }
 
 // column dots a.b into the state field `which` (only starting columns if only_init)
 template <typename TB>
-void bdots(BatchCtx& c, const double* a, const TB* b, int which, int only_init = 0) {
+void bdots(BatchCtx& c, const double* a, const TB* b, int which, int only_init = 0, int fin = BFIN_NONE) {
     const int64_t n = c.H.n_nodes;
-    const int64_t nb = dot_blocks(n);
     if (c.count_bytes) c.H.bytes += (8.0 + sizeof(TB)) * n * c.k;
-    bdot_partial_kernel<TB><<<dim3((unsigned)nb, (unsigned)((c.k + BW - 1) / BW)), 256, 0, c.s()>>>(
-        n, c.k, a, b, c.B.partial.get(), nb, c.run);
-    breduce(c, 1, which, which, only_init);
+    if (wide_columns(c))
+        bdot_wide_kernel<TB><<<dot_grid(c), 256, 0, c.s()>>>(n, c.k, a, b, c.B.partial.get(), dot_blocks(n), c.run);
+    else
+        bdot_partial_kernel<TB, false><<<dot_grid(c), 256, 0, c.s()>>>(n, c.k, a, nullptr, b, c.B.partial.get(),
+                                                                       nullptr, dot_blocks(n), c.run);
+    breduce(c, 1, which, which, only_init, fin);
 }
 
 // a.b into `which` and a2.b into `which2`, reading b once
 template <typename TB>
-void bdots2(BatchCtx& c, const double* a, const double* a2, const TB* b, int which, int which2) {
+void bdots2(BatchCtx& c, const double* a, const double* a2, const TB* b, int which, int which2, int fin) {
     const int64_t n = c.H.n_nodes;
     const int64_t nb = dot_blocks(n);
     if (c.count_bytes) c.H.bytes += (16.0 + sizeof(TB)) * n * c.k;
     double* part = c.B.partial.get();
-    bdot2_partial_kernel<TB><<<dim3((unsigned)nb, (unsigned)((c.k + BW - 1) / BW)), 256, 0, c.s()>>>(
-        n, c.k, a, a2, b, part, part + nb * c.k, nb, c.run);
-    breduce(c, 2, which, which2, 0);
+    if (wide_columns(c))
+        bdot2_wide_kernel<TB><<<dot_grid(c), 256, 0, c.s()>>>(n, c.k, a, a2, b, part, part + nb * c.k, nb, c.run);
+    else
+        bdot_partial_kernel<TB, true><<<dot_grid(c), 256, 0, c.s()>>>(n, c.k, a, a2, b, part, part + nb * c.k, nb,
+                                                                      c.run);
+    breduce(c, 2, which, which2, 0, fin);
 }
 
 void bproduct_A0(BatchCtx& c, int mode, const double* v, const double* f, double* y, double rowvecs) {
@@ -1119,39 +1287,35 @@ void iteration(BatchCtx& c, double* X, double tol) {
     Handle& H = c.H;
     BatchState& B = c.B;
     const int64_t total = H.n_nodes * (int64_t)c.k;
-    const int maxit = H.opts.maxit;
-    const unsigned cb = (unsigned)std::min(c.k, MAX_K);
     bproduct_A0(c, SPMV_PLAIN, B.P.get(), nullptr, B.Q.get(), 1);
-    bdots(c, B.P.get(), B.Q.get(), 4);
-    bcg_alpha_kernel<<<1, cb, 0, c.s()>>>(c.k, B.st.get(), c.run);
+    bdots(c, B.P.get(), B.Q.get(), 4, 0, BFIN_ALPHA);
     if (c.count_bytes) H.bytes += (B.mixed ? 60.0 : 48.0) * total;
     const int64_t nb = dot_blocks(H.n_nodes);
     const bool fuse = bfused_init(H);
-    const dim3 ug((unsigned)nb, (unsigned)((c.k + BW - 1) / BW));
+    const dim3 ug = dot_grid(c);
     Level& L0 = H.levels[0];
     BatchLevel& W0 = B.lv[0];
     const double it0 = binv_theta(H, L0);
+    const bool wide = wide_columns(c);
     if (B.mixed) {
         if (c.count_bytes && fuse) H.bytes += 8.0 * total;
-        bcg_update_kernel<float><<<ug, 256, 0, c.s()>>>(
+        (wide ? bcg_update_wide_kernel<float> : bcg_update_kernel<float>)<<<ug, 256, 0, c.s()>>>(
             H.n_nodes, c.k, X, B.R.get(), B.Rold.get(), B.P.get(), B.Q.get(), B.st.get(), W0.f32.get(),
             fuse ? L0.dinv32.get() : nullptr, W0.r32.get(), W0.d032.get(), (float)it0, B.partial.get(), nb,
             c.run);
     } else {
         if (c.count_bytes && fuse) H.bytes += 16.0 * total;
-        bcg_update_kernel<double><<<ug, 256, 0, c.s()>>>(
+        (wide ? bcg_update_wide_kernel<double> : bcg_update_kernel<double>)<<<ug, 256, 0, c.s()>>>(
             H.n_nodes, c.k, X, B.R.get(), nullptr, B.P.get(), B.Q.get(), B.st.get(), nullptr,
             fuse ? L0.dinv.get() : nullptr, W0.r.get(), W0.d0.get(), it0, B.partial.get(), nb, c.run);
     }
-    breduce(c, 1, 1, 1, 0);   // r.r
-    bcg_check_kernel<<<1, cb, 0, c.s()>>>(c.k, B.st.get(), tol, maxit, B.run.get());
+    breduce(c, 1, 1, 1, 0, BFIN_CHECK, tol);   // r.r
     bprecondition(c, B.R.get(), true, fuse);
     with_z(c, [&](auto z) {
         if (B.mixed)
-            bdots2(c, B.R.get(), B.Rold.get(), z, 2, 3);
+            bdots2(c, B.R.get(), B.Rold.get(), z, 2, 3, BFIN_BETA_FLEX);
         else
-            bdots(c, B.R.get(), z, 2);
-        bcg_beta_kernel<<<1, cb, 0, c.s()>>>(c.k, B.st.get(), B.mixed ? 1 : 0, c.run);
+            bdots(c, B.R.get(), z, 2, 0, BFIN_BETA);
         bdirection(c, z, 0);
     });
     GIAMG_HIP(hipGetLastError());
@@ -1220,7 +1384,7 @@ void start_columns(BatchCtx& c, const double* Bm, double* X, double tol) {
         bdots(c, B.R.get(), z, 2, 1);
         bdirection(c, z, 1);
     });
-    bcg_start_finish_kernel<<<1, cb, 0, s>>>(k, B.st.get());
+    bcg_start_finish_kernel<<<1, cb, 0, s>>>(k, B.st.get(), B.run.get());
     GIAMG_HIP(hipGetLastError());
 }
 
@@ -1375,8 +1539,9 @@ __global__ void bgather_kernel(int64_t n, int k, int slot, const double* __restr
         x[i] = X[i * k + slot];
 }
 
-__global__ void bfree_slot_kernel(int k, ColState* st, int slot) {
+__global__ void bfree_slot_kernel(int k, ColState* st, int slot, int* run) {
     if (threadIdx.x == 0 && slot >= 0 && slot < k) {
+        if (st[slot].active) atomicSub(run, 1);
         ColState z{};
         st[slot] = z;
     }
@@ -1544,7 +1709,7 @@ void session_retire_async(Session* S, int slot, double* x) {
     GIAMG_HIP(hipEventRecord(B.ev_in, H.stream));
     GIAMG_HIP(hipStreamWaitEvent(B.stream, B.ev_in, 0));
     bgather_kernel<<<bgrid(H.n_nodes), 256, 0, B.stream>>>(H.n_nodes, S->k, slot, S->X.get(), x);
-    bfree_slot_kernel<<<1, 64, 0, B.stream>>>(S->k, B.st.get(), slot);
+    bfree_slot_kernel<<<1, 64, 0, B.stream>>>(S->k, B.st.get(), slot, B.run.get());
     GIAMG_HIP(hipGetLastError());
 }
 

@@ -149,3 +149,22 @@ def test_batch_kernel_shapes_give_the_same_bits(env, precision, case):
         X, it = out[kind]
         assert it == it0, kind
         assert torch.equal(X, X0), kind
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_wide_batches_of_many_rows_keep_the_columns_bits(precision):
+    """70 columns of 49^3 rows take the dots and updates that walk 64 columns side
+    by side (the last 6 in a ragged block), one and ten columns those of 8: the
+    same bits."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(16, 3, perturb=0.1, seed=6)
+    s = Solver(m.coords, m.l2g, 3, 10.0, Options(precision=precision))
+    B = torch.from_numpy(synth.normal_rhs(m.n_nodes * 70, 8).reshape(m.n_nodes, 70)).to("cuda:0")
+    X, infos = s.solve_batch(B)
+    assert all(i.status == 0 and i.true_relres < 1e-9 for i in infos)
+    for cols in ((69,), tuple(range(58, 68))):
+        Xc, ic = s.solve_batch(B[:, list(cols)].contiguous())
+        for j, c in enumerate(cols):
+            assert ic[j].iters == infos[c].iters and torch.equal(Xc[:, j], X[:, c]), (cols, c)
+    s.close()
