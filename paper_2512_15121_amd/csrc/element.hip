@@ -218,8 +218,8 @@ template <typename T, int P, int NT, int V, bool COLS, bool UNIT = false>
 __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
 #pragma clang fp contract(off)
     if (a.run != nullptr && *a.run == 0) return;
-    if (a.stop != nullptr && *a.stop != 0) return;
     if (a.vnz != nullptr && *a.vnz == 0.0) return;
+    const int done = a.stop != nullptr ? *a.stop : 0;   // looked at once the loads are under way
     constexpr int N = P + 1, Q = P + 2, N2 = N * N, NL = N2 * N, Q2 = Q * Q;
     constexpr int H = (Q + 1) / 2;                 // Gauss pairs, the middle point one of its own
     static_assert(V * Q2 <= NT, "block shape");
@@ -281,6 +281,7 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
 #pragma unroll
     for (int m = 0; m < ELEM_COEF; ++m) c[m] = a.coef[m * a.ne + e];
     __syncthreads();
+    if (done) return;
     // z: nodal lines to Gauss points, values and derivatives
     {
         const const_ptr<T> tab = fresh(a.tabs);
@@ -548,7 +549,8 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(NODE_THREADS) element_node_kernel(SpmvArgs<T> a, const int32_t* __restrict__ ptr,
                                                                     const int32_t* __restrict__ ent,
                                                                     const T* __restrict__ ev) {
-    if (a.stop != nullptr && *a.stop != 0) return;
+    constexpr int U = 4;   // entries under way: a vertex has 8, most nodes one or two
+    const int done = a.stop != nullptr ? *a.stop : 0;
     const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
     const int64_t row = lb * NODE_THREADS + threadIdx.x;
     double dot = 0.0, dot2 = 0.0;
@@ -560,17 +562,28 @@ __global__ void __launch_bounds__(NODE_THREADS) element_node_kernel(SpmvArgs<T> 
         if constexpr (MODE == SPMV_RINIT) product = !(a.vnz != nullptr && *a.vnz == 0.0);
         if (product) {
             const int32_t s = ptr[row], e = ptr[row + 1];
-            for (int32_t j = s; j < e; ++j) y += ev[ent[j]];
+            for (int32_t j = s; j < e; j += U) {
+                int32_t at[U];
+                T x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (j + u < e) at[u] = ent[j + u];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (j + u < e) x[u] = ev[at[u]];
+#pragma unroll
+                for (int u = 0; u < U; ++u) y = j + u < e ? y + x[u] : y;
+            }
             if (s == e) y = a.v[row];
         }
-        epilogue_store<T, MODE>(a, row, y, in, dot, dot2);
+        if (!done) epilogue_store<T, MODE>(a, row, y, in, dot, dot2);
     }
     if constexpr (has_partials<MODE>()) {
         __shared__ double red[2 * NODE_THREADS / WAVE];
-        block_sum_to0<NODE_THREADS, n_partials<MODE>()>(red, threadIdx.x, dot, dot2);
-        if (threadIdx.x == 0) {
+        block_sum_to0<NODE_THREADS, n_partials<T, MODE>()>(red, threadIdx.x, dot, dot2);
+        if (threadIdx.x == 0 && !done) {
             a.partial[lb] = dot;
-            if (MODE == SPMV_RINIT) a.partial[a.nblk + lb] = dot2;
+            if (n_partials<T, MODE>() == 2) a.partial[a.nblk + lb] = dot2;
         }
     }
 }
@@ -948,6 +961,8 @@ void launch_element_product(int mode, const SpmvArgs<T>& args, hipStream_t s) {
         case SPMV_DOT: launch_node_kernel<T, SPMV_DOT>(a, E, e.ev, s); break;
         case SPMV_DINV: launch_node_kernel<T, SPMV_DINV>(a, E, e.ev, s); break;
         case SPMV_RINIT: launch_node_kernel<T, SPMV_RINIT>(a, E, e.ev, s); break;
+        case SPMV_CHEB_DOT: launch_node_kernel<T, SPMV_CHEB_DOT>(a, E, e.ev, s); break;
+        case SPMV_JACOBI_DOT: launch_node_kernel<T, SPMV_JACOBI_DOT>(a, E, e.ev, s); break;
         default: throw Error(GIAMG_EINVAL, "unknown product mode of the element form");
     }
     GIAMG_HIP(hipGetLastError());

@@ -25,6 +25,10 @@ enum SpmvMode : int {
     SPMV_RINIT = 8,      // y = f - A v, block partials of f . f and y . y
     SPMV_RCHEB0 = 9,     // restriction fused with the next level's zero-start Chebyshev
                          // init: y = A v, r = dinv y, x = r / theta (x holds d_0)
+    // lean and element forms only: also block partials of dot_r . result (FP32: and
+    // of dot_rold . result), the result being x_new and y
+    SPMV_CHEB_DOT = 10,
+    SPMV_JACOBI_DOT = 11,
 };
 
 // Row blocks of the streaming product: at most spmv_cap<T>() nonzeros (the
@@ -96,6 +100,7 @@ struct SpmvArgs {
     int block_cap = 0, block_threads = 0;   // shape the row blocks were built for
     int lanes = 16;                  // lanes that reduce one row (16, 4 or 1)
     const int* stop = nullptr;       // device stop flag (null: the thread's StopScope flag)
+    const double *dot_r = nullptr, *dot_rold = nullptr;   // SPMV_CHEB_DOT, SPMV_JACOBI_DOT
     const double* vnz = nullptr;     // SPMV_RINIT: when set and *vnz == 0, v is all +0 and
                                      // y = f exactly (A v = +0 row by row: every row has a
                                      // positive diagonal entry), so no product is formed
@@ -244,21 +249,37 @@ public:
 private:
     const int* prev_;
 };
+// Block partials a kernel adds up itself, in launch_reduce's order (the same
+// bits): component c of m partials at p + c stride.  p null: the scalars are
+// there already.
+struct PartialSums {
+    const double* p = nullptr;
+    int64_t m = 0, stride = 0;
+};
+// At most this many: every block of the reading kernel adds them all.
+constexpr int64_t FOLD_PARTIALS = 1024;
+// whether an update of n rows may end its iteration itself
+bool update_closes(int64_t n);
+// The updates take alpha from pq's partials (FIN_ALPHA).  With ctl (only where
+// update_closes) they end with the reduction of r . r and FIN_CONV, without it
+// with the partials; partial and pq.p must not overlap.
 void launch_pcg_update(int64_t n, double* x, double* r, double* rold, const double* p,
-                       const double* q, const double* scal, double* partial, hipStream_t s);
+                       const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
+                       hipStream_t s);
 // The same update fused with the fine level's zero-start Chebyshev init of
 // the next preconditioning: cr = dinv r_new, cd = cr inv_theta.
 void launch_pcg_update_cheb0(int64_t n, double* x, double* r, const double* p, const double* q,
-                             const double* scal, double* partial, const double* dinv, double* cr,
-                             double* cd, double inv_theta, hipStream_t s);
+                             double* scal, double* partial, const PartialSums& pq, int* ctl, const double* dinv,
+                             double* cr, double* cd, double inv_theta, hipStream_t s);
 // The flexible-CG update (r_old = r) that also writes r_new in FP32 to f32
 // and, with dinv32 non-null, the fine level's FP32 Chebyshev init (cr, cd).
 void launch_pcg_update_mixed(int64_t n, double* x, double* r, double* rold, const double* p,
-                             const double* q, const double* scal, double* partial, float* f32,
-                             const float* dinv32, float* cr, float* cd, float inv_theta, hipStream_t s);
-// p = z + beta p; z double, or float (widened exactly)
+                             const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
+                             float* f32, const float* dinv32, float* cr, float* cd, float inv_theta, hipStream_t s);
+// p = z + beta p, beta from rz's partials (FIN_BETA; z float: FIN_BETA_FLEX);
+// z double, or float (widened exactly)
 template <typename TZ>
-void launch_pcg_direction(int64_t n, const TZ* z, double* p, const double* scal, hipStream_t s);
+void launch_pcg_direction(int64_t n, const TZ* z, double* p, double* scal, const PartialSums& rz, hipStream_t s);
 void launch_power_start(int64_t n, double* v, hipStream_t s);
 void launch_scale(int64_t n, double a, const double* x, double* y, hipStream_t s);
 

@@ -288,7 +288,7 @@ spmv_stream_kernel(SpmvArgs<T> a) {
                 epilogue_load<T, MODE>(a, r0 + tid, in);
                 epilogue_store<T, MODE>(a, r0 + tid, T(0), in, dot, dot2);
             }
-            block_sum_to0<NT, n_partials<MODE>()>(red, tid, dot, dot2);
+            block_sum_to0<NT, n_partials<T, MODE>()>(red, tid, dot, dot2);
             if (tid == 0) {
                 a.partial[lb] = dot;
                 a.partial[a.nblk + lb] = dot2;
@@ -365,7 +365,7 @@ spmv_stream_kernel(SpmvArgs<T> a) {
     // 3. row epilogues
     if (own) epilogue_store<T, MODE>(a, r0 + tid, rowsum[tid], in, dot, dot2);
     if constexpr (has_partials<MODE>()) {
-        block_sum_to0<NT, n_partials<MODE>()>(red, tid, dot, dot2);
+        block_sum_to0<NT, n_partials<T, MODE>()>(red, tid, dot, dot2);
         if (tid == 0) {
             a.partial[lb] = dot;
             if (MODE == SPMV_RINIT) a.partial[a.nblk + lb] = dot2;
@@ -483,7 +483,7 @@ spmv_group_kernel(SpmvArgs<T> a) {
     __syncthreads();
     if (tid < R) epilogue_store<T, MODE>(a, row, rowsum[tid], in, dot, dot2);
     if constexpr (has_partials<MODE>()) {
-        block_sum_to0<GROUP_THREADS, n_partials<MODE>()>(red, tid, dot, dot2);
+        block_sum_to0<GROUP_THREADS, n_partials<T, MODE>()>(red, tid, dot, dot2);
         if (tid == 0) {
             a.partial[lb] = dot;
             if (MODE == SPMV_RINIT) a.partial[a.nblk + lb] = dot2;
@@ -496,7 +496,11 @@ spmv_group_kernel(SpmvArgs<T> a) {
 // straight from memory (column ids and values, then the vector), with no
 // row-block bounds, run tables or LDS staging, so a launch waits on a chain
 // three loads deep; the coarse levels (kilobytes to a few MB each) are
-// bound by that chain, not by bytes.  Lane gl sums the row's products at
+// bound by that chain, not by bytes.  So nothing waits for the stop flag before
+// the end, a lane takes eight entries at a time (the last ones clamped, their
+// products left out of the sum) and the next eight are on their way meanwhile:
+// 3375 rows of 100 entries 3.7 -> 3.3 us, four entries and single steps at the
+// row's end before.  Lane gl sums the row's products at
 // positions gl, gl + L, ... in order, each product rounded before it is
 // added (as the LDS products of the CSR form are), and the L lanes combine
 // by the same butterfly: rows equal the CSR form's bit for bit (operators
@@ -504,45 +508,73 @@ spmv_group_kernel(SpmvArgs<T> a) {
 // ---------------------------------------------------------------------------
 template <typename T, int MODE, int L>
 __global__ void __launch_bounds__(LEAN_THREADS) spmv_lean_kernel(SpmvArgs<T> a) {
-    if (stopped(a.stop)) return;
     constexpr int RPB = LEAN_THREADS / L;
+    const int done = a.stop != nullptr ? *a.stop : 0;
     const int tid = threadIdx.x, gl = tid % L;
     const int64_t row = (int64_t)blockIdx.x * RPB + tid / L;
     const bool live = row < a.n;
     const int64_t rr = live ? row : a.n - 1;
     RowIn<T> in{};
     if (gl == 0) epilogue_load<T, MODE>(a, rr, in);
-    const int64_t s = a.rp[rr], e = a.rp[rr + 1];
+    const int64_t s = a.rp[rr], e = done ? s : a.rp[rr + 1];
     const int32_t* __restrict__ ci = a.ci;
     const T* __restrict__ val = a.val;
     const T* __restrict__ v = a.v;
     T acc = 0;
-    {
+    if constexpr (L == 1) {   // a few entries per lane
 #pragma clang fp contract(off)
-        int64_t j = s + gl;
-        for (; j + 3 * L < e; j += 4 * L) {
-            const int32_t c0 = ci[j], c1 = ci[j + L], c2 = ci[j + 2 * L], c3 = ci[j + 3 * L];
-            const T a0 = val[j], a1 = val[j + L], a2 = val[j + 2 * L], a3 = val[j + 3 * L];
+        int64_t j = s;
+        for (; j + 3 < e; j += 4) {
+            const int32_t c0 = ci[j], c1 = ci[j + 1], c2 = ci[j + 2], c3 = ci[j + 3];
+            const T a0 = val[j], a1 = val[j + 1], a2 = val[j + 2], a3 = val[j + 3];
             const T p0 = a0 * v[c0], p1 = a1 * v[c1], p2 = a2 * v[c2], p3 = a3 * v[c3];
             acc += p0;
             acc += p1;
             acc += p2;
             acc += p3;
         }
-        for (; j < e; j += L) {
+        for (; j < e; ++j) {
             const T p = val[j] * v[ci[j]];
             acc += p;
+        }
+    } else {
+#pragma clang fp contract(off)
+        constexpr int U = 8;
+        int32_t c[U];
+        T w[U];
+        auto fetch = [&](int64_t j) {   // clamped to the row's last entry
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = min(j + u * L, e - 1);
+                c[u] = ci[at];
+                w[u] = val[at];
+            }
+        };
+        int64_t j = s + gl;
+        if (j < e) fetch(j);
+        for (; j < e; j += U * L) {
+            T x[U], p[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = v[c[u]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) p[u] = w[u];
+            if (j + U * L < e) fetch(j + U * L);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const T t = p[u] * x[u];
+                acc = j + u * L < e ? acc + t : acc;
+            }
         }
     }
     acc = row_group_sum<L>(acc);
     double dot = 0.0, dot2 = 0.0;
-    if (live && gl == 0) epilogue_store<T, MODE>(a, row, acc, in, dot, dot2);
+    if (live && gl == 0 && !done) epilogue_store<T, MODE>(a, row, acc, in, dot, dot2);
     if constexpr (has_partials<MODE>()) {
         __shared__ double red[2 * LEAN_THREADS / WAVE];
-        block_sum_to0<LEAN_THREADS, n_partials<MODE>()>(red, tid, dot, dot2);
-        if (tid == 0) {
+        block_sum_to0<LEAN_THREADS, n_partials<T, MODE>()>(red, tid, dot, dot2);
+        if (tid == 0 && !done) {
             a.partial[blockIdx.x] = dot;
-            if (MODE == SPMV_RINIT) a.partial[a.nblk + blockIdx.x] = dot2;
+            if (n_partials<T, MODE>() == 2) a.partial[a.nblk + blockIdx.x] = dot2;
         }
     }
 }
@@ -774,6 +806,7 @@ void launch_lean_kernel(const SpmvArgs<T>& a, hipStream_t s) {
 
 template <typename T, int MODE>
 void launch_spmv_mode(const SpmvArgs<T>& a, hipStream_t s) {
+    constexpr bool lean_only = MODE == SPMV_CHEB_DOT || MODE == SPMV_JACOBI_DOT;
     if (a.lean) {
         switch (a.lanes) {
             case 16: launch_lean_kernel<T, MODE, 16>(a, s); break;
@@ -781,6 +814,8 @@ void launch_spmv_mode(const SpmvArgs<T>& a, hipStream_t s) {
             case 1: launch_lean_kernel<T, MODE, 1>(a, s); break;
             default: throw Error(GIAMG_EINVAL, "unsupported reduction width");
         }
+    } else if constexpr (lean_only) {
+        throw Error(GIAMG_EINVAL, "product mode of the lean and element forms only");
     } else if (a.gblk != nullptr) {
         switch (a.lanes) {
             case 16: launch_group_kernel<T, MODE, 16>(a, s); break;
@@ -829,6 +864,8 @@ void launch_spmv(int mode, const SpmvArgs<T>& args, hipStream_t s) {
         case SPMV_DINV: launch_spmv_mode<T, SPMV_DINV>(a, s); break;
         case SPMV_RINIT: launch_spmv_mode<T, SPMV_RINIT>(a, s); break;
         case SPMV_RCHEB0: launch_spmv_mode<T, SPMV_RCHEB0>(a, s); break;
+        case SPMV_CHEB_DOT: launch_spmv_mode<T, SPMV_CHEB_DOT>(a, s); break;
+        case SPMV_JACOBI_DOT: launch_spmv_mode<T, SPMV_JACOBI_DOT>(a, s); break;
         default: throw Error(GIAMG_EINVAL, "unknown product mode");
     }
     GIAMG_HIP(hipGetLastError());
@@ -1042,15 +1079,28 @@ template <typename T>
 __global__ void __launch_bounds__(256) coarse_kernel(int64_t n, const double* __restrict__ inv,
                                                      const T* __restrict__ f, T* __restrict__ x,
                                                      const int* stop) {
-    if (stopped(stop)) return;
+    constexpr int U = 8;
+    const int done = stop != nullptr ? *stop : 0;
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE;
     if (row >= n) return;
     double acc = 0.0;
     const double* a = inv + row * n;
-    for (int64_t j = lane; j < n; j += WAVE) acc += a[j] * (double)f[j];
+    for (int64_t j = lane; j < n; j += U * WAVE) {
+        double m[U];
+        T g[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = min(j + u * WAVE, n - 1);
+            m[u] = a[at];
+            g[u] = f[at];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u * WAVE < n) acc = __builtin_fma(m[u], (double)g[u], acc);
+    }
     acc = wave_sum(acc);
-    if (lane == 0) x[row] = (T)acc;
+    if (lane == 0 && !done) x[row] = (T)acc;
 }
 template <typename T>
 void launch_coarse_apply(int64_t n, const double* inv, const T* f, T* x, hipStream_t s) {
@@ -1183,12 +1233,13 @@ __device__ void cg_finish(int fin, double* scal, int* ctl) {
         return;
     }
     if (fin == FIN_ALPHA) {
-        const double pq = scal[S_PQ];
-        if (!(pq > 0.0) || !isfinite(pq) || !isfinite(scal[S_RZ])) {
+        const double pq = scal[S_PQ], rz = scal[S_RZNEW];
+        scal[S_RZ] = rz;
+        if (!(pq > 0.0) || !isfinite(pq) || !isfinite(rz)) {
             scal[S_FLAG] = 1.0;
             scal[S_ALPHA] = 0.0;
         } else {
-            scal[S_ALPHA] = scal[S_RZ] / pq;
+            scal[S_ALPHA] = rz / pq;
         }
     } else if (fin == FIN_BETA_FIRST || fin == FIN_BETA || fin == FIN_BETA_FLEX) {
         const double rzn = scal[S_RZNEW];
@@ -1208,15 +1259,23 @@ __global__ void __launch_bounds__(RED_THREADS) reduce_kernel(int64_t m, const do
                                                              double* out, int fin,
                                                              double* scal,   // out may lie inside scal
                                                              int* ctl, const int* stop) {
-    if (stopped(stop)) return;
-    __shared__ double sh[RED_THREADS];
+    constexpr int U = 8;
+    const int done = stop != nullptr ? *stop : 0;
+    __shared__ double sh[RED_THREADS / WAVE];
     for (int c = 0; c < ncomp; ++c) {
         double s = 0.0;
-        for (int64_t i = threadIdx.x; i < m; i += RED_THREADS) s += partial[c * stride + i];
+        for (int64_t i = threadIdx.x; i < m; i += U * RED_THREADS) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = partial[c * stride + min(i + u * RED_THREADS, m - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * RED_THREADS < m) s += v[u];
+        }
         s = block_sum<RED_THREADS>(s, sh);
-        if (threadIdx.x == 0) out[c] = s;
+        if (threadIdx.x == 0 && !done) out[c] = s;
     }
-    if (fin != FIN_NONE && threadIdx.x == 0) {
+    if (fin != FIN_NONE && threadIdx.x == 0 && !done) {
         __threadfence_block();
         cg_finish(fin, scal, ctl);
     }
@@ -1230,21 +1289,113 @@ void launch_reduce(int64_t m, const double* partial, int64_t stride, int ncomp, 
 
 // ---------------------------------------------------------------------------
 // CG kernels
+//
+// Small problems wait for launches, not for memory: a launch costs 3 to 4 us, and
+// three of an iteration's were reductions of a few partials by one block.  So the
+// kernel that needs alpha or beta adds the partials itself, every block the same
+// ones in the reduction's order: 0.7 us more in the update (4.4 -> 5.1 us at 36 k
+// rows) for a launch of 3.0.  Together with r . z riding on the last smoothing step
+// and the stop flag looked at only once a kernel's own loads are under way, a
+// solve of 36 k rows (8^3 p = 4) went from 1.26 to 1.11 ms, 729 rows from 0.55 to 0.46.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(VEC_THREADS) pcg_update_kernel(int64_t n, double* __restrict__ x,
-                                                                 double* __restrict__ r,
-                                                                 double* __restrict__ rold,
-                                                                 const double* __restrict__ p,
-                                                                 const double* __restrict__ q,
-                                                                 const double* __restrict__ scal,
-                                                                 double* __restrict__ partial,
-                                                                 const int* stop) {
-    if (stopped(stop)) return;
-    __shared__ double sh[VEC_THREADS];
-    const double alpha = scal[S_ALPHA];
+// Sum of m partials in reduce_kernel's order by NT threads of a block (any others
+// repeat them; returned to all); sh holds RED_THREADS / WAVE doubles and may be reused at once.
+template <int NT>
+__device__ __forceinline__ double partials_sum(const double* p, int64_t m, double* sh) {
+    constexpr int NW = NT / WAVE, RW = RED_THREADS / WAVE, Q = RW / NW;
+    const int lane = threadIdx.x % WAVE, wave = threadIdx.x % NT / WAVE;
+    double s[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {   // wave `wave + q NW` of the reduction
+        s[q] = 0.0;
+        for (int64_t i = (wave + q * NW) * WAVE + lane; i < m; i += RED_THREADS) s[q] += p[i];
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if ((wave + q * NW) * WAVE < m) s[q] = wave_butterfly(s[q]);
+        if (lane == 0 && threadIdx.x < NT) sh[wave + q * NW] = s[q];
+    }
+    __syncthreads();
+    double r = sh[0];
+#pragma unroll
+    for (int w = 1; w < RW; ++w) r += sh[w];
+    __syncthreads();
+    return r;
+}
+
+// FIN_ALPHA by every block; block 0 stores the scalars (none of them is read by
+// the other blocks of the kernel).
+__device__ __forceinline__ double fold_alpha(const PartialSums& pq, double* scal, double* sh, int done) {
+    if (pq.p == nullptr) return scal[S_ALPHA];
+    const double v = partials_sum<VEC_THREADS>(pq.p, pq.m, sh);
+    const double rz = scal[S_RZNEW];
+    const bool bad = !(v > 0.0) || !isfinite(v) || !isfinite(rz);
+    const double alpha = bad ? 0.0 : rz / v;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !done) {
+        scal[S_PQ] = v;
+        scal[S_RZ] = rz;
+        scal[S_ALPHA] = alpha;
+        if (bad) scal[S_FLAG] = 1.0;
+    }
+    return alpha;
+}
+
+// Where a thread of the updates works: CLOSE runs the update's blocks, at most
+// CLOSE_BLOCKS, as the 256-thread parts of one block, which then ends the iteration
+// itself.  (Letting the last of many blocks do that, counted by an atomic, took 4 us
+// of release and acquire, more than the launch it saves.)
+constexpr int CLOSE_BLOCKS = 4;
+bool update_closes(int64_t n) { return vec_blocks(n) <= CLOSE_BLOCKS; }
+
+template <bool CLOSE>
+struct UpdateRows {
+    int64_t first, step;
+    __device__ UpdateRows() {
+        const int part = CLOSE ? threadIdx.x / VEC_THREADS : blockIdx.x;
+        first = part * (int64_t)VEC_THREADS + threadIdx.x % VEC_THREADS;
+        step = (CLOSE ? blockDim.x : gridDim.x * (int64_t)VEC_THREADS);
+    }
+};
+
+// The blocks' partials of s; CLOSE: their reduction (the order of block_sum and
+// reduce_kernel) and FIN_CONV.  sh holds RED_THREADS / WAVE doubles.
+template <bool CLOSE>
+__device__ __forceinline__ void update_sums(double s, double* partial, double* scal, int* ctl, double* sh) {
+    if constexpr (!CLOSE) {
+        s = block_sum<VEC_THREADS>(s, sh);
+        if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    } else {
+        constexpr int NW = VEC_THREADS / WAVE;
+        s = wave_butterfly(s);
+        if (threadIdx.x % WAVE == 0) sh[threadIdx.x / WAVE] = s;
+        __syncthreads();
+        if (threadIdx.x >= WAVE) return;
+        double r = 0.0;
+        if (threadIdx.x * VEC_THREADS < blockDim.x) {
+            r = sh[threadIdx.x * NW];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) r += sh[threadIdx.x * NW + w];
+        }
+        r = wave_butterfly(r);
+        if (threadIdx.x == 0) {
+            scal[S_RR] = r;
+            cg_finish(FIN_CONV, scal, ctl);
+        }
+    }
+}
+
+template <bool CLOSE>
+__global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREADS) pcg_update_kernel(
+    int64_t n, double* __restrict__ x, double* __restrict__ r, double* __restrict__ rold,
+    const double* __restrict__ p, const double* __restrict__ q, double* scal, double* partial, PartialSums pq,
+    int* ctl, const int* stop) {
+    __shared__ double sh[RED_THREADS / WAVE];
+    const int done = stop != nullptr ? *stop : 0;
+    const double alpha = fold_alpha(pq, scal, sh, done);
+    if (done) return;
+    const UpdateRows<CLOSE> rows;
     double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)VEC_THREADS + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * VEC_THREADS) {
+    for (int64_t i = rows.first; i < n; i += rows.step) {
         x[i] += alpha * p[i];
         const double ri = r[i];
         if (rold) rold[i] = ri;
@@ -1252,31 +1403,42 @@ __global__ void __launch_bounds__(VEC_THREADS) pcg_update_kernel(int64_t n, doub
         r[i] = rn;
         s += rn * rn;
     }
-    s = block_sum<VEC_THREADS>(s, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    update_sums<CLOSE>(s, partial, scal, ctl, sh);
 }
+// KERNEL<true> in one block if ctl is given, else KERNEL<false>
+#define GIAMG_UPDATE(KERNEL, ...)                                                                            \
+    do {                                                                                                     \
+        const unsigned nb = (unsigned)vec_blocks(n);                                                         \
+        if (ctl != nullptr && nb > CLOSE_BLOCKS) throw Error(GIAMG_EINVAL, "update too large to close");      \
+        if (ctl != nullptr)                                                                                  \
+            KERNEL<true><<<1, nb * VEC_THREADS, 0, s>>>(__VA_ARGS__, g_stop);                                \
+        else                                                                                                 \
+            KERNEL<false><<<nb, VEC_THREADS, 0, s>>>(__VA_ARGS__, g_stop);                                   \
+        GIAMG_HIP(hipGetLastError());                                                                        \
+    } while (0)
 void launch_pcg_update(int64_t n, double* x, double* r, double* rold, const double* p,
-                       const double* q, const double* scal, double* partial, hipStream_t s) {
-    pcg_update_kernel<<<(unsigned)vec_blocks(n), VEC_THREADS, 0, s>>>(n, x, r, rold, p, q, scal, partial,
-                                                                    g_stop);
-    GIAMG_HIP(hipGetLastError());
+                       const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
+                       hipStream_t s) {
+    GIAMG_UPDATE(pcg_update_kernel, n, x, r, rold, p, q, scal, partial, pq, ctl);
 }
 
 // The flexible-CG update of a mixed-precision solve: also r_new rounded to
 // FP32 (f32, the V-cycle input), and with dinv32 set the fine level's FP32
 // zero-start Chebyshev init (cr = dinv32 f32, cd = cr inv_theta: the
 // operations of cheb_init0_kernel<float>, so the same bits).
-__global__ void __launch_bounds__(VEC_THREADS) pcg_update_mixed_kernel(
+template <bool CLOSE>
+__global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREADS) pcg_update_mixed_kernel(
     int64_t n, double* __restrict__ x, double* __restrict__ r, double* __restrict__ rold,
-    const double* __restrict__ p, const double* __restrict__ q, const double* __restrict__ scal,
-    double* __restrict__ partial, float* __restrict__ f32, const float* __restrict__ dinv32,
-    float* __restrict__ cr, float* __restrict__ cd, float inv_theta, const int* stop) {
-    if (stopped(stop)) return;
-    __shared__ double sh[VEC_THREADS];
-    const double alpha = scal[S_ALPHA];
+    const double* __restrict__ p, const double* __restrict__ q, double* scal, double* partial, PartialSums pq,
+    int* ctl, float* __restrict__ f32, const float* __restrict__ dinv32, float* __restrict__ cr,
+    float* __restrict__ cd, float inv_theta, const int* stop) {
+    __shared__ double sh[RED_THREADS / WAVE];
+    const int done = stop != nullptr ? *stop : 0;
+    const double alpha = fold_alpha(pq, scal, sh, done);
+    if (done) return;
+    const UpdateRows<CLOSE> rows;
     double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)VEC_THREADS + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * VEC_THREADS) {
+    for (int64_t i = rows.first; i < n; i += rows.step) {
         x[i] += alpha * p[i];
         const double ri = r[i];
         rold[i] = ri;
@@ -1291,28 +1453,29 @@ __global__ void __launch_bounds__(VEC_THREADS) pcg_update_mixed_kernel(
             cd[i] = res * inv_theta;
         }
     }
-    s = block_sum<VEC_THREADS>(s, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    update_sums<CLOSE>(s, partial, scal, ctl, sh);
 }
 void launch_pcg_update_mixed(int64_t n, double* x, double* r, double* rold, const double* p,
-                             const double* q, const double* scal, double* partial, float* f32,
-                             const float* dinv32, float* cr, float* cd, float inv_theta, hipStream_t s) {
-    pcg_update_mixed_kernel<<<(unsigned)vec_blocks(n), VEC_THREADS, 0, s>>>(
-        n, x, r, rold, p, q, scal, partial, f32, dinv32, cr, cd, inv_theta, g_stop);
-    GIAMG_HIP(hipGetLastError());
+                             const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
+                             float* f32, const float* dinv32, float* cr, float* cd, float inv_theta,
+                             hipStream_t s) {
+    GIAMG_UPDATE(pcg_update_mixed_kernel, n, x, r, rold, p, q, scal, partial, pq, ctl, f32, dinv32, cr, cd,
+                 inv_theta);
 }
 
-__global__ void __launch_bounds__(VEC_THREADS) pcg_update_cheb0_kernel(
+template <bool CLOSE>
+__global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREADS) pcg_update_cheb0_kernel(
     int64_t n, double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-    const double* __restrict__ q, const double* __restrict__ scal, double* __restrict__ partial,
+    const double* __restrict__ q, double* scal, double* partial, PartialSums pq, int* ctl,
     const double* __restrict__ dinv, double* __restrict__ cr, double* __restrict__ cd, double inv_theta,
     const int* stop) {
-    if (stopped(stop)) return;
-    __shared__ double sh[VEC_THREADS];
-    const double alpha = scal[S_ALPHA];
+    __shared__ double sh[RED_THREADS / WAVE];
+    const int done = stop != nullptr ? *stop : 0;
+    const double alpha = fold_alpha(pq, scal, sh, done);
+    if (done) return;
+    const UpdateRows<CLOSE> rows;
     double s = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)VEC_THREADS + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * VEC_THREADS) {
+    for (int64_t i = rows.first; i < n; i += rows.step) {
         x[i] += alpha * p[i];
         const double rn = r[i] - alpha * q[i];
         r[i] = rn;
@@ -1321,33 +1484,50 @@ __global__ void __launch_bounds__(VEC_THREADS) pcg_update_cheb0_kernel(
         cr[i] = res;
         cd[i] = res * inv_theta;
     }
-    s = block_sum<VEC_THREADS>(s, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+    update_sums<CLOSE>(s, partial, scal, ctl, sh);
 }
 void launch_pcg_update_cheb0(int64_t n, double* x, double* r, const double* p, const double* q,
-                             const double* scal, double* partial, const double* dinv, double* cr,
-                             double* cd, double inv_theta, hipStream_t s) {
-    pcg_update_cheb0_kernel<<<(unsigned)vec_blocks(n), VEC_THREADS, 0, s>>>(n, x, r, p, q, scal, partial,
-                                                                          dinv, cr, cd, inv_theta, g_stop);
-    GIAMG_HIP(hipGetLastError());
+                             double* scal, double* partial, const PartialSums& pq, int* ctl, const double* dinv,
+                             double* cr, double* cd, double inv_theta, hipStream_t s) {
+    GIAMG_UPDATE(pcg_update_cheb0_kernel, n, x, r, p, q, scal, partial, pq, ctl, dinv, cr, cd, inv_theta);
 }
+#undef GIAMG_UPDATE
 
+// S_RZ keeps r . z of the iteration before until the next alpha is formed.
 template <typename TZ>
-__global__ void pcg_direction_kernel(int64_t n, const TZ* __restrict__ z, double* __restrict__ p,
-                                     const double* __restrict__ scal, const int* stop) {
-    if (stopped(stop)) return;
-    const double beta = scal[S_BETA];
+__global__ void __launch_bounds__(VEC_THREADS) pcg_direction_kernel(int64_t n, const TZ* __restrict__ z,
+                                                                    double* __restrict__ p, double* scal,
+                                                                    PartialSums rz, const int* stop) {
+    const int done = stop != nullptr ? *stop : 0;
+    double beta;
+    if (rz.p == nullptr) {
+        beta = scal[S_BETA];
+    } else {
+        __shared__ double sh[RED_THREADS / WAVE];
+        constexpr bool flex = sizeof(TZ) == 4;
+        const double rzn = partials_sum<VEC_THREADS>(rz.p, rz.m, sh);
+        double zrold = 0.0;
+        if (flex) zrold = partials_sum<VEC_THREADS>(rz.p + rz.stride, rz.m, sh);
+        beta = flex ? (rzn - zrold) / scal[S_RZ] : rzn / scal[S_RZ];
+        if (blockIdx.x == 0 && threadIdx.x == 0 && !done) {
+            scal[S_RZNEW] = rzn;
+            if (flex) scal[S_ZROLD] = zrold;
+            scal[S_BETA] = beta;
+            if (!isfinite(rzn)) scal[S_FLAG] = 1.0;
+        }
+    }
+    if (done) return;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = (double)z[i] + beta * p[i];
 }
 template <typename TZ>
-void launch_pcg_direction(int64_t n, const TZ* z, double* p, const double* scal, hipStream_t s) {
-    pcg_direction_kernel<TZ><<<vgrid(n), VEC_THREADS, 0, s>>>(n, z, p, scal, g_stop);
+void launch_pcg_direction(int64_t n, const TZ* z, double* p, double* scal, const PartialSums& rz, hipStream_t s) {
+    pcg_direction_kernel<TZ><<<vgrid(n), VEC_THREADS, 0, s>>>(n, z, p, scal, rz, g_stop);
     GIAMG_HIP(hipGetLastError());
 }
-template void launch_pcg_direction<double>(int64_t, const double*, double*, const double*, hipStream_t);
-template void launch_pcg_direction<float>(int64_t, const float*, double*, const double*, hipStream_t);
+template void launch_pcg_direction<double>(int64_t, const double*, double*, double*, const PartialSums&, hipStream_t);
+template void launch_pcg_direction<float>(int64_t, const float*, double*, double*, const PartialSums&, hipStream_t);
 
 // power-iteration start vector v_i = 2 u(h(i)) - 1, h = SplitMix64 stream of
 // seed 0, u = top 53 bits scaled to [0, 1)

@@ -48,27 +48,33 @@ __device__ __forceinline__ T row_group_sum(T v) {
 template <typename T>
 struct RowIn {
     T f, dinv, r, x, v, y;
+    double dr, drold;
 };
 
 template <typename T, int MODE>
 __device__ __forceinline__ void epilogue_load(const SpmvArgs<T>& a, int64_t row, RowIn<T>& in) {
-    if constexpr (MODE == SPMV_RESID || MODE == SPMV_CHEB_INIT || MODE == SPMV_JACOBI ||
-                  MODE == SPMV_RINIT)
+    constexpr bool cheb = MODE == SPMV_CHEB_STEP || MODE == SPMV_CHEB_DOT;
+    constexpr bool jacobi = MODE == SPMV_JACOBI || MODE == SPMV_JACOBI_DOT;
+    if constexpr (MODE == SPMV_RESID || MODE == SPMV_CHEB_INIT || jacobi || MODE == SPMV_RINIT)
         in.f = a.f[row];
-    if constexpr (MODE == SPMV_CHEB_INIT || MODE == SPMV_CHEB_STEP || MODE == SPMV_JACOBI ||
-                  MODE == SPMV_DINV || MODE == SPMV_RCHEB0)
+    if constexpr (MODE == SPMV_CHEB_INIT || cheb || jacobi || MODE == SPMV_DINV || MODE == SPMV_RCHEB0)
         in.dinv = a.dinv[row];
-    if constexpr (MODE == SPMV_CHEB_STEP) {
+    if constexpr (cheb) {
         in.r = a.r[row];
         in.x = (a.flags & CHEB_ASSIGN) ? T(0) : a.x[row];
     }
-    if constexpr (MODE == SPMV_CHEB_STEP || MODE == SPMV_JACOBI || MODE == SPMV_DOT)
+    if constexpr (cheb || jacobi || MODE == SPMV_DOT)
         in.v = a.v[row];
+    if constexpr (MODE == SPMV_CHEB_DOT || MODE == SPMV_JACOBI_DOT) {
+        in.dr = a.dot_r[row];
+        if constexpr (sizeof(T) == 4) in.drold = a.dot_rold[row];
+    }
     if constexpr (MODE == SPMV_ADD) in.y = a.y[row];
 }
 
 // Row epilogue: y is (A v)_row.  `dot` collects this row's share of a block
-// partial (DOT: v.y; RINIT: f.f in dot, y.y in dot2).
+// partial (DOT: v.y; RINIT: f.f in dot, y.y in dot2; CHEB_DOT, JACOBI_DOT:
+// dot_r . result and, in FP32, dot_rold . result).
 template <typename T, int MODE>
 __device__ __forceinline__ void epilogue_store(const SpmvArgs<T>& a, int64_t row, T y,
                                                const RowIn<T>& in, double& dot, double& dot2) {
@@ -82,20 +88,30 @@ __device__ __forceinline__ void epilogue_store(const SpmvArgs<T>& a, int64_t row
         const T res = in.dinv * (in.f - y);
         a.r[row] = res;
         a.y[row] = res * a.inv_theta;
-    } else if constexpr (MODE == SPMV_CHEB_STEP) {
+    } else if constexpr (MODE == SPMV_CHEB_STEP || MODE == SPMV_CHEB_DOT) {
         const T rr = in.r - in.dinv * y;
         const T dn = a.c1 * in.v + a.c2 * rr;
         a.r[row] = rr;
         a.y[row] = dn;
         const T inc = (a.flags & CHEB_LAST) ? in.v + dn : in.v;
-        a.x[row] = in.x + inc;
+        const T xn = in.x + inc;
+        a.x[row] = xn;
+        if constexpr (MODE == SPMV_CHEB_DOT) {
+            dot += in.dr * (double)xn;
+            if constexpr (sizeof(T) == 4) dot2 += in.drold * (double)xn;
+        }
     } else if constexpr (MODE == SPMV_RCHEB0) {
         a.y[row] = y;
         const T res = in.dinv * y;
         a.r[row] = res;
         a.x[row] = res * a.inv_theta;
-    } else if constexpr (MODE == SPMV_JACOBI) {
-        a.y[row] = in.v + a.omega * in.dinv * (in.f - y);
+    } else if constexpr (MODE == SPMV_JACOBI || MODE == SPMV_JACOBI_DOT) {
+        const T xn = in.v + a.omega * in.dinv * (in.f - y);
+        a.y[row] = xn;
+        if constexpr (MODE == SPMV_JACOBI_DOT) {
+            dot += in.dr * (double)xn;
+            if constexpr (sizeof(T) == 4) dot2 += in.drold * (double)xn;
+        }
     } else if constexpr (MODE == SPMV_DOT) {
         a.y[row] = y;
         dot += (double)in.v * (double)y;
@@ -110,7 +126,9 @@ __device__ __forceinline__ void epilogue_store(const SpmvArgs<T>& a, int64_t row
 }
 
 template <int MODE>
-constexpr bool has_partials() { return MODE == SPMV_DOT || MODE == SPMV_RINIT; }
+constexpr bool has_partials() {
+    return MODE == SPMV_DOT || MODE == SPMV_RINIT || MODE == SPMV_CHEB_DOT || MODE == SPMV_JACOBI_DOT;
+}
 
 // Butterfly sum over the lanes of a wave with partners 32, 16, 8, 4, 2, 1 in
 // that order (the order of group_sum<WAVE>): the two steps across 16-lane
@@ -149,8 +167,10 @@ __device__ __forceinline__ void block_sum_to0(double* red, int tid, double& a, d
     }
 }
 
-template <int MODE>
-constexpr int n_partials() { return MODE == SPMV_RINIT ? 2 : 1; }
+template <typename T, int MODE>
+constexpr int n_partials() {
+    return MODE == SPMV_RINIT || (sizeof(T) == 4 && (MODE == SPMV_CHEB_DOT || MODE == SPMV_JACOBI_DOT)) ? 2 : 1;
+}
 
 // Row-local tail of a block product: acc = (A v)[row][col].
 template <typename T, int MODE>

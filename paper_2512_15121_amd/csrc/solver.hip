@@ -628,6 +628,8 @@ double spmv_bytes(int mode, const SpmvArgs<T>& a) {
         case SPMV_DINV: rows = 2; break;              // dinv, y
         case SPMV_RINIT: rows = 2; break;             // f, y
         case SPMV_RCHEB0: rows = 4; break;            // dinv, y, r, d_0
+        case SPMV_CHEB_DOT: rows = 6 + 8.0 * (vb == 4 ? 2 : 1) / vb; break;     // CHEB_STEP, r (r_old)
+        case SPMV_JACOBI_DOT: rows = 3 + 8.0 * (vb == 4 ? 2 : 1) / vb; break;
     }
     if (a.elem != nullptr) {   // element map, coefficients, element results out and in, node lists, vectors
         const ElementForm& E = *a.elem;
@@ -738,6 +740,22 @@ ChebCoef cheb_coef(const Handle& H, const Level& L) {
 }
 
 
+// Dots of the CG iteration that the V-cycle's last kernel can take along: the
+// partials of r . z (and r_old . z) at `partial`, m of them each if m > 0 on return.
+struct CgDots {
+    const double *r, *rold;
+    double* partial;
+    int64_t m = 0;
+};
+// The product `mode` of the fine level's last smoothing step with those dots.
+template <typename T>
+int with_dots(const Level& L, int mode, SpmvArgs<T>& a, CgDots* dots) {
+    if (dots == nullptr || !(L.elem_products || L.A.lean)) return mode;
+    a.dot_r = dots->r; a.dot_rold = dots->rold; a.partial = dots->partial;
+    dots->m = a.nblk;
+    return mode == SPMV_JACOBI ? SPMV_JACOBI_DOT : SPMV_CHEB_DOT;
+}
+
 // Chebyshev acceleration of Jacobi (Saad, Algorithm 12.1, on D^-1 A):
 //   r_0 = D^-1 (f - A x_0), d_0 = r_0 / theta,
 //   x_{j+1} = x_j + d_j,
@@ -753,7 +771,7 @@ ChebCoef cheb_coef(const Handle& H, const Level& L) {
 // shorter than those of A on the p-levels.
 template <typename T>
 void smooth_chebyshev(Handle& H, Level& L, const T* f, T* x, bool zero_start,
-                      const T* t = nullptr, const T* e = nullptr, bool init_done = false) {
+                      const T* t, const T* e, bool init_done, CgDots* dots) {
     const int k = H.opts.degree;
     const ChebCoef c = cheb_coef(H, L);
     T* r = LV<T>::r(L);
@@ -792,7 +810,7 @@ void smooth_chebyshev(Handle& H, Level& L, const T* f, T* x, bool zero_start,
             H.prof.pending.push_back({GIAMG_PHASE_FINE_STEP, H.prof.iter, H.prof.half, a.ev_start,
                                       a.ev_stop});
         }
-        run_spmv(H, SPMV_CHEB_STEP, a);
+        run_spmv(H, j == k - 1 ? with_dots(L, SPMV_CHEB_STEP, a, dots) : SPMV_CHEB_STEP, a);
     }
 }
 
@@ -805,20 +823,21 @@ bool fused_init_ok(const Handle& H) {
 
 // Weighted Jacobi x <- x + omega D^-1 (f - A x), ping-pong between x and d0.
 template <typename T>
-void smooth_jacobi(Handle& H, Level& L, const T* f, T* x, bool zero_start) {
+void smooth_jacobi(Handle& H, Level& L, const T* f, T* x, bool zero_start, CgDots* dots) {
     const int sweeps = H.opts.degree;
     const T w = (T)H.opts.omega;
     T* buf[2] = {x, LV<T>::d0(L)};
     int cur = 0, start = 0;
-    if (zero_start) {
+    if (zero_start) {   // from the buffer that ends the sweeps in x
+        cur = (sweeps - 1) & 1;
         H.bytes += 3.0 * sizeof(T) * L.n;
-        launch_jacobi0<T>(L.n, f, LV<T>::dinv(L), x, w, H.stream);
+        launch_jacobi0<T>(L.n, f, LV<T>::dinv(L), buf[cur], w, H.stream);
         start = 1;
     }
     for (int s = start; s < sweeps; ++s) {
         SpmvArgs<T> a = args_A<T>(L);
         a.v = buf[cur]; a.y = buf[1 - cur]; a.f = f; a.omega = w;
-        run_spmv(H, SPMV_JACOBI, a);
+        run_spmv(H, s == sweeps - 1 ? with_dots(L, SPMV_JACOBI, a, dots) : SPMV_JACOBI, a);
         cur = 1 - cur;
     }
     if (cur == 1) {
@@ -829,11 +848,11 @@ void smooth_jacobi(Handle& H, Level& L, const T* f, T* x, bool zero_start) {
 
 template <typename T>
 void smooth(Handle& H, Level& L, const T* f, T* x, bool zero_start, const T* t = nullptr,
-            const T* e = nullptr, bool init_done = false) {
+            const T* e = nullptr, bool init_done = false, CgDots* dots = nullptr) {
     if (H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV)
-        smooth_chebyshev<T>(H, L, f, x, zero_start, t, e, init_done);
+        smooth_chebyshev<T>(H, L, f, x, zero_start, t, e, init_done, dots);
     else
-        smooth_jacobi<T>(H, L, f, x, zero_start);
+        smooth_jacobi<T>(H, L, f, x, zero_start, dots);
 }
 
 template <typename T>
@@ -869,8 +888,9 @@ void prolong_add(Handle& H, Level& L, const T* ec, T* x) {
 
 // Algorithm 1: one V-cycle from level l for right-hand side f, result in x.
 // init_done: level l's zero-start smoother init was written with f (fused).
+// dots: for level l, taken along by its last smoothing step where that can.
 template <typename T>
-void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false) {
+void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false, CgDots* dots = nullptr) {
     Level& L = H.levels[l];
     if (l + 1 == H.levels.size()) {
         Phase ph(H, GIAMG_PHASE_COARSE);
@@ -904,9 +924,9 @@ void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false) {
     Phase ph(H, GIAMG_PHASE_SMOOTH);
     Phase ph0(H, l == 0 ? GIAMG_PHASE_FIRST_SMOOTH : -1);
     if (L.elem_products)   // A x costs less than (A P) e there
-        smooth<T>(H, L, f, x, false);
+        smooth<T>(H, L, f, x, false, nullptr, nullptr, false, dots);
     else
-        smooth<T>(H, L, f, x, false, LV<T>::t(L), LV<T>::x(C));
+        smooth<T>(H, L, f, x, false, LV<T>::t(L), LV<T>::x(C), false, dots);
 }
 
 // z = V-cycle(r).  init_done: the fine level's smoother init was fused into
@@ -914,7 +934,8 @@ void vcycle(Handle& H, size_t l, const T* f, T* x, bool init_done = false) {
 // (r rounded; r32_ready: the CG update wrote it) and z stays in FP32 in
 // level 0's x32 (zvec32), read by the dots and the direction update widened
 // exactly; z is not written.
-void precondition(Handle& H, const double* r, double* z, bool init_done = false, bool r32_ready = false) {
+void precondition(Handle& H, const double* r, double* z, bool init_done = false, bool r32_ready = false,
+                  CgDots* dots = nullptr) {
     if (H.opts.preconditioner == GIAMG_PRECOND_JACOBI) {   // z = D^-1 r
         Level& L = H.levels[0];
         H.bytes += 24.0 * L.n;
@@ -928,9 +949,9 @@ void precondition(Handle& H, const double* r, double* z, bool init_done = false,
             H.bytes += 12.0 * L.n;
             launch_convert<double, float>(L.n, r, L.f32.get(), H.stream);
         }
-        vcycle<float>(H, 0, L.f32.get(), L.x32.get(), init_done);
+        vcycle<float>(H, 0, L.f32.get(), L.x32.get(), init_done, dots);
     } else {
-        vcycle<double>(H, 0, r, z, init_done);
+        vcycle<double>(H, 0, r, z, init_done, dots);
     }
 }
 
@@ -1038,6 +1059,8 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
             // init rides on the CG update (bitwise the same vectors; FP32 in
             // mixed precision)
             const bool fused = fused_init_ok(H) && H.levels.size() > 1;
+            // r . z with the last smoothing step, but where bits are kept (element_form_allowed)
+            const bool dots_ride = element_form_allowed(H) && H.levels.size() > 1;
             double* xi = w.x;
             H.bytes += 16.0 * n;
             launch_copy<double>(n, x, xi, s);
@@ -1053,60 +1076,65 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
                     H.bytes += (flexible ? 56.0 : 48.0) * n;
                     run_spmv(H, SPMV_DOT, a);
                 }
-                {
+                // the scalars in launches of their own, or by the kernels that need them
+                PartialSums pq, rz;
+                double* rr = w.partial;
+                if (gs <= FOLD_PARTIALS) {
+                    pq = {w.partial, gs, 0};
+                    rr += gs;
+                } else {
                     Phase ph(H, GIAMG_PHASE_CG_DOT);
                     launch_reduce(gs, w.partial, 0, 1, w.scal + S_PQ, st, FIN_ALPHA, w.scal);
                 }
+                int* close = update_closes(n) ? w.ctl : nullptr;
                 {
                     Phase ph(H, GIAMG_PHASE_CG_UPDATE);
+                    Level& F = H.levels[0];
                     if (flexible) {   // also r in FP32 (and level 0's FP32 Chebyshev r_0, d_0)
-                        Level& F = H.levels[0];
                         H.bytes += (fused ? 16.0 : 4.0) * n;
-                        launch_pcg_update_mixed(n, xi, w.r, w.rold, w.p, w.q,
-                                                w.scal, w.partial, F.f32.get(),
+                        launch_pcg_update_mixed(n, xi, w.r, w.rold, w.p, w.q, w.scal, rr, pq, close, F.f32.get(),
                                                 fused ? F.dinv32.get() : nullptr, F.r32.get(),
                                                 F.d032.get(), (float)cheb_coef(H, F).inv_theta, st);
                     } else if (fused) {   // the update also writes level 0's Chebyshev r_0, d_0
-                        Level& F = H.levels[0];
                         H.bytes += 24.0 * n;
-                        launch_pcg_update_cheb0(n, xi, w.r, w.p, w.q, w.scal,
-                                                w.partial, F.dinv.get(), F.r.get(), F.d0.get(),
-                                                cheb_coef(H, F).inv_theta, st);
+                        launch_pcg_update_cheb0(n, xi, w.r, w.p, w.q, w.scal, rr, pq, close, F.dinv.get(),
+                                                F.r.get(), F.d0.get(), cheb_coef(H, F).inv_theta, st);
                     } else {
-                        launch_pcg_update(n, xi, w.r, flexible ? w.rold : nullptr, w.p,
-                                          w.q, w.scal, w.partial, st);
+                        launch_pcg_update(n, xi, w.r, nullptr, w.p, w.q, w.scal, rr, pq, close, st);
                     }
                 }
-                {
+                if (!close) {
                     Phase ph(H, GIAMG_PHASE_CG_DOT);
-                    launch_reduce(gv, w.partial, 0, 1, w.scal + S_RR, st, FIN_CONV,
-                                  w.scal, w.ctl);
+                    launch_reduce(gv, rr, 0, 1, w.scal + S_RR, st, FIN_CONV, w.scal, w.ctl);
                 }
                 const double b1 = H.bytes;
                 H.prof.half = 2;
-                precondition(H, w.r, w.z, fused, flexible);
-                if (flexible) {
-                    {
-                        Phase ph(H, GIAMG_PHASE_CG_DOT);
-                        H.bytes += 20.0 * n;
+                CgDots dots{w.r, w.rold, w.partial};
+                precondition(H, w.r, w.z, fused, flexible, dots_ride ? &dots : nullptr);
+                int64_t m = dots.m;
+                if (m == 0) {
+                    Phase ph(H, GIAMG_PHASE_CG_DOT);
+                    m = gv;
+                    H.bytes += (flexible ? 20.0 : 16.0) * n;
+                    if (flexible)
                         launch_dot2_partial(n, w.r, zvec32(H), w.rold, w.partial, st);
-                        launch_reduce(gv, w.partial, gv, 2, w.scal + S_RZNEW, st, FIN_BETA_FLEX,
-                                      w.scal);
-                    }
-                    Phase ph(H, GIAMG_PHASE_CG_UPDATE);
-                    H.bytes += 20.0 * n;
-                    launch_pcg_direction(n, zvec32(H), w.p, w.scal, st);
-                } else {
-                    {
-                        Phase ph(H, GIAMG_PHASE_CG_DOT);
-                        H.bytes += 16.0 * n;
+                    else
                         launch_dot_partial(n, w.r, w.z, w.partial, st);
-                        launch_reduce(gv, w.partial, 0, 1, w.scal + S_RZNEW, st, FIN_BETA,
-                                      w.scal);
-                    }
+                }
+                if (m <= FOLD_PARTIALS) {
+                    rz = {w.partial, m, m};
+                } else {
+                    Phase ph(H, GIAMG_PHASE_CG_DOT);
+                    launch_reduce(m, w.partial, m, flexible ? 2 : 1, w.scal + S_RZNEW, st,
+                                  flexible ? FIN_BETA_FLEX : FIN_BETA, w.scal);
+                }
+                {
                     Phase ph(H, GIAMG_PHASE_CG_UPDATE);
-                    H.bytes += 24.0 * n;
-                    launch_pcg_direction(n, w.z, w.p, w.scal, st);
+                    H.bytes += (flexible ? 20.0 : 24.0) * n;
+                    if (flexible)
+                        launch_pcg_direction(n, zvec32(H), w.p, w.scal, rz, st);
+                    else
+                        launch_pcg_direction(n, w.z, w.p, w.scal, rz, st);
                 }
                 H.prof.half = 0;
                 H.it_part1 = b1 - b0;

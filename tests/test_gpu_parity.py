@@ -839,3 +839,30 @@ def test_jacobi_pcg_baseline_parity(torch_dev):
     with pytest.raises(giamg.GiamgError) as e:
         _solver(name, preconditioner="jacobi", precision="mixed")
     assert e.value.code == giamg.EINVAL
+
+
+# (n, p, options): update blocks of 1024 rows: one, exactly four (the update ends
+# the iteration itself up to there), five, and too many partials to be added in
+# the kernels that need them; r . z with and without a last smoothing step to ride on
+CG_SIZES = [(4, 2, {}), (4, 2, {"smoother": "jacobi"}), (4, 2, {"smoother": "jacobi", "degree": 3}),
+            (5, 3, {"degree": 1}), (5, 3, {}), (8, 2, {}), (8, 2, {"smoother": "jacobi", "degree": 1}), (22, 3, {})]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,p,kw", CG_SIZES)
+def test_cg_scalars_at_the_edges_of_their_forms(torch_dev, n, p, kw, precision):
+    """Single and batched solves share no CG kernel; both stop at a relative
+    residual of 1e-10 of the same operator, so they are 1e-8 apart at most."""
+    torch, dev = torch_dev
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=6)
+    s = Solver(m.coords, m.l2g, p, 2.0, Options(precision=precision, **kw))
+    b = torch.from_numpy(synth.normal_rhs(m.n_nodes, 8)).to(dev)
+    x, info = s.solve(b)
+    X, infos = s.solve_batch(b.reshape(-1, 1).contiguous())
+    assert info.status == 0 and info.relres < 1e-10 and info.true_relres < 1e-9
+    assert abs(info.iters - infos[0].iters) <= 1
+    assert torch.linalg.norm(x - X[:, 0]) <= 1e-8 * torch.linalg.norm(x)
+    again, _ = s.solve(b)
+    assert torch.equal(x, again)
+    s.close()
