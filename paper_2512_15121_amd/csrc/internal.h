@@ -353,6 +353,9 @@ HostCSR sa_transfer(const HostCSR& A, uint64_t seed, double theta, std::vector<i
 HostCSR transpose(const HostCSR& M);
 // dense SPD inverse through Cholesky; returns false if not positive definite.
 bool spd_inverse(const std::vector<double>& A, int64_t n, std::vector<double>& inv);
+// The same of a device operator, exactly symmetric, by block sweeps on the
+// device (dense.hip); inv is allocated, and of no use if false is returned.
+bool spd_inverse_device(const DevCSR& A, DevBuf<double>& inv, hipStream_t s);
 
 uint64_t splitmix64(uint64_t seed, uint64_t i);
 // Checks of a mesh and options before a hierarchy is built (giamg_setup and

@@ -473,12 +473,17 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         Level& Lc = H.levels.back();
         H.nc = Lc.n;
         GIAMG_REQUIRE(H.nc <= 16384, "coarsest level too large for the dense solve");
-        HostCSR Ah;
-        download_csr(Lc.A, Ah, H.stream);
-        std::vector<double> dense(H.nc * H.nc, 0.0), inv;
-        for (int64_t i = 0; i < H.nc; ++i)
-            for (int64_t s = Ah.rp[i]; s < Ah.rp[i + 1]; ++s) dense[i * H.nc + Ah.ci[s]] = Ah.val[s];
-        if (H.nc > 0) {
+        // On the device from two tiles on (64 rows: 0.1 ms either way; 512 rows: host 8.8 ms,
+        // device 0.6; 1331 rows: 86 and 1.3), but where bits are kept (element_form_allowed).
+        if (H.nc > 64 && element_form_allowed(H)) {
+            if (!spd_inverse_device(Lc.A, H.coarse_inv, H.stream))
+                throw Error(GIAMG_EINVAL, "coarsest operator is not positive definite");
+        } else if (H.nc > 0) {
+            HostCSR Ah;
+            download_csr(Lc.A, Ah, H.stream);
+            std::vector<double> dense(H.nc * H.nc, 0.0), inv;
+            for (int64_t i = 0; i < H.nc; ++i)
+                for (int64_t s = Ah.rp[i]; s < Ah.rp[i + 1]; ++s) dense[i * H.nc + Ah.ci[s]] = Ah.val[s];
             if (!spd_inverse(dense, H.nc, inv))
                 throw Error(GIAMG_EINVAL, "coarsest operator is not positive definite");
             H.coarse_inv.alloc(H.nc * H.nc);

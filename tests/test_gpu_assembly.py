@@ -150,3 +150,33 @@ def test_device_p_transfer_matches_host_bitwise(torch_dev, name):
         for a, b in ((pd, ph), (rd, rh)):
             assert all(np.array_equal(x, y) for x, y in zip(a, b))
         assert np.array_equal(gd, gh)
+
+
+# (mesh size, boundary condition) of an order-1 operator that is its own coarsest
+# level, (n + 1)^3 rows: 2 tiles of 64 rows with 61 in the last, 6 with 23, 8 full
+# ones, 12 with 25
+@pytest.mark.parametrize("n,bc", [(4, "dirichlet"), (6, "dirichlet"), (6, "pin"), (7, "dirichlet"), (8, "dirichlet")])
+def test_coarsest_inverse_on_the_device(n, bc):
+    """Against LAPACK's inverse, to the bound of the host's inverse (n eps cond,
+    with cond below 1e3: 1e-11), and exactly symmetric."""
+    import scipy.sparse as sp
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, 1, perturb=0.1, seed=3)
+    s = Solver(m.coords, m.l2g, 1, 2.0, Options(bc=bc, coarse_max=2000))
+    l = s.num_levels() - 1
+    rp, ci, val = s.level_csr(l)
+    A = sp.csr_matrix((val, ci, rp)).toarray()
+    nc = A.shape[0]
+    f = torch.zeros(nc, dtype=torch.float64, device="cuda:0")
+    out = torch.zeros_like(f)
+    X = np.empty((nc, nc))
+    for c in range(nc):
+        f[c] = 1.0
+        s.apply("coarse", l, f, out=out)
+        X[:, c] = out.cpu().numpy()
+        f[c] = 0.0
+    s.close()
+    ref = np.linalg.inv(A)
+    assert np.array_equal(X, X.T)
+    assert np.max(np.abs(X - ref)) <= 1e-11 * np.max(np.abs(ref))
