@@ -238,6 +238,9 @@ enum ScalarSlot : int {
 // CG control block (device ints): stop flag, iterations done, iteration cap
 enum CtlSlot : int { C_STOP = 0, C_ITERS = 1, C_MAXIT = 2, C_COUNT = 4 };
 
+// Before a solve: all scalars 0 but the tolerance, the control block {0, 0, maxit}.
+void launch_cg_begin(double tol, int maxit, double* scal, int* ctl, hipStream_t s);
+
 // While a StopScope is open, every kernel this thread launches through the
 // wrappers of this header returns at once once *flag is nonzero.
 class StopScope {

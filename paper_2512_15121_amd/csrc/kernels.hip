@@ -1493,6 +1493,16 @@ void launch_pcg_update_cheb0(int64_t n, double* x, double* r, const double* p, c
 }
 #undef GIAMG_UPDATE
 
+__global__ void cg_begin_kernel(double tol, int maxit, double* scal, int* ctl) {
+    const int i = threadIdx.x;
+    if (i < S_COUNT) scal[i] = i == S_TOL ? tol : 0.0;
+    if (i < C_COUNT) ctl[i] = i == C_MAXIT ? maxit : 0;
+}
+void launch_cg_begin(double tol, int maxit, double* scal, int* ctl, hipStream_t s) {
+    cg_begin_kernel<<<1, WAVE, 0, s>>>(tol, maxit, scal, ctl);
+    GIAMG_HIP(hipGetLastError());
+}
+
 // S_RZ keeps r . z of the iteration before until the next alpha is formed.
 template <typename TZ>
 __global__ void __launch_bounds__(VEC_THREADS) pcg_direction_kernel(int64_t n, const TZ* __restrict__ z,

@@ -1011,7 +1011,7 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
     H.prof.iter = 0;
     H.prof.half = 0;
     GIAMG_HIP(hipEventRecord(H.ev0, s));
-    launch_fill(S_COUNT, 0.0, w.scal, s);
+    launch_cg_begin(tol, H.opts.maxit, w.scal, w.ctl, s);   // scalars and control block of the whole solve
     launch_nonzero_flag(n, x, w.scal + S_XNZ, s);
     rinit(w.r, true);
     launch_reduce(gs, w.partial, gs, 2, w.scal + S_BB, s);
@@ -1027,15 +1027,6 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
     } else {
         relres = std::sqrt(H.host_scal[S_RR]) / bnorm;
         if (!(relres < tol) && H.opts.maxit > 0) {
-            // device-side convergence test: tolerance and control block
-            H.host_scal[S_TOL] = tol;
-            GIAMG_HIP(hipMemcpyAsync(w.scal + S_TOL, H.host_scal + S_TOL, sizeof(double),
-                                     hipMemcpyHostToDevice, s));
-            H.host_ctl[C_STOP] = 0;
-            H.host_ctl[C_ITERS] = 0;
-            H.host_ctl[C_MAXIT] = H.opts.maxit;
-            H.host_ctl[3] = 0;
-            GIAMG_HIP(hipMemcpyAsync(w.ctl, H.host_ctl, C_COUNT * sizeof(int), hipMemcpyHostToDevice, s));
             precondition(H, w.r, w.z);
             if (flexible) {
                 H.bytes += 32.0 * n;
@@ -1186,6 +1177,8 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
                     launched += todo;
                     GIAMG_HIP(hipMemcpyAsync(H.host_ctl, w.ctl, C_COUNT * sizeof(int),
                                              hipMemcpyDeviceToHost, its));
+                    GIAMG_HIP(hipMemcpyAsync(H.host_scal, w.scal, S_COUNT * sizeof(double),
+                                             hipMemcpyDeviceToHost, its));
                     GIAMG_HIP(hipStreamSynchronize(its));
                     if (H.host_ctl[C_STOP] != 0 || launched >= H.opts.maxit) break;
                     chunk = 1;
@@ -1207,7 +1200,6 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
             // bytes of the work that ran: the iteration that stopped skipped its second half
             const int halves2 = std::max(0, (stop == 2 ? iters : iters - 1));
             H.bytes = bytes0 + 16.0 * n + part1 * (stop == 2 ? iters + 1 : iters) + part2 * halves2;
-            fetch_scalars(H, w.scal);
             relres = std::sqrt(H.host_scal[S_RR]) / bnorm;
         } else if (!(relres < tol)) {
             status = GIAMG_ENOTCONV;
