@@ -893,14 +893,188 @@ void launch_node_block(const SpmmArgs<T>& a, const ElementForm& E, const T* ev, 
         element_node_block_kernel<T, MODE, 1><<<grid, NODE_THREADS, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
 }
 
+// ---------------------------------------------------------------------------
+// Transfers between the fine level and the next order q (M = q + 1 coarse nodes per
+// axis): contraction of an element's values with the 1-D interpolation along one
+// axis after the other.  A block takes V elements, each thread a line at a time.
+// The rows of P hold 8 entries on average at p = 4; the element form reads no entry
+// but the maps and the vectors.  32^3 p = 4, FP64: P 47 -> 23 us (map, coarse values, x
+// read and written: 55 MB; bound by its chain of three passes and the scattered
+// update of x), R 42 -> 14 + 8 us (its node step adds a coarse node's elements);
+// 13^3 p = 5 to order 3: 25 -> 6 and 26 -> 10 us.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct XferArgs {
+    int64_t ne = 0;
+    int M = 0;
+    const int32_t* own = nullptr;
+    const int32_t* cmap = nullptr;
+    const T* i1 = nullptr;           // [p + 1][M]
+    const T* v = nullptr;
+    T* y = nullptr;                  // R: element results [ne][M^3]; P: the fine vector
+    const int* stop = nullptr;
+};
+constexpr int XFER_THREADS = 256;
+template <int P> constexpr int xfer_elems() { return XFER_THREADS / ((P + 1) * (P + 1)); }
+
+template <typename T, int P>
+__global__ void __launch_bounds__(XFER_THREADS) element_restrict_kernel(XferArgs<T> a) {
+#pragma clang fp contract(off)
+    constexpr int N = P + 1, N2 = N * N, N3 = N2 * N, V = xfer_elems<P>(), ITER = (V * N3 + XFER_THREADS - 1) / XFER_THREADS;
+    __shared__ T s0[V * N3], s1[V * N2 * P], si[N * P];
+    const int done = a.stop != nullptr ? *a.stop : 0;
+    const int tid = threadIdx.x, M = a.M;
+    const int64_t first = xcd_block(blockIdx.x, gridDim.x) * V;
+    const int cnt = (int)min((int64_t)V, a.ne - first);
+    const int32_t* __restrict__ own = a.own + first * N3;
+    int32_t g[ITER];
+    T x[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) g[it] = own[min(tid + it * XFER_THREADS, cnt * N3 - 1)];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) x[it] = a.v[max(g[it], 0)];
+    if (tid < N * M) si[tid] = a.i1[tid];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+        const int t = tid + it * XFER_THREADS;
+        if (t < V * N3) s0[t] = g[it] >= 0 ? x[it] : T(0);
+    }
+    __syncthreads();
+    if (done) return;
+    if (tid < cnt * N2) {   // z: [i][j][k] -> [i][j][c]
+        T l[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) l[k] = s0[tid * N + k];
+        for (int c = 0; c < M; ++c) {
+            T r = 0;
+#pragma unroll
+            for (int k = 0; k < N; ++k) r = mad(si[k * M + c], l[k], r);
+            s1[tid * M + c] = r;
+        }
+    }
+    __syncthreads();
+    const unsigned m = M, m2 = m * m;
+    for (unsigned t = tid; t < cnt * N * m; t += XFER_THREADS) {   // y: -> [i][b][c]
+        const unsigned vi = t / m, c = t - vi * m;
+        T l[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) l[j] = s1[(vi * N + j) * m + c];
+        for (unsigned b = 0; b < m; ++b) {
+            T r = 0;
+#pragma unroll
+            for (int j = 0; j < N; ++j) r = mad(si[j * m + b], l[j], r);
+            s0[vi * m2 + b * m + c] = r;
+        }
+    }
+    __syncthreads();
+    for (unsigned t = tid; t < cnt * m2; t += XFER_THREADS) {      // x: -> [a][b][c]
+        const unsigned e = t / m2, bc = t - e * m2;
+        T l[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) l[i] = s0[(e * N + i) * m2 + bc];
+        T* out = a.y + (first + e) * m2 * m + bc;
+        for (unsigned q = 0; q < m; ++q) {
+            T r = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) r = mad(si[i * m + q], l[i], r);
+            out[q * m2] = r;
+        }
+    }
+}
+
+template <typename T, int P>
+__global__ void __launch_bounds__(XFER_THREADS) element_prolong_kernel(XferArgs<T> a) {
+#pragma clang fp contract(off)
+    constexpr int N = P + 1, N2 = N * N, N3 = N2 * N, V = xfer_elems<P>(), ITER = (V * N3 + XFER_THREADS - 1) / XFER_THREADS;
+    __shared__ T s0[V * N2 * P], s1[V * N3], si[N * P];
+    const int done = a.stop != nullptr ? *a.stop : 0;
+    const int tid = threadIdx.x;
+    const unsigned m = a.M, m2 = m * m, m3 = m2 * m;
+    const int64_t first = xcd_block(blockIdx.x, gridDim.x) * V;
+    const int cnt = (int)min((int64_t)V, a.ne - first);
+    const int32_t* __restrict__ own = a.own + first * N3;
+    const int32_t* __restrict__ cmap = a.cmap + first * m3;
+    int32_t g[ITER];
+    T y[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) g[it] = own[min(tid + it * XFER_THREADS, cnt * N3 - 1)];
+    if (tid < N * (int)m) si[tid] = a.i1[tid];
+    for (unsigned t = tid; t < cnt * m3; t += XFER_THREADS) {
+        const int32_t c = cmap[t];
+        s0[t] = c >= 0 ? a.v[c] : T(0);
+    }
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) y[it] = a.y[max(g[it], 0)];
+    __syncthreads();
+    if (done) return;
+    for (unsigned t = tid; t < cnt * m2; t += XFER_THREADS) {      // x: [a][b][c] -> [i][b][c]
+        const unsigned e = t / m2, bc = t - e * m2;
+        T r[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) r[i] = 0;
+        for (unsigned q = 0; q < m; ++q) {
+            const T c = s0[e * m3 + q * m2 + bc];
+#pragma unroll
+            for (int i = 0; i < N; ++i) r[i] = mad(si[i * m + q], c, r[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) s1[(e * N + i) * m2 + bc] = r[i];
+    }
+    __syncthreads();
+    for (unsigned t = tid; t < cnt * N * m; t += XFER_THREADS) {   // y: -> [i][j][c]
+        const unsigned vi = t / m, c = t - vi * m;
+        T r[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) r[j] = 0;
+        for (unsigned b = 0; b < m; ++b) {
+            const T w = s1[vi * m2 + b * m + c];
+#pragma unroll
+            for (int j = 0; j < N; ++j) r[j] = mad(si[j * m + b], w, r[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) s0[(vi * N + j) * m + c] = r[j];
+    }
+    __syncthreads();
+    if (tid < cnt * N2) {                                          // z: -> [i][j][k]
+        T r[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) r[k] = 0;
+        for (unsigned c = 0; c < m; ++c) {
+            const T w = s0[tid * m + c];
+#pragma unroll
+            for (int k = 0; k < N; ++k) r[k] = mad(si[k * m + c], w, r[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) s1[tid * N + k] = r[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+        const int t = tid + it * XFER_THREADS;
+        if (t < cnt * N3 && g[it] >= 0) a.y[g[it]] = y[it] + s1[t];
+    }
+}
+
+__global__ void transfer_own_kernel(int64_t m, const int32_t* __restrict__ map, const int32_t* __restrict__ nptr,
+                                    const int32_t* __restrict__ nent, int32_t* __restrict__ own) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < m; t += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t g = map[t];
+        own[t] = g >= 0 && nent[nptr[g]] == t ? g : -1;
+    }
+}
+
 template <typename T, int MODE>
-void launch_node_kernel(const SpmvArgs<T>& a, const ElementForm& E, const T* ev, hipStream_t s) {
+void launch_node_lists(const SpmvArgs<T>& a, const int32_t* nptr, const int32_t* nent, const T* ev, hipStream_t s) {
     const dim3 grid((unsigned)a.nblk), block(NODE_THREADS);
     if (a.ev_stop != nullptr)
-        hipExtLaunchKernelGGL((element_node_kernel<T, MODE>), grid, block, 0, s, nullptr, a.ev_stop, 0, a,
-                              E.nptr.get(), E.nent.get(), ev);
+        hipExtLaunchKernelGGL((element_node_kernel<T, MODE>), grid, block, 0, s, nullptr, a.ev_stop, 0, a, nptr, nent,
+                              ev);
     else
-        element_node_kernel<T, MODE><<<grid, block, 0, s>>>(a, E.nptr.get(), E.nent.get(), ev);
+        element_node_kernel<T, MODE><<<grid, block, 0, s>>>(a, nptr, nent, ev);
+}
+template <typename T, int MODE>
+void launch_node_kernel(const SpmvArgs<T>& a, const ElementForm& E, const T* ev, hipStream_t s) {
+    launch_node_lists<T, MODE>(a, E.nptr.get(), E.nent.get(), ev, s);
 }
 
 template <typename T> const T* form_coef(const ElementForm& E);
@@ -968,6 +1142,46 @@ void launch_element_product(int mode, const SpmvArgs<T>& args, hipStream_t s) {
     GIAMG_HIP(hipGetLastError());
 }
 template <typename T>
+void launch_transfer(int mode, const SpmvArgs<T>& args, hipStream_t s) {
+    SpmvArgs<T> a = args;
+    const TransferForm& X = *a.xfer;
+    const bool down = mode != SPMV_ADD;
+    XferArgs<T> x;
+    x.ne = X.ne; x.M = X.q + 1; x.own = X.own.get(); x.cmap = X.cmap.get();
+    if constexpr (sizeof(T) == 8) x.i1 = X.i1.get(); else x.i1 = X.i132.get();
+    x.v = a.v; x.y = down ? reinterpret_cast<T*>(X.ev) : a.y; x.stop = a.stop;
+    if (x.i1 == nullptr) throw Error(GIAMG_EINVAL, "transfer form without this precision");
+    const hipEvent_t end = down ? nullptr : a.ev_stop;
+#define GIAMG_XFER(P)                                                                                     \
+    case P: {                                                                                             \
+        const dim3 grid((unsigned)((X.ne + xfer_elems<P>() - 1) / xfer_elems<P>())), block(XFER_THREADS); \
+        auto* k = down ? element_restrict_kernel<T, P> : element_prolong_kernel<T, P>;                    \
+        if (a.ev_start != nullptr)                                                                        \
+            hipExtLaunchKernelGGL(k, grid, block, 0, s, a.ev_start, end, 0, x);                           \
+        else                                                                                              \
+            k<<<grid, block, 0, s>>>(x);                                                                  \
+        break;                                                                                            \
+    }
+    switch (X.p) {
+        GIAMG_XFER(2) GIAMG_XFER(3) GIAMG_XFER(4) GIAMG_XFER(5) GIAMG_XFER(6)
+        GIAMG_XFER(7) GIAMG_XFER(8) GIAMG_XFER(9) GIAMG_XFER(10)
+        default: throw Error(GIAMG_EINVAL, "transfer form of an unsupported order");
+    }
+#undef GIAMG_XFER
+    if (down) {   // every coarse node has entries, so the node step never looks at v
+        a.nblk = element_blocks(a.n);
+        switch (mode) {
+            case SPMV_PLAIN: launch_node_lists<T, SPMV_PLAIN>(a, X.nptr.get(), X.nent.get(), x.y, s); break;
+            case SPMV_RCHEB0: launch_node_lists<T, SPMV_RCHEB0>(a, X.nptr.get(), X.nent.get(), x.y, s); break;
+            default: throw Error(GIAMG_EINVAL, "unknown product mode of the transfer form");
+        }
+    }
+    GIAMG_HIP(hipGetLastError());
+}
+template void launch_transfer<double>(int, const SpmvArgs<double>&, hipStream_t);
+template void launch_transfer<float>(int, const SpmvArgs<float>&, hipStream_t);
+
+template <typename T>
 void launch_element_block(int mode, const SpmmArgs<T>& a, const ElementForm& E, double* ev, hipStream_t s) {
     ElemArgs<T> e;
     e.ne = E.ne; e.map = E.map.get(); e.v = a.v; e.ev = reinterpret_cast<T*>(ev);
@@ -1022,6 +1236,27 @@ void build_element_matrices(ElementForm& E, bool mixed, hipStream_t s) {
     GIAMG_HIP(hipStreamSynchronize(s));
     E.mat = std::move(mat);
     E.mat32 = std::move(mat32);
+}
+
+// Per node its entries of map[m], ascending.
+static void build_node_lists(const int32_t* map, int64_t m, int64_t n, DevBuf<int32_t>& nptr, DevBuf<int32_t>& nent,
+                      hipStream_t s) {
+    DevBuf<int32_t> counts((size_t)n);
+    GIAMG_HIP(hipMemsetAsync(counts.get(), 0, n * sizeof(int32_t), s));
+    node_count_kernel<<<setup_grid(m), 256, 0, s>>>(m, map, counts.get());
+    GIAMG_HIP(hipGetLastError());
+    std::vector<int32_t> hc((size_t)n), ptr((size_t)n + 1, 0);
+    GIAMG_HIP(hipMemcpyAsync(hc.data(), counts.get(), n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    GIAMG_HIP(hipStreamSynchronize(s));
+    for (int64_t i = 0; i < n; ++i) ptr[i + 1] = ptr[i] + hc[i];
+    nptr.alloc((size_t)n + 1);
+    nent.alloc((size_t)std::max<int32_t>(ptr[n], 1));
+    GIAMG_HIP(hipMemcpyAsync(nptr.get(), ptr.data(), ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    GIAMG_HIP(hipMemsetAsync(counts.get(), 0, n * sizeof(int32_t), s));
+    node_place_kernel<<<setup_grid(m), 256, 0, s>>>(m, map, nptr.get(), counts.get(), nent.get());
+    node_sort_kernel<<<setup_grid(n), 256, 0, s>>>(n, nptr.get(), nent.get());
+    GIAMG_HIP(hipGetLastError());
+    GIAMG_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
 }
 
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
@@ -1110,23 +1345,38 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
         E.tabs32.alloc(tabs.size());
         launch_convert<double, float>((int64_t)tabs.size(), E.tabs.get(), E.tabs32.get(), s);
     }
-    // node -> entries
-    DevBuf<int32_t> counts((size_t)n);
-    GIAMG_HIP(hipMemsetAsync(counts.get(), 0, n * sizeof(int32_t), s));
-    node_count_kernel<<<setup_grid(m), 256, 0, s>>>(m, E.map.get(), counts.get());
+    build_node_lists(E.map.get(), m, n, E.nptr, E.nent, s);
+}
+
+void build_transfer_form(TransferForm& X, const ElementForm& E, const std::vector<int32_t>& coarse_l2g, int q,
+                         int64_t n_coarse, bool mixed, hipStream_t s) {
+    const int p = E.order, N = p + 1, M = q + 1;
+    const int64_t m = E.ne * N * N * N, mc = E.ne * M * M * M;
+    GIAMG_REQUIRE(q >= 1 && q < p && (int64_t)coarse_l2g.size() == mc, "transfer form of unexpected sizes");
+    std::vector<double> xp, xq, w, i1;
+    gll_points(p, xp, w);
+    gll_points(q, xq, w);
+    for (int i = 0; i < N; ++i)
+        for (int c = 0; c < M; ++c) {
+            const double v = lagrange_value(xq, c, xp[i]);
+            i1.push_back(std::fabs(v) <= 1e-12 ? 0.0 : v);   // the structural zeros of p_transfer_maps
+        }
+    X.p = p;
+    X.ne = E.ne;
+    X.ev = E.ev.get();
+    X.own.alloc((size_t)m);
+    X.cmap.alloc((size_t)mc);
+    X.i1.alloc(i1.size());
+    transfer_own_kernel<<<setup_grid(m), 256, 0, s>>>(m, E.map.get(), E.nptr.get(), E.nent.get(), X.own.get());
     GIAMG_HIP(hipGetLastError());
-    std::vector<int32_t> hc((size_t)n), ptr((size_t)n + 1, 0);
-    GIAMG_HIP(hipMemcpyAsync(hc.data(), counts.get(), n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    GIAMG_HIP(hipStreamSynchronize(s));
-    for (int64_t i = 0; i < n; ++i) ptr[i + 1] = ptr[i] + hc[i];
-    E.nptr.alloc((size_t)n + 1);
-    E.nent.alloc((size_t)std::max<int32_t>(ptr[n], 1));
-    GIAMG_HIP(hipMemcpyAsync(E.nptr.get(), ptr.data(), ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    GIAMG_HIP(hipMemsetAsync(counts.get(), 0, n * sizeof(int32_t), s));
-    node_place_kernel<<<setup_grid(m), 256, 0, s>>>(m, E.map.get(), E.nptr.get(), counts.get(), E.nent.get());
-    node_sort_kernel<<<setup_grid(n), 256, 0, s>>>(n, E.nptr.get(), E.nent.get());
-    GIAMG_HIP(hipGetLastError());
-    GIAMG_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
+    GIAMG_HIP(hipMemcpyAsync(X.cmap.get(), coarse_l2g.data(), mc * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    GIAMG_HIP(hipMemcpyAsync(X.i1.get(), i1.data(), i1.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    if (mixed) {
+        X.i132.alloc(i1.size());
+        launch_convert<double, float>((int64_t)i1.size(), X.i1.get(), X.i132.get(), s);
+    }
+    build_node_lists(X.cmap.get(), mc, n_coarse, X.nptr, X.nent, s);
+    X.q = q;
 }
 
 }  // namespace giamg

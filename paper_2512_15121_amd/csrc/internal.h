@@ -198,6 +198,24 @@ struct ElementForm {
                (int64_t)(coef32.n + tabs32.n + mat32.n) * 4;
     }
 };
+// The p-transfer below the fine level in the element form's terms: P and R = P^T
+// are the 1-D interpolation along each axis of an element, every free fine node
+// taken from the first of its elements.  q == 0: not built.
+struct TransferForm {
+    int p = 0, q = 0;
+    int64_t ne = 0;
+    DevBuf<int32_t> own;           // [ne][(p+1)^3] node if its first entry is here, else -1
+    DevBuf<int32_t> cmap;          // [ne][(q+1)^3] coarse node, -1 = constrained
+    DevBuf<int32_t> nptr, nent;    // per coarse node: its entries of cmap, ascending
+    DevBuf<double> i1;             // [(p+1)][(q+1)] interpolation
+    DevBuf<float> i132;            // mixed precision
+    double* ev = nullptr;          // the element form's result array
+    int64_t device_bytes() const {
+        return (int64_t)(own.n + cmap.n + nptr.n + nent.n) * 4 + (int64_t)i1.n * 8 + (int64_t)i132.n * 4;
+    }
+};
+void build_transfer_form(TransferForm& X, const ElementForm& E, const std::vector<int32_t>& coarse_l2g, int q,
+                         int64_t n_coarse, bool mixed, hipStream_t s);
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
                         hipStream_t s);
@@ -219,6 +237,7 @@ struct Level {
                                    // from the Galerkin product for the post-smoothing residual
     ElementForm E;                 // fine level: element form, where the products use it
     bool elem_products = false;    // the single-vector products run in the element form
+    TransferForm X;                // and with them, where q > 0, the transfers to the next level
     DevBuf<double> dinv;
     DevBuf<float> dinv32;
     double lam_hat = 0.0;

@@ -127,6 +127,7 @@ struct SpmvArgs {
     // reading rp / ci / val / v directly
     bool lean = false;
     const ElementForm* elem = nullptr;   // host only: the product runs in the element form
+    const TransferForm* xfer = nullptr;  // host only: P (SPMV_ADD) or R by its element form
 };
 
 // Arguments of a block product over k columns (block vectors row-major [n][k]).
@@ -156,6 +157,8 @@ struct SpmmArgs {
 int64_t element_blocks(int64_t n);
 template <typename T>
 void launch_element_product(int mode, const SpmvArgs<T>& a, hipStream_t s);
+template <typename T>
+void launch_transfer(int mode, const SpmvArgs<T>& a, hipStream_t s);
 // The block product over k columns; ev holds an element result per map entry
 // and column.  A column's bits do not depend on k.
 template <typename T>

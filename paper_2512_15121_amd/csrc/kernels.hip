@@ -847,6 +847,10 @@ void launch_spmv(int mode, const SpmvArgs<T>& args, hipStream_t s) {
         launch_element_product<T>(mode, a, s);
         return;
     }
+    if (a.xfer != nullptr) {
+        launch_transfer<T>(mode, a, s);
+        return;
+    }
     if (!a.lean && a.gblk == nullptr) {
         if (a.rblk == nullptr || a.bdesc == nullptr) throw Error(GIAMG_EINVAL, "operator without row blocks");
         // the kernel's LDS arrays hold spmv_cap<T>() products and spmv_threads<T>() rows

@@ -437,6 +437,14 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         spgemm(F.R, F.AP, C.A, H.stream);
         H.setup_ms[3] += ms_since(t0);
         H.levels.push_back(std::move(C));
+        // Transfers by the element form from a million entries of P on.  Whole solves with and
+        // without: 1.9 M (16^3 p = 4) 2.08 and 2.16 ms, 5.8 M (9^3 p = 6 mixed) 1.48 and 1.57, 10.8 M
+        // (13^3 p = 5, to order 3) 2.18 and 2.58; 0.24 M (8^3 p = 4), where R's third launch costs
+        // more than it saves, 1.15 and 1.09.  The modal basis injects (one entry per row), and
+        // with the boundary kept constrained nodes have rows in P.
+        if (step == 0 && H.levels[0].elem_products && H.levels[0].P.nnz > 1000000 &&
+            o.basis == GIAMG_BASIS_NODAL && !o.keep_boundary)
+            build_transfer_form(H.levels[0].X, H.levels[0].E, H.levels[1].l2g, q, nc, mixed, H.stream);
         free_mask.assign(nc, 1);
         order = q;
     }
@@ -566,7 +574,7 @@ int64_t handle_device_bytes(const Handle& H) {
     };
     int64_t b = 0;
     for (const Level& L : H.levels) {
-        b += csr(L.A) + csr(L.P) + csr(L.R) + csr(L.AP) + L.E.device_bytes();
+        b += csr(L.A) + csr(L.P) + csr(L.R) + csr(L.AP) + L.E.device_bytes() + L.X.device_bytes();
         b += (int64_t)(L.dinv.n + L.f.n + L.x.n + L.r.n + L.d0.n + L.d1.n + L.t.n) * 8;
         b += (int64_t)(L.dinv32.n + L.f32.n + L.x32.n + L.r32.n + L.d032.n + L.d132.n + L.t32.n) * 4;
     }
@@ -640,6 +648,13 @@ double spmv_bytes(int mode, const SpmvArgs<T>& a) {
         const ElementForm& E = *a.elem;
         return 4.0 * E.map.n + ELEM_COEF * vb * E.ne + 2.0 * vb * E.map.n + 4.0 * (E.nptr.n + E.nent.n) +
                vb * a.ncols + rows * vb * a.n;
+    }
+    if (a.xfer != nullptr) {   // maps, vectors, R: element results out and in, node lists
+        const TransferForm& X = *a.xfer;
+        const double fine = mode == SPMV_ADD ? a.n : a.ncols, coarse = mode == SPMV_ADD ? a.ncols : a.n;
+        return 4.0 * X.own.n + vb * (fine + coarse) +
+               (mode == SPMV_ADD ? 4.0 * X.cmap.n + vb * fine
+                                 : 2.0 * vb * X.cmap.n + 4.0 * (X.nptr.n + X.nent.n) + (rows - 1) * vb * coarse);
     }
     if (a.gblk != nullptr)   // grouped: slots per entry, block records, row list, group table
         return vb * a.nnz + 2.0 * a.gentries + 8.0 * a.gnruns + (4.0 + 32.0) * (a.nblk + 1) + 4.0 * a.n +
@@ -868,8 +883,21 @@ void residual(Handle& H, Level& L, const T* f, const T* x, T* out) {
 }
 
 template <typename T>
-void restrict_to(Handle& H, Level& L, const T* r, T* fc) {
+SpmvArgs<T> args_R(const Level& L) {
     SpmvArgs<T> a = args_of<T>(L.R, LV<T>::R(L));
+    if (L.X.q > 0) a.xfer = &L.X;
+    return a;
+}
+template <typename T>
+SpmvArgs<T> args_P(const Level& L) {
+    SpmvArgs<T> a = args_of<T>(L.P, LV<T>::P(L));
+    if (L.X.q > 0) a.xfer = &L.X;
+    return a;
+}
+
+template <typename T>
+void restrict_to(Handle& H, Level& L, const T* r, T* fc) {
+    SpmvArgs<T> a = args_R<T>(L);
     a.v = r; a.y = fc;
     run_spmv(H, SPMV_PLAIN, a);
 }
@@ -877,7 +905,7 @@ void restrict_to(Handle& H, Level& L, const T* r, T* fc) {
 // Restriction fused with the zero-start Chebyshev init of level C.
 template <typename T>
 void restrict_cheb0(Handle& H, Level& L, Level& C, const T* r) {
-    SpmvArgs<T> a = args_of<T>(L.R, LV<T>::R(L));
+    SpmvArgs<T> a = args_R<T>(L);
     a.v = r; a.y = LV<T>::f(C); a.dinv = LV<T>::dinv(C);
     a.r = LV<T>::r(C); a.x = LV<T>::d0(C);
     a.inv_theta = (T)cheb_coef(H, C).inv_theta;
@@ -886,7 +914,7 @@ void restrict_cheb0(Handle& H, Level& L, Level& C, const T* r) {
 
 template <typename T>
 void prolong_add(Handle& H, Level& L, const T* ec, T* x) {
-    SpmvArgs<T> a = args_of<T>(L.P, LV<T>::P(L));
+    SpmvArgs<T> a = args_P<T>(L);
     a.v = ec; a.y = x;
     run_spmv(H, SPMV_ADD, a);
 }
@@ -1345,12 +1373,12 @@ void time_kernel_t(Handle& H, int kernel, size_t l, int reps, double* ms, double
         }
     } else if (kernel == GIAMG_KERNEL_RESTRICT) {
         Level& C = H.levels[l + 1];
-        a = args_of<T>(L.R, LV<T>::R(L));
+        a = args_R<T>(L);
         a.v = LV<T>::t(L); a.y = LV<T>::f(C);
     } else if (kernel == GIAMG_KERNEL_PROLONG) {
         Level& C = H.levels[l + 1];
         mode = SPMV_ADD;
-        a = args_of<T>(L.P, LV<T>::P(L));
+        a = args_P<T>(L);
         a.v = LV<T>::x(C); a.y = LV<T>::t(L);
     } else {
         throw Error(GIAMG_EINVAL, "unknown kernel");

@@ -109,3 +109,40 @@ def test_pinned_mixed_handles_keep_the_assembled_rows():
         X.append(s.solve_batch(B)[0])
         s.close()
     assert torch.equal(x[0], x[1]) and torch.equal(X[0], X[1])
+
+
+# (n, p, schedule): every order the transfers' element form takes (a million entries of P), with
+# divisor and other coarse orders, meshes whose last block of elements is partly filled
+TRANSFERS = [(35, 2, ()), (22, 3, ()), (14, 4, ()), (9, 4, (3, 1)), (7, 5, (3, 1)), (7, 5, (4, 2, 1)), (6, 6, ()),
+             (9, 7, ()), (4, 8, ()), (4, 9, ()), (3, 10, ())]
+
+
+@pytest.mark.parametrize("n,p,schedule", TRANSFERS)
+def test_element_transfers_match_the_assembled_ones(n, p, schedule):
+    """x + P e and R t against the stored P and R = P^T.  An entry sums along
+    three axes of at most 11 terms and over 8 elements, and the 1-D factors' moduli
+    multiply to |P|: 64 roundings of |P| |e| and |R| |t| bound the difference."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=7)
+    for precision in ("fp64", "mixed"):
+        s = Solver(m.coords, m.l2g, p, 2.0, Options(precision=precision, schedule=schedule))
+        d, c = s.level(0), s.level(1)
+        assert s.time_kernel("prolong", 0, 1)[1] < 8 * d["nnz_P"] + 24 * d["rows"]   # not the stored values
+        rp, ci, val = s.level_csr(0, "P")
+        P = sp.csr_matrix((val, ci, rp), shape=(d["rows"], c["rows"]))
+        rng = np.random.default_rng(p)
+        e, t = rng.standard_normal(c["rows"]), rng.standard_normal(d["rows"])
+        fp32 = precision == "mixed"
+        dt = torch.float32 if fp32 else torch.float64
+        eps = 2.0 ** -23 if fp32 else 2.0 ** -52
+        et, tt = torch.from_numpy(e).to("cuda:0", dt), torch.from_numpy(t).to("cuda:0", dt)
+        e, t = et.double().cpu().numpy(), tt.double().cpu().numpy()
+        x = tt.clone()
+        s.apply("prolong_add", 0, et, out=x, fp32=fp32)
+        got = x.double().cpu().numpy()
+        assert np.all(np.abs(got - (t + P @ e)) <= 64 * eps * (np.abs(t) + abs(P) @ np.abs(e)))
+        f = torch.zeros(c["rows"], dtype=dt, device="cuda:0")
+        s.apply("restrict", 0, tt, out=f, fp32=fp32)
+        assert np.all(np.abs(f.double().cpu().numpy() - P.T @ t) <= 64 * eps * (abs(P).T @ np.abs(t)))
+        s.close()
