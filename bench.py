@@ -45,7 +45,8 @@ WORKLOADS = {
 # Jacobi smoothing (omega = 2/3, two sweeps), p2 -> p1.
 MANUFACTURED = dict(n=4, p=2, lam=1.0)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_cheb_step.json")
-KERNEL_SOURCES = ["paper_2512_15121_amd/csrc/kernels.hip", "paper_2512_15121_amd/csrc/kernels.h"]
+KERNEL_SOURCES = ["paper_2512_15121_amd/csrc/" + f
+                  for f in ("kernels.hip", "kernels.h", "row_epilogue.h", "element.hip")]
 
 
 def kernel_source_hash():
@@ -83,6 +84,14 @@ def cheb_step_algorithmic_bytes(nnz, n, vb):
     the five row-local streams of the update (residual read and written,
     inverse diagonal read, iterate read and written)."""
     return (vb + 4.0) * nnz + 8.0 * (n + 1) + 2.0 * vb * n + 5.0 * vb * n
+
+
+def element_step_algorithmic_bytes(n_elem, p, n, vb):
+    """The same of a step that applies the operator element by element: the
+    element-to-node map (32-bit), 21 trilinear coefficients per element, and the
+    seven vector streams.  The element results between its two kernels are not
+    counted."""
+    return 4.0 * n_elem * (p + 1) ** 3 + 21.0 * vb * n_elem + 7.0 * vb * n
 
 
 def time_solves(torch, solver, bt, steps, warmup):
@@ -595,16 +604,24 @@ def main():
     # dominant kernel: the fused Chebyshev step on the fine operator, timed in
     # the timed solves above; algorithmic bytes from the operator's sizes
     n0, nnz0 = levels[0]["rows"], levels[0]["nnz_A"]
-    alg_bytes = cheb_step_algorithmic_bytes(nnz0, n0, 8)
+    # (of the rows, or of the element form, which reads no value per nonzero and
+    # is bound by FP64 arithmetic and LDS in its element kernel, not by HBM)
     iso_ms, fmt_bytes = solver.time_kernel("cheb_step", level=0, reps=50)
+    elem = fmt_bytes < 8.0 * nnz0
+
+    def step_bytes(vb):
+        return (element_step_algorithmic_bytes(w["n"] ** 3, w["p"], n0, vb) if elem
+                else cheb_step_algorithmic_bytes(nnz0, n0, vb))
+    alg_bytes = step_bytes(8)
     achieved = alg_bytes / (step_ms * 1e-3) / 1e9
     stream_gbs = read_bandwidth(4 << 30, 10)
     traffic = traffic_entry(args.workload)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                 "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                 "traffic": traffic,
-                "kernel": "spmv_stream_kernel<double, SPMV_CHEB_STEP, 16, 1> (staged gathers) "
-                          "on the fine level",
+                "kernel": (f"element_kernel<double, {w['p']}> and element_node_kernel<double, SPMV_CHEB_STEP>"
+                           if elem else "spmv_stream_kernel<double, SPMV_CHEB_STEP, 16, 1> (staged gathers)")
+                          + " on the fine level",
                 "bytes_per_launch": alg_bytes,
                 "ms_per_launch": round(step_ms, 5),
                 "launches_timed": step_launches,
@@ -634,7 +651,7 @@ def main():
         sm = Solver(mesh.coords, mesh.l2g, w["p"], lam, Options(precision="mixed"))
         el_m, inf_m, xm, step32_ms, _ = time_solves(torch, sm, bt, args.steps, args.warmup)
         err = (torch.linalg.norm(xm - x) / torch.linalg.norm(x)).item()
-        alg32 = cheb_step_algorithmic_bytes(nnz0, n0, 4)
+        alg32 = step_bytes(4)
         extra["mixed"] = {"solves_per_s": round(args.steps / el_m, 3),
                           "speedup_vs_fp64": round(el_m and elapsed / el_m, 3),
                           "iterations": inf_m[-1].iters, "true_relres": inf_m[-1].true_relres,

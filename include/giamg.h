@@ -33,7 +33,8 @@
  *   - The fine operator's products in giamg_solve, giamg_solve_noalloc and
  *     giamg_apply run over the elements (sum factorisation, same operator to
  *     rounding) where it is large enough (at least 4 M and 0.15 M p^2
- *     nonzeros, p >= 2), over its CSR rows otherwise.  direct_gathers,
+ *     nonzeros, p >= 2), over its CSR rows otherwise; from a million entries
+ *     of P on its transfers do so too.  direct_gathers,
  *     row_groups and lean_max_nnz choose the form of the CSR products.
  */
 #ifndef GIAMG_H
