@@ -577,19 +577,17 @@ __device__ __forceinline__ void stop_column(ColState& s, int status, int* run) {
     atomicSub(run, 1);
 }
 
-// CG scalar updates of one column, applied by the reduction that completes
+// CG scalar updates of one running column, applied by the reduction that completes
 // their dots: alpha after p.q, the convergence test after r.r, beta after r.z.
 enum BatchFinish : int { BFIN_NONE = 0, BFIN_ALPHA = 1, BFIN_CHECK = 2, BFIN_BETA = 3, BFIN_BETA_FLEX = 4 };
 __device__ void bcg_finish(int fin, ColState& s, double tol, int maxit, int* run) {
     if (fin == BFIN_ALPHA) {
         s.alpha = 0.0;
-        if (!s.active) return;
         if (!(s.pq > 0.0) || !isfinite(s.pq) || !isfinite(s.rz))
             stop_column(s, GIAMG_EBREAKDOWN, run);
         else
             s.alpha = s.rz / s.pq;
     } else if (fin == BFIN_CHECK) {
-        if (!s.active) return;
         s.iters += 1;
         const double rel = sqrt(s.rr) / sqrt(s.bb);
         if (!isfinite(rel))
@@ -599,7 +597,6 @@ __device__ void bcg_finish(int fin, ColState& s, double tol, int maxit, int* run
         else if (s.iters >= maxit)
             stop_column(s, GIAMG_ENOTCONV, run);
     } else if (fin == BFIN_BETA || fin == BFIN_BETA_FLEX) {
-        if (!s.active) return;
         const double rzn = s.rznew;
         s.beta = fin == BFIN_BETA_FLEX ? (rzn - s.zrold) / s.rz : rzn / s.rz;
         s.rz = rzn;
@@ -611,13 +608,16 @@ __device__ void bcg_finish(int fin, ColState& s, double tol, int maxit, int* run
 // field which[set] of its state (only starting columns if only_init), sets
 // nb*k apart; then the column's scalar update.  Each column is summed on its
 // own, so a column's bits do not depend on k.  run: the number of running
-// columns (any nonzero value: work to do).
+// columns (any nonzero value: work to do).  With a scalar update other blocks of
+// the launch count *run down, so whether a block works is decided by its own
+// column alone (written by its own thread 0, behind the last barrier): a column
+// that has stopped keeps its sums.
 __global__ void __launch_bounds__(256) bdot_reduce_kernel(int64_t nb, int k, int sets, const double* __restrict__ partial,
                                                           ColState* st, int which0, int which1, int only_init,
                                                           int fin, double tol, int maxit, int* run) {
-    if (run && *run == 0) return;
-    __shared__ double sh[256 / BW];
     const int64_t c = blockIdx.x;
+    if (fin != BFIN_NONE ? !st[c].active : run && *run == 0) return;
+    __shared__ double sh[256 / BW];
     for (int set = 0; set < sets; ++set) {
         const double* __restrict__ p = partial + (int64_t)set * nb * k + c * nb;
         double s = 0.0;
