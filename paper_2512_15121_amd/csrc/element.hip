@@ -1063,6 +1063,34 @@ __global__ void transfer_own_kernel(int64_t m, const int32_t* __restrict__ map, 
     }
 }
 
+// Whether every row of P is what the node's first element gives: as many entries
+// as that element has coarse nodes with a nonzero weight (P's row is the union over
+// the node's elements, first occurrence kept), and no element lists a coarse node twice.
+__global__ void transfer_rows_kernel(int64_t m, int N, int M, const int32_t* __restrict__ own,
+                                     const int32_t* __restrict__ cmap, const double* __restrict__ i1,
+                                     const int64_t* __restrict__ rp, int* bad) {
+    const int M3 = M * M * M;
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < m; t += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t g = own[t];
+        if (g < 0) continue;
+        const int64_t e = t / (N * N * N);
+        const int loc = (int)(t - e * (N * N * N)), i = loc / (N * N), j = loc / N % N, k = loc % N;
+        int count = 0;
+        for (int c = 0; c < M3; ++c)
+            count += i1[i * M + c / (M * M)] != 0.0 && i1[j * M + c / M % M] != 0.0 && i1[k * M + c % M] != 0.0 &&
+                     cmap[e * M3 + c] >= 0;
+        if (count != rp[g + 1] - rp[g]) *bad = 1;
+    }
+}
+__global__ void transfer_twice_kernel(int64_t mc, int M3, const int32_t* __restrict__ cmap, int* bad) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < mc; t += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t c = cmap[t];
+        if (c < 0) continue;
+        for (int64_t u = t / M3 * M3; u < t; ++u)
+            if (cmap[u] == c) *bad = 1;
+    }
+}
+
 template <typename T, int MODE>
 void launch_node_lists(const SpmvArgs<T>& a, const int32_t* nptr, const int32_t* nent, const T* ev, hipStream_t s) {
     const dim3 grid((unsigned)a.nblk), block(NODE_THREADS);
@@ -1348,8 +1376,8 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     build_node_lists(E.map.get(), m, n, E.nptr, E.nent, s);
 }
 
-void build_transfer_form(TransferForm& X, const ElementForm& E, const std::vector<int32_t>& coarse_l2g, int q,
-                         int64_t n_coarse, bool mixed, hipStream_t s) {
+bool build_transfer_form(TransferForm& X, const ElementForm& E, const DevCSR& P, const std::vector<int32_t>& coarse_l2g,
+                         int q, bool mixed, hipStream_t s) {
     const int p = E.order, N = p + 1, M = q + 1;
     const int64_t m = E.ne * N * N * N, mc = E.ne * M * M * M;
     GIAMG_REQUIRE(q >= 1 && q < p && (int64_t)coarse_l2g.size() == mc, "transfer form of unexpected sizes");
@@ -1375,8 +1403,19 @@ void build_transfer_form(TransferForm& X, const ElementForm& E, const std::vecto
         X.i132.alloc(i1.size());
         launch_convert<double, float>((int64_t)i1.size(), X.i1.get(), X.i132.get(), s);
     }
-    build_node_lists(X.cmap.get(), mc, n_coarse, X.nptr, X.nent, s);
+    DevBuf<int> bad(1);
+    GIAMG_HIP(hipMemsetAsync(bad.get(), 0, sizeof(int), s));
+    transfer_rows_kernel<<<setup_grid(m), 256, 0, s>>>(m, N, M, X.own.get(), X.cmap.get(), X.i1.get(), P.rp.get(),
+                                                       bad.get());
+    transfer_twice_kernel<<<setup_grid(mc), 256, 0, s>>>(mc, M * M * M, X.cmap.get(), bad.get());
+    GIAMG_HIP(hipGetLastError());
+    int hbad = 0;
+    GIAMG_HIP(hipMemcpyAsync(&hbad, bad.get(), sizeof(int), hipMemcpyDeviceToHost, s));
+    GIAMG_HIP(hipStreamSynchronize(s));   // also: the host arrays go out of scope
+    if (hbad) return false;
+    build_node_lists(X.cmap.get(), mc, P.ncols, X.nptr, X.nent, s);
     X.q = q;
+    return true;
 }
 
 }  // namespace giamg

@@ -214,8 +214,11 @@ struct TransferForm {
         return (int64_t)(own.n + cmap.n + nptr.n + nent.n) * 4 + (int64_t)i1.n * 8 + (int64_t)i132.n * 4;
     }
 };
-void build_transfer_form(TransferForm& X, const ElementForm& E, const std::vector<int32_t>& coarse_l2g, int q,
-                         int64_t n_coarse, bool mixed, hipStream_t s);
+// False (X then of no use) where P's rows are not those of their nodes' first elements:
+// elements turned against their neighbours, whose coarse numberings differ where an
+// order's kept nodes lie unevenly, and elements that list a node twice.
+bool build_transfer_form(TransferForm& X, const ElementForm& E, const DevCSR& P, const std::vector<int32_t>& coarse_l2g,
+                         int q, bool mixed, hipStream_t s);
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
                         hipStream_t s);

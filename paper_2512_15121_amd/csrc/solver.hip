@@ -443,8 +443,11 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         // more than it saves, 1.15 and 1.09.  The modal basis injects (one entry per row), and
         // with the boundary kept constrained nodes have rows in P.
         if (step == 0 && H.levels[0].elem_products && H.levels[0].P.nnz > 1000000 &&
-            o.basis == GIAMG_BASIS_NODAL && !o.keep_boundary)
-            build_transfer_form(H.levels[0].X, H.levels[0].E, H.levels[1].l2g, q, nc, mixed, H.stream);
+            o.basis == GIAMG_BASIS_NODAL && !o.keep_boundary) {
+            TransferForm X;
+            if (build_transfer_form(X, H.levels[0].E, H.levels[0].P, H.levels[1].l2g, q, mixed, H.stream))
+                H.levels[0].X = std::move(X);
+        }
         free_mask.assign(nc, 1);
         order = q;
     }

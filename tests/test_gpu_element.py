@@ -146,3 +146,59 @@ def test_element_transfers_match_the_assembled_ones(n, p, schedule):
         s.apply("restrict", 0, tt, out=f, fp32=fp32)
         assert np.all(np.abs(f.double().cpu().numpy() - P.T @ t) <= 64 * eps * (abs(P).T @ np.abs(t)))
         s.close()
+
+
+def _turned(n, p):
+    """Every third element turned by half a turn about its third axis."""
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=7)
+    l2g = m.l2g.reshape(-1, p + 1, p + 1, p + 1).copy()
+    l2g[::3] = l2g[::3, ::-1, ::-1, :]
+    return m.coords, np.ascontiguousarray(l2g.reshape(m.l2g.shape))
+
+
+def _sector(n, p):
+    """A quarter of a cylinder: the elements at its axis list each node there p + 1 times."""
+    m = synth.hex_mesh(n, p)
+    r, t = m.coords[:, 0], m.coords[:, 1] * np.pi / 2
+    coords = np.stack([r * np.cos(t), r * np.sin(t), m.coords[:, 2]], 1)
+    L = n * p + 1
+    ids = np.arange(L ** 3).reshape(L, L, L)
+    ids[0] = ids[0, :1]
+    used, l2g = np.unique(ids.reshape(-1)[m.l2g], return_inverse=True)
+    return np.ascontiguousarray(coords[used]), l2g.reshape(m.l2g.shape).astype(np.int32)
+
+
+# order 2 keeps an order-5 element's nodes unevenly, order 3 evenly
+@pytest.mark.parametrize("mesh,n,p,schedule,form", [(_turned, 9, 5, (2, 1), False), (_turned, 7, 5, (3, 1), True),
+                                                    (_sector, 14, 4, (), False)])
+def test_transfers_on_turned_and_collapsed_elements(mesh, n, p, schedule, form):
+    """P's rows are unions over a node's elements with the first weight of a coarse
+    node kept: where an element alone does not give them, the transfers keep the
+    stored rows (bound as above).  Products run over the elements on these meshes
+    too, against the assembled rows to the bound of the module."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    coords, l2g = mesh(n, p)
+    s = Solver(coords, l2g, p, 2.0, Options(schedule=schedule, bc="pin"))
+    d, c = s.level(0), s.level(1)
+
+    def rows(which, cols):
+        rp, ci, val = s.level_csr(0, which)
+        return sp.csr_matrix((val, ci, rp), shape=(d["rows"], cols))
+    P, A = rows("P", c["rows"]), rows("A", d["rows"])
+    assert P.nnz > 1000000 and s.time_kernel("spmv", 0, 1)[1] < 8 * A.nnz
+    assert (s.time_kernel("prolong", 0, 1)[1] < 8 * P.nnz + 24 * d["rows"]) == form
+    rng = np.random.default_rng(p)
+    e, t = rng.standard_normal(c["rows"]), rng.standard_normal(d["rows"])
+    dev = lambda v: torch.from_numpy(v).to("cuda:0")  # noqa: E731
+    eps = 2.0 ** -52
+    x = dev(t).clone()
+    s.apply("prolong_add", 0, dev(e), out=x)
+    assert np.all(np.abs(x.cpu().numpy() - (t + P @ e)) <= 64 * eps * (np.abs(t) + abs(P) @ np.abs(e)))
+    f = torch.zeros(c["rows"], dtype=torch.float64, device="cuda:0")
+    s.apply("restrict", 0, dev(t), out=f)
+    assert np.all(np.abs(f.cpu().numpy() - P.T @ t) <= 64 * eps * (abs(P).T @ np.abs(t)))
+    y = torch.zeros_like(x)
+    s.apply("spmv", 0, dev(t), out=y)
+    assert np.max(np.abs(y.cpu().numpy() - A @ t)) <= (6 * (p + 2) + 40) * 32 * eps * np.max(abs(A) @ np.abs(t))
+    s.close()
