@@ -1022,7 +1022,7 @@ void spmm(BatchCtx& c, int mode, const DevCSR& M, SpmmArgs<T> a, const std::stri
     if (c.B.elem && &M == &c.H.levels[0].A) {
         const ElementForm& E = c.H.levels[0].E;
         if (c.count_bytes)
-            c.H.bytes += 4.0 * (2.0 * E.map.n + E.nptr.n) + ELEM_COEF * sizeof(T) * E.ne +
+            c.H.bytes += 4.0 * (2.0 * E.map.n + E.nptr.n) + elem_coefs<T>() * sizeof(T) * E.ne +
                          sizeof(T) * (2.0 * E.map.n * c.k + (double)M.ncols * c.k + rowvecs * M.nrows * c.k);
         launch_element_block<T>(mode, a, E, c.B.ev.get(), c.s());
         return;

@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <cmath>
 
 #include "kernels.h"
 #include "row_epilogue.h"
@@ -53,7 +55,7 @@ struct ElemArgs {
     const int32_t* map = nullptr;    // [ne][nl] node of each local position, -1 constrained
     const T* v = nullptr;
     T* ev = nullptr;                 // [ne][nl]
-    const T* coef = nullptr;         // [ELEM_COEF][ne] trilinear coefficients
+    const T* coef = nullptr;         // [elem_coefs][ne] trilinear coefficients
     const T* tabs = nullptr;         // 1-D tables (element_tables)
     T lambda = 0, ps = 1, pt = -1;   // pair transform of the inner positions (element_tables)
     int k = 1;                       // columns of v ([n][k]) and ev ([ne][nl][k])
@@ -277,9 +279,9 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
             if (t < V * NL) sh[(t % NL) * V + t / NL] = g[it] >= 0 ? x[it] : T(0);
         }
     }
-    T c[ELEM_COEF];   // the element's geometry, used at the quadrature points
+    T c[elem_coefs<T>()];   // the element's geometry, used at the quadrature points
 #pragma unroll
-    for (int m = 0; m < ELEM_COEF; ++m) c[m] = a.coef[m * a.ne + e];
+    for (int m = 0; m < elem_coefs<T>(); ++m) c[m] = a.coef[m * a.ne + e];
     __syncthreads();
     if (done) return;
     // z: nodal lines to Gauss points, values and derivatives
@@ -398,6 +400,12 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
         for (int q = 0; q < H; ++q) {
             const Rec<T, N> r{tab + q * 2 * N};
             const T xi = gq[q], w = wq[q] * wyz;
+            // FP32: h and lambda h^3 of the scaled element (exact: powers of two)
+            T ws = w, mass = a.lambda;
+            if constexpr (elem_coefs<T>() > ELEM_COEF) {
+                ws = w * c[ELEM_COEF];
+                mass = c[ELEM_COEF + 1];
+            }
             const bool pair = Q % 2 == 0 || q < H - 1;
             const T ve = even_l(r, u0), vo = odd_l(r, u0);
             const T xe = even_d(r, u0), xo = odd_d(r, u0);
@@ -428,13 +436,13 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
                 const T det = h == 0 ? te + to : te - to;
                 const T ux = h == 0 ? xe + xo : xe - xo, uy = h == 0 ? ye + yo : ye - yo;
                 const T uz = h == 0 ? ze + zo : ze - zo, val = h == 0 ? ve + vo : ve - vo;
-                const T s = w * recip(det);
+                const T s = ws * recip(det);
 #pragma unroll
                 for (int m = 0; m < 3; ++m) W[m] = s * mad(gz[m], uz, mad(gy[m], uy, gx[m] * ux));
                 f[h][0] = mad(gx[2], W[2], mad(gx[1], W[1], gx[0] * W[0]));
                 f[h][1] = mad(gy[2], W[2], mad(gy[1], W[1], gy[0] * W[0]));
                 f[h][2] = mad(gz[2], W[2], mad(gz[1], W[1], gz[0] * W[0]));
-                f[h][3] = (a.lambda * w) * (det * val);
+                f[h][3] = (mass * w) * (det * val);
             }
             add_d(r, f[0][0] + f[1][0], f[0][0] - f[1][0], o0);
             add_l(r, f[0][3] + f[1][3], f[0][3] - f[1][3], o0);
@@ -1287,6 +1295,61 @@ static void build_node_lists(const int32_t* map, int64_t m, int64_t n, DevBuf<in
     GIAMG_HIP(hipStreamSynchronize(s));   // the host arrays go out of scope
 }
 
+// Coefficients of x = sum over the corners of X_c (1 +- xi)(1 +- eta)(1 +- zeta) / 8; corner
+// c = 4 i + 2 j + k; xi, eta, zeta, xi eta, xi zeta, eta zeta, xi eta zeta, three axes each.
+static void trilinear_coefs(const double* corners, double* coef) {
+    const int sub[7] = {4, 2, 1, 6, 5, 3, 7};
+    for (int t = 0; t < 7; ++t)
+        for (int r = 0; r < 3; ++r) {
+            double v = 0.0;
+            for (int c = 0; c < 8; ++c) {
+                const int low = __builtin_popcount(sub[t] & ~c) & 1;   // one minus sign per -1 side
+                v += (low ? -1.0 : 1.0) * corners[c * 3 + r];
+            }
+            coef[3 * t + r] = 0.125 * v;
+        }
+}
+// Exponent of the power of two that an element is scaled by in FP32: its largest coefficient's.
+static int element_exponent(const double* coef) {
+    double m = 0.0;
+    for (int i = 0; i < ELEM_COEF; ++i) m = std::max(m, std::fabs(coef[i]));
+    return m > 0.0 ? std::ilogb(m) : 0;
+}
+
+bool fp32_geometry(const std::vector<double>& corners, int64_t ne, int p, double lambda) {
+    std::vector<double> g, w;
+    gauss_points(p + 2, g, w);
+    const double at[3] = {g.front(), 0.0, g.back()};
+    std::atomic<bool> ok{true};
+    parallel_for(ne, 1 << 12, [&](int64_t b, int64_t en) {
+        bool good = true;
+        for (int64_t e = b; e < en && good; ++e) {
+            double c[ELEM_COEF];
+            trilinear_coefs(corners.data() + (size_t)e * 24, c);
+            const int ex = element_exponent(c);
+            good = std::abs(ex) <= 64 && std::ldexp(lambda, 3 * ex) <= 0x1p100;
+            for (double& v : c) v = std::ldexp(v, -ex);
+            for (int q = 0; q < 27 && good; ++q) {
+                const double xi = at[q / 9], eta = at[q / 3 % 3], zeta = at[q % 3];
+                double J[3][3], len[3];   // columns dx/dxi, dx/deta, dx/dzeta
+                for (int m = 0; m < 3; ++m) {
+                    J[0][m] = c[m] + c[9 + m] * eta + c[12 + m] * zeta + c[18 + m] * eta * zeta;
+                    J[1][m] = c[3 + m] + c[9 + m] * xi + c[15 + m] * zeta + c[18 + m] * xi * zeta;
+                    J[2][m] = c[6 + m] + c[12 + m] * xi + c[15 + m] * eta + c[18 + m] * xi * eta;
+                }
+                for (int d = 0; d < 3; ++d)
+                    len[d] = std::sqrt(J[d][0] * J[d][0] + J[d][1] * J[d][1] + J[d][2] * J[d][2]);
+                const double det = J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) +
+                                   J[0][1] * (J[1][2] * J[2][0] - J[1][0] * J[2][2]) +
+                                   J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
+                good = std::min({len[0], len[1], len[2]}) >= 0x1p-20 && det >= 0x1p-10 * len[0] * len[1] * len[2];
+            }
+        }
+        if (!good) ok = false;
+    });
+    return ok;
+}
+
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
                         hipStream_t s) {
@@ -1325,20 +1388,19 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     });
     E.map.alloc(m);
     GIAMG_HIP(hipMemcpyAsync(E.map.get(), map.data(), m * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    // x = sum over the corners of X_c (1 +- xi)(1 +- eta)(1 +- zeta) / 8; corner c = 4 i + 2 j + k
     std::vector<double> coef((size_t)ELEM_COEF * ne);
-    const int sub[7] = {4, 2, 1, 6, 5, 3, 7};   // xi, eta, zeta, xi eta, xi zeta, eta zeta, xi eta zeta
+    std::vector<float> coef32(mixed ? (size_t)elem_coefs<float>() * ne : 0);
     parallel_for(ne, 1 << 12, [&](int64_t b, int64_t en) {
-        for (int64_t e = b; e < en; ++e)
-            for (int t = 0; t < 7; ++t)
-                for (int r = 0; r < 3; ++r) {
-                    double v = 0.0;
-                    for (int c = 0; c < 8; ++c) {
-                        const int low = __builtin_popcount(sub[t] & ~c) & 1;   // one minus sign per -1 side
-                        v += (low ? -1.0 : 1.0) * corners[(size_t)e * 24 + c * 3 + r];
-                    }
-                    coef[(size_t)(3 * t + r) * ne + e] = 0.125 * v;
-                }
+        for (int64_t e = b; e < en; ++e) {
+            double c[ELEM_COEF];
+            trilinear_coefs(corners.data() + (size_t)e * 24, c);
+            for (int m = 0; m < ELEM_COEF; ++m) coef[(size_t)m * ne + e] = c[m];
+            if (!mixed) continue;
+            const int ex = element_exponent(c);
+            for (int m = 0; m < ELEM_COEF; ++m) coef32[(size_t)m * ne + e] = (float)std::ldexp(c[m], -ex);
+            coef32[(size_t)ELEM_COEF * ne + e] = (float)std::ldexp(1.0, ex);
+            coef32[(size_t)(ELEM_COEF + 1) * ne + e] = (float)std::ldexp(lambda, 3 * ex);
+        }
     });
     E.coef.alloc(coef.size());
     GIAMG_HIP(hipMemcpyAsync(E.coef.get(), coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice, s));
@@ -1368,8 +1430,8 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
     E.tabs.alloc(tabs.size());
     GIAMG_HIP(hipMemcpyAsync(E.tabs.get(), tabs.data(), tabs.size() * sizeof(double), hipMemcpyHostToDevice, s));
     if (mixed) {
-        E.coef32.alloc(coef.size());
-        launch_convert<double, float>((int64_t)coef.size(), E.coef.get(), E.coef32.get(), s);
+        E.coef32.alloc(coef32.size());
+        GIAMG_HIP(hipMemcpyAsync(E.coef32.get(), coef32.data(), coef32.size() * sizeof(float), hipMemcpyHostToDevice, s));
         E.tabs32.alloc(tabs.size());
         launch_convert<double, float>((int64_t)tabs.size(), E.tabs.get(), E.tabs32.get(), s);
     }

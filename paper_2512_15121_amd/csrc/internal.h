@@ -180,6 +180,12 @@ void setup_row_blocks32(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s
 // built, except ev (the single-vector products' work array; block products
 // bring their own).
 constexpr int ELEM_COEF = 21;      // trilinear coefficients per element (without the constant)
+// In FP32 the coefficients are those of the element scaled to size 1 by a power of two
+// h (exact), with h and lambda h^3 behind them: the determinant goes as h^3 and the
+// gradients' products as h^2, so a mesh in metres of elements of nanometres, whose
+// entries (they go as h) FP32 holds, would leave its range inside the kernel.
+template <typename T>
+constexpr int elem_coefs() { return sizeof(T) == 4 ? ELEM_COEF + 2 : ELEM_COEF; }
 struct ElementForm {
     int order = 0;
     int64_t ne = 0;
@@ -187,7 +193,7 @@ struct ElementForm {
     double ps = 1.0, pt = -1.0;    // pair transform of the inner 1-D positions (build_element_form)
     DevBuf<int32_t> map;           // [ne][(order+1)^3] node, -1 = constrained
     DevBuf<int32_t> nptr, nent;    // per node: its entries of ev, ascending ([n + 1], one per map entry >= 0)
-    DevBuf<double> coef, tabs;     // [ELEM_COEF][ne]; 1-D tables
+    DevBuf<double> coef, tabs;     // [elem_coefs][ne]; 1-D tables
     DevBuf<float> coef32, tabs32;  // mixed precision
     DevBuf<double> ev;             // [ne][(order+1)^3] element results (either precision)
     DevBuf<double> mat;            // element matrices in tiles (block products, order <= 4)
@@ -222,6 +228,11 @@ bool build_transfer_form(TransferForm& X, const ElementForm& E, const DevCSR& P,
 void build_element_form(ElementForm& E, const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                         int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, bool mixed,
                         hipStream_t s);
+// Whether FP32 serves the elements' geometry: a determinant that is not lost in its
+// terms' rounding (at least 2^-10 of the product of the edges' lengths, so 14 of 24 bits
+// are left of it), edges within 2^20 of each other, and h and lambda h^3 far from the
+// ends of the range.  The assembled entries, formed in 64 bits, need none of this.
+bool fp32_geometry(const std::vector<double>& corners, int64_t ne, int p, double lambda);
 // The matrices of every element (order <= 4), FP32 copies with mixed.
 void build_element_matrices(ElementForm& E, bool mixed, hipStream_t s);
 
@@ -262,6 +273,7 @@ struct Handle {
     std::vector<uint8_t> constrained;
     // geometry kept for the load-vector helpers
     std::vector<double> corners;      // [n_elem][8][3]
+    bool fp32_elements = true;        // fp32_geometry of the mesh (mixed precision)
     std::vector<int32_t> l2g;         // fine element map
     // coarsest level: dense inverse (FP64), rows nc
     int64_t nc = 0;
@@ -311,9 +323,10 @@ void ensure_element_form(Handle& H);
 // alone, and the rounding of the FP32 cycle, not its convergence, decides how far
 // the solution is shifted (any other rounding, of the FP64 products too, moves
 // it by 1e-10 to 2e-8 of itself at a tolerance of 1e-10).  These handles keep the
-// assembled rows, and with them their solutions to the last bit.
+// assembled rows, and with them their solutions to the last bit.  Nor in mixed
+// precision on elements whose geometry FP32 does not serve (fp32_geometry).
 inline bool element_form_allowed(const Handle& H) {
-    return !(H.opts.precision == GIAMG_PREC_MIXED && H.opts.bc == GIAMG_BC_PIN);
+    return H.opts.precision != GIAMG_PREC_MIXED || (H.opts.bc != GIAMG_BC_PIN && H.fp32_elements);
 }
 
 // ---- host setup (setup_host.cpp) -------------------------------------------

@@ -346,6 +346,7 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     for (auto c : H.constrained) ncons += c;
     GIAMG_REQUIRE(H.lambda > 0.0 || ncons > 0, "lambda = 0 needs at least one constrained node");
     element_corners(coords, l2g, ne, H.porder, H.corners, o.basis);
+    H.fp32_elements = !mixed || fp32_geometry(H.corners, ne, H.porder, H.lambda);
     H.l2g.assign(l2g, l2g + ne * (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1));
     H.levels.clear();
     H.levels.emplace_back();
@@ -649,7 +650,7 @@ double spmv_bytes(int mode, const SpmvArgs<T>& a) {
     }
     if (a.elem != nullptr) {   // element map, coefficients, element results out and in, node lists, vectors
         const ElementForm& E = *a.elem;
-        return 4.0 * E.map.n + ELEM_COEF * vb * E.ne + 2.0 * vb * E.map.n + 4.0 * (E.nptr.n + E.nent.n) +
+        return 4.0 * E.map.n + elem_coefs<T>() * vb * E.ne + 2.0 * vb * E.map.n + 4.0 * (E.nptr.n + E.nent.n) +
                vb * a.ncols + rows * vb * a.n;
     }
     if (a.xfer != nullptr) {   // maps, vectors, R: element results out and in, node lists

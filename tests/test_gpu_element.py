@@ -202,3 +202,61 @@ def test_transfers_on_turned_and_collapsed_elements(mesh, n, p, schedule, form):
     s.apply("spmv", 0, dev(t), out=y)
     assert np.max(np.abs(y.cpu().numpy() - A @ t)) <= (6 * (p + 2) + 40) * 32 * eps * np.max(abs(A) @ np.abs(t))
     s.close()
+
+
+# single products over the elements (p = 4, 2), and block products of order 5
+@pytest.mark.parametrize("n,p,batch", [(9, 4, False), (21, 2, False), (4, 5, True)])
+def test_fp32_cycle_in_any_unit_of_length(n, p, batch):
+    """The entries go as the element size h (lambda h^2 kept): with h scaled by a power
+    of two every number of a mixed solve is scaled by one too (identity rows apart,
+    whose right-hand sides are zero here), so the solution times it is the same to the
+    last bit.  2^-47 and 2^47 take (h / 2)^3 out of FP32's range, the entries not."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=3)
+    x = {}
+    for e in (0, -47, 47):
+        h = 2.0 ** e
+        s = Solver(m.coords * h, m.l2g, p, 3.0 / (h * h), Options(precision="mixed"))
+        if not batch:
+            assert s.time_kernel("spmv", 0, 1)[1] < 8 * s.level(0)["nnz_A"]
+        b = synth.normal_rhs(m.n_nodes, 5) * ~s.constrained()
+        bt = torch.from_numpy(b).to("cuda:0")
+        if batch:
+            X, (info,) = s.solve_batch(bt.reshape(-1, 1).contiguous())
+            x[e] = X[:, 0] * h
+        else:
+            xs, info = s.solve(bt)
+            x[e] = xs * h
+        assert info.status == 0 and info.true_relres < 1e-9, e
+        s.close()
+    assert torch.equal(x[0], x[-47]) and torch.equal(x[0], x[47])
+
+
+@pytest.mark.parametrize("shear,form", [(100.0, True), (1e4, False)])
+def test_sheared_elements_keep_the_precision_of_the_fp32_products(shear, form):
+    """Elements sheared so far that FP32 loses their determinant keep the assembled
+    rows in mixed precision (their FP32 products round (p + 2)^3 multiply-adds at
+    most); the form serves those it is good for, to the bound of the module times the
+    growth of a determinant's rounding, the shear."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    n, p = 9, 4
+    m = synth.hex_mesh(n, p)
+    rng = np.random.default_rng(2)
+    turn, _ = np.linalg.qr(rng.standard_normal((3, 3)))
+    turn *= np.linalg.det(turn)
+    S = np.eye(3)
+    S[0, 1] = shear
+    s = Solver(m.coords @ (turn @ S).T, m.l2g, p, 2.0, Options(precision="mixed"))
+    d = s.level(0)
+    rp, ci, val = s.level_csr(0)
+    A = sp.csr_matrix((val, ci, rp), shape=(d["rows"],) * 2)
+    assert (s.time_kernel("spmv", 0, 1)[1] < 8 * A.nnz) == form
+    x = torch.from_numpy(rng.standard_normal(d["rows"])).to("cuda:0", torch.float32)
+    y = torch.zeros_like(x)
+    s.apply("spmv", 0, x, out=y, fp32=True)
+    s.close()
+    xh = x.double().cpu().numpy()
+    bound = ((6 * (p + 2) + 40) * 64 * shear if form else 2 * (p + 2) ** 3) * 2.0 ** -24 * np.max(abs(A) @ np.abs(xh))
+    assert np.max(np.abs(y.double().cpu().numpy() - A @ xh)) <= bound
