@@ -1010,10 +1010,12 @@ Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 // k = 64 15.6 / 19.1 ms, k = 8 6.6 / 14.8, k = 1 5.5 / 13; 16^3 p = 4 k = 64 20.5 / 26.9,
 // 11^3 p = 4 k = 8 4.8 / 12.2; 16^3 p = 2 k = 64 4.4 / 4.6, k = 16 3.1 / 3.7; 10^3 p = 5
 // k = 64 30 / 34, k = 8 9.9 / 46; 8^3 p = 6 k = 48 13 / 23.  Sum factorisation at p = 4
-// loses at k = 64 (16^3: 43 ms).
+// loses at k = 64 (16^3: 43 ms).  The matrices and results take memory that the rows
+// do not; where the device has none left, the handle's batches take the rows
+// (tuned_state).
 bool block_element_form(const Handle& H) {
     const int64_t nl = (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1);
-    return element_form_allowed(H) && H.porder >= 2 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
+    return element_form_allowed(H) && !H.block_rows && H.porder >= 2 && H.porder <= 10 && H.n_elem * nl < (int64_t(1) << 31);
 }
 
 template <typename T>
@@ -1357,12 +1359,6 @@ std::unique_ptr<BatchState> make_state(Handle& H, int k) {
     return B;
 }
 
-void ensure_state(Handle& H, int k) {
-    if (H.batch && H.batch->k == k) return;
-    H.batch.reset();
-    H.batch.reset(make_state(H, k).release());
-}
-
 // Start the columns flagged `init` without touching the others (their
 // recursive residuals and directions stay as they are).
 void start_columns(BatchCtx& c, const double* Bm, double* X, double tol) {
@@ -1410,6 +1406,37 @@ void tune_all(Handle& H, BatchState& B, int k) {
     }
 }
 
+// A state with its operators tuned.  Where the element form's memory is what is
+// missing, the handle's block products take the rows from then on.
+std::unique_ptr<BatchState> tuned_state(Handle& H, int k) {
+    while (true) {
+        const bool elem = block_element_form(H), had_matrices = H.levels[0].E.mat.get() != nullptr;
+        std::unique_ptr<BatchState> B;
+        try {
+            B = make_state(H, k);
+            // memory of the caller's allocator may still be in use on the handle's stream
+            GIAMG_HIP(hipEventRecord(B->ev_in, H.stream));
+            GIAMG_HIP(hipStreamWaitEvent(B->stream, B->ev_in, 0));
+            tune_all(H, *B, k);
+            return B;
+        } catch (const Error& e) {
+            if (B) (void)hipStreamSynchronize(B->stream);
+            if (e.code != GIAMG_ENOMEM || !elem) throw;
+            H.block_rows = true;
+            if (!had_matrices) {   // no other state of this handle reads them
+                H.levels[0].E.mat.release();
+                H.levels[0].E.mat32.release();
+            }
+        }
+    }
+}
+
+void ensure_state(Handle& H, int k) {
+    if (H.batch && H.batch->k == k) return;
+    H.batch.reset();
+    H.batch.reset(tuned_state(H, k).release());
+}
+
 }  // namespace
 
 int solve_batch(Handle& H, const double* Bm, double* X, int32_t k, double tol, giamg_info* infos) {
@@ -1423,8 +1450,6 @@ int solve_batch(Handle& H, const double* Bm, double* X, int32_t k, double tol, g
     const unsigned cb = (unsigned)std::min(k, MAX_K);
     BatchCtx c{H, B, k, B.run.get(), true};
     H.bytes = 0.0;
-    // tune every operator before anything is captured
-    tune_all(H, B, k);
     hipEvent_t t0, t1;
     GIAMG_HIP(hipEventCreate(&t0));
     GIAMG_HIP(hipEventCreate(&t1));
@@ -1575,22 +1600,21 @@ Session* session_create(Handle& H, int k, double tol) {
     S->H = &H;
     S->k = k;
     S->tol = tol;
-    S->B = make_state(H, k);
-    BatchState& B = *S->B;
-    hipStream_t s = B.stream;
-    GIAMG_HIP(hipEventRecord(B.ev_in, H.stream));
-    GIAMG_HIP(hipStreamWaitEvent(s, B.ev_in, 0));
     const size_t tot = (size_t)H.n_nodes * k;
     S->Bm.alloc(tot);
     S->X.alloc(tot);
     S->slots.alloc(k);
+    S->B = tuned_state(H, k);
+    BatchState& B = *S->B;
+    hipStream_t s = B.stream;
+    GIAMG_HIP(hipEventRecord(B.ev_in, H.stream));
+    GIAMG_HIP(hipStreamWaitEvent(s, B.ev_in, 0));
     GIAMG_HIP(hipMemsetAsync(S->Bm.get(), 0, tot * sizeof(double), s));
     GIAMG_HIP(hipMemsetAsync(S->X.get(), 0, tot * sizeof(double), s));
     for (DevBuf<double>* v : {&B.R, &B.Z, &B.P, &B.Q})
         if (v->get()) GIAMG_HIP(hipMemsetAsync(v->get(), 0, tot * sizeof(double), s));
     bclear_state_kernel<<<1, 256, 0, s>>>(k, B.st.get());
     GIAMG_HIP(hipMemsetAsync(B.run.get(), 0, sizeof(int), s));
-    tune_all(H, B, k);
     BatchCtx c{H, B, k, B.run.get(), false};
     {
         std::lock_guard<std::mutex> cap(capture_mutex());

@@ -296,6 +296,7 @@ struct Handle {
     int64_t partial_cap = 0;
     // batched state
     std::unique_ptr<BatchState, BatchDeleter> batch;
+    bool block_rows = false;          // no memory for the block products' element form: rows from then on
     double bytes = 0.0;               // algorithmic bytes of launched kernels
     double setup_ms[7] = {0, 0, 0, 0, 0, 0, 0};
     // phase profiling (giamg_profile_enable): event intervals per category,
