@@ -64,6 +64,7 @@ struct ElemArgs {
     const double* vnz = nullptr;     // when set and zero, v is +0: nothing to do
     double* mat = nullptr;           // UNIT: element matrices in tiles
     float* mat32 = nullptr;
+    int64_t pair0 = 0;               // UNIT: first (element, column) pair of this launch
 };
 
 // Every multiply-add is written out, so each instance of the kernel gives the
@@ -234,7 +235,7 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
     __shared__ T sh[V * 3 * N * Q2];
     const int tid = threadIdx.x;
     const int v = tid % V, line = tid / V;
-    const int64_t first = xcd_block(blockIdx.x, gridDim.x) * V;   // element, or pair
+    const int64_t first = (UNIT ? a.pair0 : 0) + xcd_block(blockIdx.x, gridDim.x) * V;   // element, or pair
     const int64_t total = COLS ? a.ne * a.k : a.ne;
     const int64_t mine = min(first + v, total - 1);
     const int64_t e = COLS ? (total <= (int64_t)UINT32_MAX ? (uint32_t)mine / (uint32_t)a.k : mine / a.k) : mine;
@@ -807,11 +808,17 @@ void launch_dense_order(int p, const ElemArgs<T>& a, const T* mats, hipStream_t 
     GIAMG_HIP(hipGetLastError());
 }
 
+// In launches of at most UNIT_BLOCKS blocks (a launch holds less than 2^32 threads;
+// one for all pairs would pass that from 9.9 M elements of order 2 on).
+constexpr int64_t UNIT_BLOCKS = 1 << 16;
 template <int P>
-void launch_unit(const ElemArgs<double>& a, hipStream_t s) {
+void launch_unit(ElemArgs<double> a, hipStream_t s) {
     constexpr int NT = 256, V = NT / ((P + 2) * (P + 2));
     const int64_t pairs = a.ne * a.k;
-    element_kernel<double, P, NT, V, true, true><<<(unsigned)((pairs + V - 1) / V), NT, 0, s>>>(a);
+    for (a.pair0 = 0; a.pair0 < pairs; a.pair0 += UNIT_BLOCKS * V) {
+        const int64_t blocks = std::min(UNIT_BLOCKS, (pairs - a.pair0 + V - 1) / V);
+        element_kernel<double, P, NT, V, true, true><<<(unsigned)blocks, NT, 0, s>>>(a);
+    }
 }
 
 // The node step over k columns: one thread per node and VW columns, which it

@@ -260,3 +260,21 @@ def test_sheared_elements_keep_the_precision_of_the_fp32_products(shear, form):
     xh = x.double().cpu().numpy()
     bound = ((6 * (p + 2) + 40) * 64 * shear if form else 2 * (p + 2) ** 3) * 2.0 ** -24 * np.max(abs(A) @ np.abs(xh))
     assert np.max(np.abs(y.double().cpu().numpy() - A @ xh)) <= bound
+
+
+@pytest.mark.parametrize("n,p", [(16, 4), (41, 2)])
+def test_element_matrices_of_several_launches(n, p):
+    """73 k and 116 k blocks form the matrices, two launches of at most 65536.  Batched
+    against the single solve, which has no matrices: both stop at a relative residual
+    of 1e-10 of the same operator, 1e-8 apart at most, for every column."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=6)
+    s = Solver(m.coords, m.l2g, p, 2.0, Options())
+    B = torch.from_numpy(synth.normal_rhs(m.n_nodes * 3, 8).reshape(m.n_nodes, 3)).to("cuda:0")
+    X, infos = s.solve_batch(B)
+    for j in range(3):
+        x, info = s.solve(B[:, j].contiguous())
+        assert infos[j].status == 0 and infos[j].true_relres < 1e-9 and abs(infos[j].iters - info.iters) <= 1
+        assert torch.linalg.norm(x - X[:, j]) <= 1e-8 * torch.linalg.norm(x)
+    s.close()
