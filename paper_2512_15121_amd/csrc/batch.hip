@@ -1325,6 +1325,33 @@ void iteration(BatchCtx& c, double* X, double tol) {
     GIAMG_HIP(hipGetLastError());
 }
 
+// What no block product reads once the fine ones run over the elements: the fine
+// level's rows (their sizes stay) and single-vector element form, the tables and work
+// vectors of single-vector products on every level, and in mixed precision, whose
+// cycle is FP32, the other operators' FP64 values.  At p = 4 the rows of A and A P
+// take up to 199 KB per element, the matrices that replace them 131 KB and eight
+// columns of results 8 KB.
+void release_single_vector_parts(Handle& H) {
+    Level& F = H.levels[0];
+    DevCSR A;
+    A.nrows = F.A.nrows; A.ncols = F.A.ncols; A.nnz = F.A.nnz;
+    F.A = std::move(A);
+    F.AP = DevCSR();
+    F.X = TransferForm();
+    F.E.ev.release();
+    F.elem_products = false;
+    for (Level& L : H.levels) {
+        for (DevCSR* M : {&L.A, &L.P, &L.R, &L.AP}) {
+            M->blk.release_staging();
+            M->blk32.release_staging();
+            if (H.opts.precision == GIAMG_PREC_MIXED) M->val.release();
+        }
+        for (DevBuf<double>* v : {&L.f, &L.x, &L.r, &L.d0, &L.d1, &L.t}) v->release();
+        for (DevBuf<float>* v : {&L.f32, &L.x32, &L.r32, &L.d032, &L.d132, &L.t32}) v->release();
+    }
+    for (DevBuf<double>* v : {&H.x, &H.r, &H.z, &H.p, &H.q, &H.rold, &H.tmp}) v->release();
+}
+
 std::unique_ptr<BatchState> make_state(Handle& H, int k) {
     std::unique_ptr<BatchState> B(new BatchState());
     B->k = k;
@@ -1341,6 +1368,7 @@ std::unique_ptr<BatchState> make_state(Handle& H, int k) {
     }
     if (block_element_form(H)) {
         ensure_element_form(H);
+        if (H.batches_only) release_single_vector_parts(H);
         if (H.porder <= 4) build_element_matrices(H.levels[0].E, B->mixed, H.stream);
         B->elem = true;
         B->ev.alloc(H.levels[0].E.map.n * (size_t)k);
@@ -1392,7 +1420,7 @@ void tune_all(Handle& H, BatchState& B, int k) {
         Level& L = H.levels[l];
         const std::string sl = std::to_string(l);
         const bool elem = l == 0 && B.elem;
-        if (!elem) tile_for<double>(t, L.A, "A" + sl);
+        if (!elem && (l == 0 || !B.mixed)) tile_for<double>(t, L.A, "A" + sl);   // mixed: the cycle is FP32
         if (l + 1 == H.levels.size()) continue;
         const bool ap = H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV && !elem;
         if (B.mixed) {
@@ -1423,7 +1451,7 @@ std::unique_ptr<BatchState> tuned_state(Handle& H, int k) {
             return B;
         } catch (const Error& e) {
             if (B) (void)hipStreamSynchronize(B->stream);
-            if (e.code != GIAMG_ENOMEM || !elem) throw;
+            if (e.code != GIAMG_ENOMEM || !elem || H.levels[0].A.rp.get() == nullptr) throw;
             H.block_rows = true;
             if (!had_matrices) {   // no other state of this handle reads them
                 H.levels[0].E.mat.release();

@@ -297,6 +297,7 @@ struct Handle {
     // batched state
     std::unique_ptr<BatchState, BatchDeleter> batch;
     bool block_rows = false;          // no memory for the block products' element form: rows from then on
+    bool batches_only = false;        // set by the owner (server): no single solves, no level_csr
     double bytes = 0.0;               // algorithmic bytes of launched kernels
     double setup_ms[7] = {0, 0, 0, 0, 0, 0, 0};
     // phase profiling (giamg_profile_enable): event intervals per category,

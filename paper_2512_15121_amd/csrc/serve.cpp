@@ -132,9 +132,10 @@ struct Server {
     }
 
     // Device bytes of a problem's group: measured after its first setup,
-    // before that an estimate (mean row length (p+2)^3 on hexahedral meshes;
-    // coarse levels, transfers and work vectors add ~25 %; then the element
-    // form's results per slot and, up to p = 4, the elements' matrices).
+    // before that an estimate of its setup (mean row length (p+2)^3 on hexahedral
+    // meshes, or the elements' matrices that take the rows' place up to p = 4;
+    // coarse levels, transfers and work vectors add ~25 %; then the element form's
+    // results per slot).
     int64_t need(const Problem& P) const {
         if (P.known_bytes >= 0) return P.known_bytes;
         const double rows = (double)P.n_nodes;
@@ -142,8 +143,8 @@ struct Server {
         const double vb = P.opts.precision == GIAMG_PREC_MIXED ? 16.0 : 12.0;
         const double nl = (P.p + 1.0) * (P.p + 1.0) * (P.p + 1.0);
         const double mats = P.p <= 4 ? (nl + 5.0) * (nl + 5.0) * (vb - 4.0) : 0.0;   // FP64, FP32 copy if mixed
-        return (int64_t)(1.25 * (vb * nnz + 150.0 * rows + 80.0 * rows * o.slots) +
-                         (double)P.n_elem * (8.0 * nl * o.slots + mats));
+        return (int64_t)(1.25 * (std::max(vb * nnz, mats * P.n_elem) + 150.0 * rows + 80.0 * rows * o.slots) +
+                         8.0 * nl * P.n_elem * o.slots);
     }
 
     void setup_main() {
@@ -168,6 +169,7 @@ struct Server {
                 Handle& H = *g->H;
                 H.stream = g->stream;
                 H.opts = P.opts;
+                H.batches_only = true;   // sessions only: the fine rows go where the blocks do without
                 H.porder = P.p;
                 H.lambda = P.lambda;
                 H.n_nodes = P.n_nodes;

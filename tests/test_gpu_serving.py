@@ -234,3 +234,38 @@ def test_server_rejects_invalid_problem(torch_dev):
     x, info, _ = srv.wait(srv.submit(pid, synth.normal_rhs(m.n_nodes, 5)))
     assert info.status == 0 and np.isfinite(x).all()
     srv.close()
+
+
+@pytest.mark.parametrize("n,p,precision", [(9, 3, "fp64"), (16, 3, "mixed"), (6, 4, "fp64"), (8, 4, "mixed"),
+                                           (10, 4, "fp64"), (10, 4, "mixed"), (4, 5, "fp64"), (4, 5, "mixed")])
+def test_served_hierarchies_hold_no_more_than_their_rows_would(torch_dev, n, p, precision):
+    """Block products over the elements keep matrices and results; the fine rows that
+    they make unread are given back, so a resident hierarchy takes no more than one whose
+    products read the rows: (FP64 8, mixed 12) + 4 bytes per nonzero of every operator,
+    the block vectors (six of each level, four of CG, right-hand sides, solutions, staging),
+    the single-vector ones and the coarse inverse, without any tables.  Solutions are
+    those of a batch of the same problem, bit for bit."""
+    torch, dev = torch_dev
+    from paper_2512_15121_amd import Options, Server, Solver
+    slots = 4
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=5)
+    opts = Options(precision=precision, coarse_max=300)
+    s = Solver(m.coords, m.l2g, p, 3.0, opts)
+    levels = [s.level(l) for l in range(s.num_levels())]
+    fine, vec = m.n_nodes, 4 if precision == "mixed" else 8
+    bound = sum((4 + 8 + 8 - vec) * d["nnz_" + q] for d in levels for q in ("A", "P", "R", "AP"))
+    bound += sum(6 * d["rows"] * (slots * vec + 8 + 8 - vec) for d in levels)
+    bound += (4 + 3) * fine * slots * 8 + 10 * fine * 8 + 8 * levels[-1]["rows"] ** 2
+    B = synth.normal_rhs(fine * 6, 9).reshape(fine, 6)
+    X, infos = s.solve_batch(torch.from_numpy(B).to(dev), tol=1e-10)
+    s.close()
+    srv = Server(hbm_budget=8 << 30, slots=slots, chunk=2, tol=1e-10)
+    pid = srv.add_problem(m.coords, m.l2g, p, 3.0, opts)
+    out = [srv.wait(r) for r in [srv.submit(pid, np.ascontiguousarray(B[:, j])) for j in range(6)]]
+    st = srv.stats()
+    srv.close()
+    print(f"n = {n}, p = {p}, {precision}: {st['resident_bytes']} bytes, bound {bound}")
+    assert st["resident_bytes"] <= bound
+    for j, (x, info, _) in enumerate(out):
+        assert info.status == 0 and info.iters == infos[j].iters
+        assert np.array_equal(x, X[:, j].cpu().numpy())
