@@ -1119,7 +1119,7 @@ void bsmooth(BatchCtx& c, size_t l, const T* f, T* x, bool zero_start, const T* 
                                                                     (T)(1.0 / theta), deg == 1, c.run);
         }
     } else {
-        const bool ap = e != nullptr && !(l == 0 && c.B.elem);   // A x costs less there
+        const bool ap = e != nullptr && L.AP.nrows > 0 && !(l == 0 && c.B.elem);   // A x costs less there
         const DevCSR& M = ap ? L.AP : L.A;
         SpmmArgs<T> a = bargs<T>(M, ap ? BL<T>::AP(L) : BL<T>::A(L), k, c.run);
         a.v = ap ? e : x; a.f = ap ? t : f; a.r = r; a.y = d[0]; a.dinv = BL<T>::dinv(L);
@@ -1373,6 +1373,8 @@ std::unique_ptr<BatchState> make_state(Handle& H, int k) {
         B->elem = true;
         B->ev.alloc(H.levels[0].E.map.n * (size_t)k);
     }
+    Level& F = H.levels[0];
+    if (!B->elem && B->mixed && F.A.nnz > 0 && F.A.val32.get() == nullptr) make_fp32_values(F.A, H.stream);
     const size_t tot = (size_t)H.n_nodes * k;
     B->R.alloc(tot); B->P.alloc(tot); B->Q.alloc(tot);
     if (!B->mixed) B->Z.alloc(tot);   // mixed precision: z stays in level 0's x32
@@ -1422,7 +1424,7 @@ void tune_all(Handle& H, BatchState& B, int k) {
         const bool elem = l == 0 && B.elem;
         if (!elem && (l == 0 || !B.mixed)) tile_for<double>(t, L.A, "A" + sl);   // mixed: the cycle is FP32
         if (l + 1 == H.levels.size()) continue;
-        const bool ap = H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV && !elem;
+        const bool ap = H.opts.smoother == GIAMG_SMOOTHER_CHEBYSHEV && !elem && L.AP.nrows > 0;
         if (B.mixed) {
             if (!elem) tile_for<float>(t, L.A, "A" + sl);
             tile_for<float>(t, L.R, "R" + sl);

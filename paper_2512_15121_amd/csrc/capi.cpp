@@ -329,7 +329,7 @@ int giamg_level_describe(giamg_handle h, int32_t level, giamg_level_desc* out) {
         out->nnz_P = L.P.nnz;
         out->nnz_R = L.R.nnz;
         out->lam_hat = L.lam_hat;
-        out->nnz_AP = L.AP.nnz;
+        out->nnz_AP = L.AP.nrows > 0 ? L.AP.nnz : L.nnz_AP;
         out->staged_nnz_A = L.A.blk.nnz_staged;
         out->runs_A = L.A.blk.nruns;
         out->groups_A = L.A.gnblk > 0 ? L.A.ggroups : 0;
@@ -351,6 +351,12 @@ int giamg_level_csr(giamg_handle h, int32_t level, int32_t which, int64_t* row_p
                                  : which == GIAMG_MAT_AP ? &L.AP
                                                          : nullptr;
         GIAMG_REQUIRE(M != nullptr, "unknown matrix");
+        giamg::AllocStreamScope alloc_scope(h->h.stream);
+        giamg::DevCSR AP;   // formed again where it is not kept
+        if (M == &L.AP && M->nrows == 0 && L.nnz_AP > 0) {
+            giamg::spgemm(L.A, L.P, AP, h->h.stream, false);
+            M = &AP;
+        }
         GIAMG_REQUIRE(M->nrows > 0 || which == GIAMG_MAT_A, "matrix absent on this level");
         hipStream_t s = h->h.stream;
         if (row_ptr)

@@ -129,6 +129,13 @@ struct RowBlocks {
         slot.release();
         nruns = nnz_staged = 0;
     }
+    void release_arrays() {   // the counts stay
+        rblk.release();
+        bdesc.release();
+        run_ptr.release();
+        runs.release();
+        slot.release();
+    }
     int64_t device_bytes() const {
         return (int64_t)(rblk.n + bdesc.n) * 8 + (int64_t)(run_ptr.n + runs.n) * 4 + (int64_t)slot.n * 2;
     }
@@ -164,10 +171,19 @@ struct DevCSR {
     // memory in blocks of LEAN_THREADS / lanes rows; no staging tables.
     bool lean = false;
     int64_t lean_nblk = 0;
-    void release_grouping() {
-        gnblk = gentries = ggroups = gnruns = 0;
+    void release_group_arrays() {
         gblk.release(); grows.release(); ggrp.release(); gslot.release();
         grun_ptr.release(); gruns.release(); gval.release(); gval32.release();
+    }
+    void release_grouping() {
+        gnblk = gentries = ggroups = gnruns = 0;
+        release_group_arrays();
+    }
+    // The arrays of the single-vector product forms; their counts stay.
+    void release_product_arrays() {
+        blk.release_arrays();
+        blk32.release_arrays();
+        release_group_arrays();
     }
 };
 // Build the FP64 row blocks of d (and its lanes) from a host copy of its row
@@ -250,7 +266,9 @@ struct Level {
     DevCSR AP;                     // A P (rows of this level, columns of the next), kept
                                    // from the Galerkin product for the post-smoothing residual
     ElementForm E;                 // fine level: element form, where the products use it
-    bool elem_products = false;    // the single-vector products run in the element form
+    bool elem_products = false;    // the single-vector products run in the element form: of A only
+                                   // the FP64 rows are kept, of A P nothing but its size
+    int64_t nnz_AP = 0;            // entries of an A P that is not kept
     TransferForm X;                // and with them, where q > 0, the transfers to the next level
     DevBuf<double> dinv;
     DevBuf<float> dinv32;
@@ -409,6 +427,7 @@ void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32);
 void download_csr(const DevCSR& d, HostCSR& h, hipStream_t s);
 void make_fp32_values(DevCSR& d, hipStream_t s);
 // C = A * B with the full symbolic structure (device SpGEMM).
-void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s);
+// C = A B; tables: with the tables of its single-vector products.
+void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s, bool tables = true);
 
 }  // namespace giamg

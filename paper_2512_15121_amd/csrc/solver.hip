@@ -165,11 +165,11 @@ SpmvArgs<T> args_of(const DevCSR& M, const T* val) {
 // Product arguments over a level's operator: the element form where built.
 template <typename T>
 SpmvArgs<T> args_of_level(const Level& L, const T* val) {
-    SpmvArgs<T> a = args_of<T>(L.A, val);
-    if (L.elem_products) {
-        a.elem = &L.E;
-        a.nblk = element_blocks(a.n);
-    }
+    if (!L.elem_products) return args_of<T>(L.A, val);
+    SpmvArgs<T> a;
+    a.n = L.A.nrows; a.ncols = L.A.ncols; a.nnz = L.A.nnz;
+    a.elem = &L.E;
+    a.nblk = element_blocks(a.n);
     return a;
 }
 
@@ -429,13 +429,17 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
             break;
         }
         t0 = clock_t_::now();
-        spgemm(F.A, F.P, F.AP, H.stream);
+        spgemm(F.A, F.P, F.AP, H.stream, !F.elem_products);
         Level C;
         C.kind = GIAMG_LEVEL_P;
         C.order = q;
         C.n = nc;
         C.l2g = std::move(l2g_next);
         spgemm(F.R, F.AP, C.A, H.stream);
+        if (F.elem_products) {   // no product reads it (vcycle, bsmooth)
+            F.nnz_AP = F.AP.nnz;
+            F.AP = DevCSR();
+        }
         H.setup_ms[3] += ms_since(t0);
         H.levels.push_back(std::move(C));
         // Transfers by the element form from a million entries of P on.  Whole solves with and
@@ -508,6 +512,12 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     t0 = clock_t_::now();
     if (o.lean_max_nnz > 0) assign_lean_forms(H, o.lean_max_nnz);
     if (o.row_groups && !o.direct_gathers) build_grouped_forms(H, mixed);
+    // (built so that a level's description tells what its rows' products would use)
+    if (H.levels[0].elem_products) H.levels[0].A.release_product_arrays();
+    if (H.levels[0].X.q > 0) {
+        H.levels[0].P.release_product_arrays();
+        H.levels[0].R.release_product_arrays();
+    }
     const double grouping_ms = ms_since(t0);
     // work buffers
     int64_t maxn = 1, maxblk = 1;
@@ -529,9 +539,9 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     for (size_t l = 0; l < H.levels.size(); ++l) {
         Level& L = H.levels[l];
         alloc_level_vectors(L, mixed);
-        if (mixed) make_fp32_operator(L.A, H.stream);
+        if (mixed && !L.elem_products) make_fp32_operator(L.A, H.stream);
         if (l + 1 == H.levels.size() && !jacobi) break;
-        if (mixed) make_fp32_operator(L.AP, H.stream);
+        if (mixed && L.AP.nrows > 0) make_fp32_operator(L.AP, H.stream);
         L.dinv.alloc(L.n);
         DevBuf<int> bad(1);
         GIAMG_HIP(hipMemsetAsync(bad.get(), 0, sizeof(int), H.stream));
@@ -887,17 +897,18 @@ void residual(Handle& H, Level& L, const T* f, const T* x, T* out) {
 }
 
 template <typename T>
-SpmvArgs<T> args_R(const Level& L) {
-    SpmvArgs<T> a = args_of<T>(L.R, LV<T>::R(L));
-    if (L.X.q > 0) a.xfer = &L.X;
+SpmvArgs<T> args_transfer(const Level& L, const DevCSR& M, const T* val) {
+    if (L.X.q == 0) return args_of<T>(M, val);
+    SpmvArgs<T> a;
+    a.n = M.nrows; a.ncols = M.ncols; a.nnz = M.nnz;
+    a.xfer = &L.X;
+    a.nblk = element_blocks(a.n);
     return a;
 }
 template <typename T>
-SpmvArgs<T> args_P(const Level& L) {
-    SpmvArgs<T> a = args_of<T>(L.P, LV<T>::P(L));
-    if (L.X.q > 0) a.xfer = &L.X;
-    return a;
-}
+SpmvArgs<T> args_R(const Level& L) { return args_transfer<T>(L, L.R, LV<T>::R(L)); }
+template <typename T>
+SpmvArgs<T> args_P(const Level& L) { return args_transfer<T>(L, L.P, LV<T>::P(L)); }
 
 template <typename T>
 void restrict_to(Handle& H, Level& L, const T* r, T* fc) {

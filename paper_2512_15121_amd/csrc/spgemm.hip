@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(SG_WAVE) sg_numeric_kernel(int64_t n, const in
     }
 }
 
-void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s) {
+void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s, bool tables) {
     GIAMG_REQUIRE(A.ncols == B.nrows, "spgemm: inner dimensions differ");
     const int64_t n = A.nrows;
     C.nrows = n;
@@ -196,7 +196,7 @@ void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s) {
     C.val.alloc(C.nnz);
     if (C.nnz == 0) {
         GIAMG_HIP(hipStreamSynchronize(s));
-        setup_row_blocks(C, hrp, s);
+        if (tables) setup_row_blocks(C, hrp, s);
         return;
     }
     sg_fill_kernel<<<(unsigned)n, SG_WAVE, 0, s>>>(n, A.rp.get(), A.ci.get(), B.rp.get(), B.ci.get(),
@@ -216,7 +216,7 @@ void spgemm(const DevCSR& A, const DevCSR& B, DevCSR& C, hipStream_t s) {
     }
     GIAMG_HIP(hipGetLastError());
     GIAMG_HIP(hipStreamSynchronize(s));
-    setup_row_blocks(C, hrp, s);
+    if (tables) setup_row_blocks(C, hrp, s);
 }
 
 }  // namespace giamg

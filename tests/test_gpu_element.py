@@ -278,3 +278,56 @@ def test_element_matrices_of_several_launches(n, p):
         assert infos[j].status == 0 and infos[j].true_relres < 1e-9 and abs(infos[j].iters - info.iters) <= 1
         assert torch.linalg.norm(x - X[:, j]) <= 1e-8 * torch.linalg.norm(x)
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,p", [(14, 4), (22, 3), (7, 5)])
+def test_handles_keep_nothing_that_their_products_do_not_read(n, p, precision):
+    """With the products over the elements a handle's memory is bounded by the FP64
+    rows of A (level_csr), P and R and their FP32 copies, the coarse levels with A P
+    and tables (2 bytes per entry and precision), the element and transfer forms, and
+    vectors: no FP32 copy of A, no A P, no tables of either.  level_csr still gives
+    A P, and a level's description the tables' counts."""
+    import torch
+    from paper_2512_15121_amd import Options, Solver, giamg
+    m = synth.hex_mesh(n, p, perturb=0.1, seed=5)
+    live = {}
+
+    def alloc(nbytes, stream):
+        q = torch.cuda.caching_allocator_alloc(nbytes, 0, stream)
+        live[q] = nbytes
+        return q
+
+    def release(q):
+        live.pop(q)
+        torch.cuda.caching_allocator_delete(q)
+
+    giamg.set_allocator(alloc, release)
+    try:
+        s = Solver(m.coords, m.l2g, p, 2.0, Options(precision=precision, coarse_max=300))
+        held = sum(live.values())
+        d = [s.level(l) for l in range(s.num_levels())]
+        assert s.time_kernel("spmv", 0, 1)[1] < 8 * d[0]["nnz_A"]
+        f32 = 4 if precision == "mixed" else 0
+        nl, nodes = (p + 1) ** 3, sum(lv["rows"] for lv in d)
+        bound = 12 * d[0]["nnz_A"] + (12 + f32) * (d[0]["nnz_P"] + d[0]["nnz_R"])
+        bound += sum((12 + f32 + 2 + f32 // 2) * lv["nnz_" + q] for lv in d[1:] for q in ("A", "P", "R", "AP"))
+        bound += m.n_elem * (4 * nl + 8 * nl + 4 * nl + 21 * 8 + 23 * f32)      # map, results, entries, geometry
+        bound += m.n_elem * (4 * nl + 2 * 4 * (nl // 2))                        # transfers' maps and entries
+        bound += nodes * (4 * 8 + 4 * 4 + 7 * (8 + f32)) + 7 * 8 * m.n_nodes    # row pointers, lists, vectors
+        bound += 8 * d[-1]["rows"] ** 2 + nodes * 8                             # coarse inverse, row blocks, partials
+        print(f"n = {n}, p = {p}, {precision}: {held} bytes, bound {bound}")
+        assert held <= bound
+        if d[0]["nnz_A"] > 2000000:
+            assert d[0]["staged_nnz_A"] == d[0]["nnz_A"]
+        mats = []
+        for which, cols in (("A", d[0]["rows"]), ("P", d[1]["rows"]), ("AP", d[1]["rows"])):
+            rp, ci, val = s.level_csr(0, which)
+            mats.append(sp.csr_matrix((val, ci, rp), shape=(d[0]["rows"], cols)))
+        A, P, AP = mats
+        assert d[0]["nnz_AP"] == AP.nnz
+        assert abs(AP - A @ P).max() <= 1e-12 * (abs(A) @ abs(P)).max()
+        s.close()
+        assert live == {}
+    finally:
+        giamg.set_allocator()
