@@ -207,3 +207,24 @@ def test_stopped_columns_keep_their_reported_residuals(precision):
         assert (infos[slot].iters, infos[slot].status, infos[slot].relres) == first[j], j
     ses.close()
     s.close()
+
+
+def test_batch_kernel_shapes_on_the_rows_give_the_same_bits(env):
+    """The comparison of the block-product shapes above where the fine products do read
+    the rows (mixed precision with one pinned node; elsewhere they run over the
+    elements whatever the shape): p = 4, FP64 product and FP32 cycle, rows grouped by
+    7, 6, 5, 4, 3 and 1."""
+    torch, dev, _, _ = env
+    k = 70
+    m = synth.hex_mesh(3, 4, perturb=0.1, seed=6)
+    from paper_2512_15121_amd import Options, Solver
+    s = Solver(m.coords, m.l2g, 4, 0.0, Options(bc="pin", coarse_max=100, precision="mixed"))
+    assert s.time_kernel("spmv", 0, 1)[1] >= 8 * s.level(0)["nnz_A"]
+    s.close()
+    B = synth.pinned_normal_batch(m.n_nodes, k, 35)
+    out = _shape_solutions(torch, dev, m, 4, 0.0, "pin", "mixed", B)
+    X0, it0 = out["lanes"]
+    assert all(st == 0 for _, st in it0)
+    for kind in ("wave", "group"):
+        X, it = out[kind]
+        assert it == it0 and torch.equal(X, X0), kind

@@ -161,3 +161,36 @@ def test_product_forms_fullsize_bitwise(full):
     assert torch.linalg.norm(x1 - x2) <= 1e-10 * torch.linalg.norm(x2)
     s.close()
     s3.close()
+
+
+def test_row_product_forms_fullsize_bitwise(full):
+    """Grouped, CSR-staged and direct products of the fine rows at the benchmark size, FP64
+    and FP32, bit for bit, on handles whose products read the rows (mixed precision
+    with one pinned node: elsewhere at this size they run over the elements, whichever
+    form the rows have).  Whole solves agree bit for bit between the CSR forms, and with
+    the grouped form (other partials of the dots, and the constant held by one node
+    alone) to 1e-7."""
+    torch, m, _, _ = full
+    from paper_2512_15121_amd import Solver, Options
+    rng = np.random.default_rng(5)
+    x = torch.from_numpy(rng.standard_normal(m.n_nodes)).to("cuda:0")
+    b = torch.from_numpy(synth.pinned_normal_batch(m.n_nodes, 1, 12)[:, 0].copy()).to("cuda:0")
+    ys, sols = [], []
+    for kw in ({}, {"direct_gathers": True}, {"row_groups": True}):
+        s = Solver(m.coords, m.l2g, P_ORD, 0.0, Options(precision="mixed", bc="pin", **kw))
+        d = s.level(0)
+        assert s.time_kernel("spmv", 0, 1)[1] >= 8 * d["nnz_A"], "the product reads the rows' values"
+        assert (d["staged_nnz_A"] == d["nnz_A"]) == (not kw) and (d["groups_A"] > 0) == ("row_groups" in kw)
+        y, y32 = torch.zeros_like(x), torch.zeros_like(x, dtype=torch.float32)
+        s.apply("spmv", 0, x, out=y)
+        s.apply("spmv", 0, x.float(), out=y32, fp32=True)
+        ys.append((y, y32))
+        xs, info = s.solve(b, tol=1e-10)
+        assert info.status == 0 and info.true_relres < 1e-9
+        sols.append((xs, info.iters))
+        s.close()
+    for y, y32 in ys[1:]:
+        assert torch.equal(y, ys[0][0]) and torch.equal(y32, ys[0][1])
+    assert sols[0][1] == sols[1][1] and torch.equal(sols[0][0], sols[1][0])
+    assert abs(sols[2][1] - sols[0][1]) <= 1
+    assert torch.linalg.norm(sols[2][0] - sols[0][0]) <= 1e-7 * torch.linalg.norm(sols[0][0])
