@@ -1102,6 +1102,7 @@ __global__ void __launch_bounds__(256) coarse_kernel(int64_t n, const double* __
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (j + u * WAVE < n) acc = __builtin_fma(m[u], (double)g[u], acc);
+        if (done) break;   // after the first loads, under way with the flag's: 9261 rows hold 0.7 GB
     }
     acc = wave_sum(acc);
     if (lane == 0 && !done) x[row] = (T)acc;
@@ -1275,6 +1276,7 @@ __global__ void __launch_bounds__(RED_THREADS) reduce_kernel(int64_t m, const do
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (i + u * RED_THREADS < m) s += v[u];
+            if (done) break;
         }
         s = block_sum<RED_THREADS>(s, sh);
         if (threadIdx.x == 0 && !done) out[c] = s;
