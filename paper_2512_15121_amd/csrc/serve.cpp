@@ -49,6 +49,7 @@ struct Problem {
     int group = -1;          // resident group, or -1
     int64_t known_bytes = -1;  // device bytes measured at its last setup
     int64_t reserved = 0;      // bytes reserved while its setup runs
+    int64_t passing = 0;       // and those that its setup takes beyond them, one setup at a time
     bool setting_up = false;
     int failed = 0;          // error code of a failed setup
     std::string fail_msg;
@@ -131,20 +132,34 @@ struct Server {
         setup_done.clear();
     }
 
-    // Device bytes of a problem's group: measured after its first setup,
-    // before that an estimate of its setup (mean row length (p+2)^3 on hexahedral
-    // meshes, or the elements' matrices that take the rows' place up to p = 4;
-    // coarse levels, transfers and work vectors add ~25 %; then the element form's
-    // results per slot).
+    // Bytes of a fine operator's rows (mean row length (p+2)^3 on hexahedral meshes).
+    static double row_bytes(const Problem& P) {
+        const double vb = P.opts.precision == GIAMG_PREC_MIXED ? 16.0 : 12.0;
+        return vb * P.n_nodes * (P.p + 2.0) * (P.p + 2.0) * (P.p + 2.0);
+    }
+
+    // Device bytes of a problem's group: measured after its first setup, before that
+    // an estimate.  Where the block products run over the elements the rows go after
+    // setup: their results per slot, up to p = 4 the elements' matrices, and coarse
+    // levels and transfers (a tenth of the rows) remain; elsewhere the rows, and ~25 %
+    // for the rest.
     int64_t need(const Problem& P) const {
         if (P.known_bytes >= 0) return P.known_bytes;
-        const double rows = (double)P.n_nodes;
-        const double nnz = rows * (P.p + 2.0) * (P.p + 2.0) * (P.p + 2.0);
-        const double vb = P.opts.precision == GIAMG_PREC_MIXED ? 16.0 : 12.0;
+        const double rows = (double)P.n_nodes, vectors = 150.0 * rows + 80.0 * rows * o.slots;
+        if (P.p < 2 || (P.opts.precision == GIAMG_PREC_MIXED && P.opts.bc == GIAMG_BC_PIN))
+            return (int64_t)(1.25 * (row_bytes(P) + vectors));
         const double nl = (P.p + 1.0) * (P.p + 1.0) * (P.p + 1.0);
-        const double mats = P.p <= 4 ? (nl + 5.0) * (nl + 5.0) * (vb - 4.0) : 0.0;   // FP64, FP32 copy if mixed
-        return (int64_t)(1.25 * (std::max(vb * nnz, mats * P.n_elem) + 150.0 * rows + 80.0 * rows * o.slots) +
-                         8.0 * nl * P.n_elem * o.slots);
+        const double mats = P.p <= 4 ? (nl + 5.0) * (nl + 5.0) * (P.opts.precision == GIAMG_PREC_MIXED ? 12.0 : 8.0) : 0.0;
+        return (int64_t)(0.1 * row_bytes(P) + 1.25 * vectors + P.n_elem * (mats + 8.0 * nl * o.slots));
+    }
+    // Device bytes at the peak of its setup: the rows, A P and tables, before they go.
+    int64_t setup_need(const Problem& P) const { return std::max(need(P), (int64_t)(1.5 * row_bytes(P) + 250.0 * P.n_nodes)); }
+    // requires mu held: the setups under way take the most that one of them does beyond
+    // its reservation (the worker makes them one after the other)
+    int64_t passing() const {
+        int64_t b = 0;
+        for (const Problem& P : problems) b = std::max(b, P.passing);
+        return b;
     }
 
     void setup_main() {
@@ -200,7 +215,7 @@ struct Server {
                 problems[pid].fail_msg = "setup failed: " + msg;
                 problems[pid].setting_up = false;
                 reserved -= problems[pid].reserved;
-                problems[pid].reserved = 0;
+                problems[pid].reserved = problems[pid].passing = 0;
                 g.reset();
             } else {
                 setup_done.push_back(std::move(g));
@@ -239,10 +254,12 @@ struct Server {
         cv_done.notify_all();
     }
 
-    // requires mu held: evict idle groups (LRU) until `bytes` more fit; a
-    // group larger than the budget is admitted only into an empty cache
-    bool make_room(int64_t bytes, const std::map<int, std::vector<Request*>>& queued) {
-        while (resident + reserved + bytes > o.hbm_budget) {
+    // requires mu held: evict idle groups (LRU) until `bytes` more fit, and `more`
+    // while the setup lasts; a group larger than the budget is admitted only into
+    // an empty cache
+    bool make_room(int64_t bytes, int64_t more, const std::map<int, std::vector<Request*>>& queued) {
+        const int64_t all = bytes + std::max(more, passing());
+        while (resident + reserved + all > o.hbm_budget) {
             if (resident == 0 && reserved == 0) return true;
             int victim = -1;
             for (size_t i = 0; i < groups.size(); ++i) {
@@ -379,7 +396,7 @@ struct Server {
                     setup_done.pop_back();
                     Problem& P = problems[g->problem];
                     reserved -= P.reserved;
-                    P.reserved = 0;
+                    P.reserved = P.passing = 0;
                     P.known_bytes = g->bytes;
                     resident += g->bytes;
                     st.peak_bytes = std::max(st.peak_bytes, resident);
@@ -413,9 +430,11 @@ struct Server {
                         wanted[P.group].push_back(&r);
                     } else if (!P.setting_up) {
                         const int64_t est = need(P);
-                        if (make_room(est, wanted)) {
+                        const int64_t more = setup_need(P) - est;
+                        if (make_room(est, more, wanted)) {
                             P.setting_up = true;
                             P.reserved = est;
+                            P.passing = more;
                             reserved += est;
                             setup_jobs.push_back(r.problem);
                             cv_setup.notify_one();

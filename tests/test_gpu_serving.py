@@ -269,3 +269,59 @@ def test_served_hierarchies_hold_no_more_than_their_rows_would(torch_dev, n, p, 
     for j, (x, info, _) in enumerate(out):
         assert info.status == 0 and info.iters == infos[j].iters
         assert np.array_equal(x, X[:, j].cpu().numpy())
+
+
+def test_server_setups_stay_within_the_budget(torch_dev):
+    """A hierarchy takes several times its resident bytes while it is set up (the fine
+    rows go at its end).  Twelve problems round and round in a budget for a few: what is
+    allocated never passes it, set up for the first time or again.  With room for all
+    and one setup, requests that arrive together evict nothing."""
+    import threading
+    torch, dev = torch_dev
+    from paper_2512_15121_amd import Options, Server, giamg
+    n, p, slots = 4, 5, 2
+    mesh = synth.hex_mesh(n, p, perturb=0.1, seed=5)
+    rows = 12 * mesh.n_nodes * (p + 2) ** 3
+    state, live, lock = {"sum": 0, "peak": 0}, {}, threading.Lock()
+
+    def alloc(nbytes, stream):
+        q = torch.cuda.caching_allocator_alloc(nbytes, 0, stream)
+        with lock:
+            live[q] = nbytes
+            state["sum"] += nbytes
+            state["peak"] = max(state["peak"], state["sum"])
+        return q
+
+    def release(q):
+        with lock:
+            state["sum"] -= live.pop(q)
+        torch.cuda.caching_allocator_delete(q)
+
+    b = synth.normal_rhs(mesh.n_nodes, 3)
+
+    def serve(budget, count, together):
+        srv = Server(hbm_budget=budget, slots=slots, chunk=2, tol=1e-10)
+        try:
+            pids = [srv.add_problem(mesh.coords, mesh.l2g, p, 1.0 + i, Options()) for i in range(count)]
+            for first, ids in ((True, pids), (False, pids)):
+                if together and first:
+                    srv.wait(srv.submit(ids[0], b))
+                    for r in [srv.submit(i, b) for i in ids]:
+                        assert srv.wait(r)[1].status == 0
+                else:
+                    for i in ids:
+                        assert srv.wait(srv.submit(i, b))[1].status == 0
+            return srv.stats()
+        finally:
+            srv.close()
+
+    giamg.set_allocator(alloc, release)
+    try:
+        st = serve(int(2.2 * rows), 12, False)
+        assert st["evictions"] > 0 and st["setups"] > 12
+        assert state["peak"] <= int(2.2 * rows), state["peak"]
+        st = serve(int(2.5 * rows), 3, True)
+        assert st["evictions"] == 0 and st["setups"] == 3
+        assert live == {}
+    finally:
+        giamg.set_allocator()
