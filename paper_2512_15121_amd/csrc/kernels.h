@@ -269,7 +269,7 @@ bool update_closes(int64_t n);
 // The updates take alpha from pq's partials (FIN_ALPHA).  With ctl (only where
 // update_closes) they end with the reduction of r . r and FIN_CONV, without it
 // with the partials; partial and pq.p must not overlap.
-void launch_pcg_update(int64_t n, double* x, double* r, double* rold, const double* p,
+void launch_pcg_update(int64_t n, double* x, double* r, const double* p,
                        const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
                        hipStream_t s);
 // The same update fused with the fine level's zero-start Chebyshev init of

@@ -1392,9 +1392,8 @@ __device__ __forceinline__ void update_sums(double s, double* partial, double* s
 
 template <bool CLOSE>
 __global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREADS) pcg_update_kernel(
-    int64_t n, double* __restrict__ x, double* __restrict__ r, double* __restrict__ rold,
-    const double* __restrict__ p, const double* __restrict__ q, double* scal, double* partial, PartialSums pq,
-    int* ctl, const int* stop) {
+    int64_t n, double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
+    const double* __restrict__ q, double* scal, double* partial, PartialSums pq, int* ctl, const int* stop) {
     __shared__ double sh[RED_THREADS / WAVE];
     const int done = stop != nullptr ? *stop : 0;
     const double alpha = fold_alpha(pq, scal, sh, done);
@@ -1403,9 +1402,7 @@ __global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREA
     double s = 0.0;
     for (int64_t i = rows.first; i < n; i += rows.step) {
         x[i] += alpha * p[i];
-        const double ri = r[i];
-        if (rold) rold[i] = ri;
-        const double rn = ri - alpha * q[i];
+        const double rn = r[i] - alpha * q[i];
         r[i] = rn;
         s += rn * rn;
     }
@@ -1422,10 +1419,10 @@ __global__ void __launch_bounds__(CLOSE ? CLOSE_BLOCKS * VEC_THREADS : VEC_THREA
             KERNEL<false><<<nb, VEC_THREADS, 0, s>>>(__VA_ARGS__, g_stop);                                   \
         GIAMG_HIP(hipGetLastError());                                                                        \
     } while (0)
-void launch_pcg_update(int64_t n, double* x, double* r, double* rold, const double* p,
+void launch_pcg_update(int64_t n, double* x, double* r, const double* p,
                        const double* q, double* scal, double* partial, const PartialSums& pq, int* ctl,
                        hipStream_t s) {
-    GIAMG_UPDATE(pcg_update_kernel, n, x, r, rold, p, q, scal, partial, pq, ctl);
+    GIAMG_UPDATE(pcg_update_kernel, n, x, r, p, q, scal, partial, pq, ctl);
 }
 
 // The flexible-CG update of a mixed-precision solve: also r_new rounded to

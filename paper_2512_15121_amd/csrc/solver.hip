@@ -1139,7 +1139,7 @@ int solve_on(Handle& H, const CgWork& w, bool allow_graph, const double* b, doub
                         launch_pcg_update_cheb0(n, xi, w.r, w.p, w.q, w.scal, rr, pq, close, F.dinv.get(),
                                                 F.r.get(), F.d0.get(), cheb_coef(H, F).inv_theta, st);
                     } else {
-                        launch_pcg_update(n, xi, w.r, nullptr, w.p, w.q, w.scal, rr, pq, close, st);
+                        launch_pcg_update(n, xi, w.r, w.p, w.q, w.scal, rr, pq, close, st);
                     }
                 }
                 if (!close) {
