@@ -903,7 +903,11 @@ bool spd_inverse(const std::vector<double>& A, int64_t n, std::vector<double>& i
         for (int64_t j = 0; j < n; ++j) {
             double d = L[j * n + j];
             for (int64_t k = 0; k < j; ++k) d -= L[j * n + k] * L[j * n + k];
-            if (!(d > 0.0)) {
+            // every thread forms the same d, so all of them leave at the same column
+            // (a flag of one that is a column ahead would let a slower one leave
+            // before the barrier the others wait at)
+            const bool fail = !(d > 0.0);
+            if (fail) {
                 ok = false;
             } else {
                 d = std::sqrt(d);
@@ -915,7 +919,7 @@ bool spd_inverse(const std::vector<double>& A, int64_t n, std::vector<double>& i
             }
             arrived.fetch_add(1);   // column j done: the next reads it
             while (arrived.load() < (j + 1) * nt) std::this_thread::yield();
-            if (!ok) return;
+            if (fail) return;
             // every thread has read the diagonal entry of column j; later
             // columns do not read it, the solves do
             if (t == 0) L[j * n + j] = d;

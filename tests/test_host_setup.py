@@ -5,6 +5,10 @@ next-level element maps, aggregates.  Floating point within tolerances set
 by the arithmetic: assembled values (the same quadrature summed in another
 order: a few ulps of the largest term) and transfer values.
 """
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -242,3 +246,33 @@ def test_coarse_inverse_rejects_indefinite_and_bad_sizes():
         assert lib.giamg_host_coarse_inverse(giamg._ptr(buf), n, giamg._ptr(buf)) == giamg.EINVAL
     with pytest.raises(ValueError):
         giamg.host_coarse_inverse(np.zeros((3, 4)))
+
+
+def test_coarse_inverse_of_an_indefinite_matrix_returns():
+    """A pivot that is not positive ends the factorisation on every thread at the same
+    column, whichever is ahead (in a process of its own: a thread that left early
+    would leave the others waiting for good)."""
+    code = """
+import os
+import subprocess
+import sys
+
+import numpy as np
+from paper_2512_15121_amd import giamg
+rng = np.random.default_rng(0)
+for n in (64, 129, 200):
+    for bad in (n - 1, n // 2, 1, 0):
+        A = rng.standard_normal((n, n))
+        A = A @ A.T + n * np.eye(n)
+        A[bad, bad] = -1.0
+        for _ in range(50):
+            try:
+                giamg.host_coarse_inverse(A)
+            except giamg.GiamgError as e:
+                assert e.code == giamg.EINVAL
+            else:
+                raise AssertionError("accepted")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
