@@ -604,8 +604,7 @@ def main():
     # dominant kernel: the fused Chebyshev step on the fine operator, timed in
     # the timed solves above; algorithmic bytes from the operator's sizes
     n0, nnz0 = levels[0]["rows"], levels[0]["nnz_A"]
-    # (of the rows, or of the element form, which reads no value per nonzero and
-    # is bound by FP64 arithmetic and LDS in its element kernel, not by HBM)
+    # (of the rows, or of the element form, which reads no value per nonzero)
     iso_ms, fmt_bytes = solver.time_kernel("cheb_step", level=0, reps=50)
     elem = fmt_bytes < 8.0 * nnz0
 
@@ -616,7 +615,9 @@ def main():
     achieved = alg_bytes / (step_ms * 1e-3) / 1e9
     stream_gbs = read_bandwidth(4 << 30, 10)
     traffic = traffic_entry(args.workload)
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
+    # the element form's step: instruction and LDS latency at the three waves per SIMD that
+    # the FP64 element kernel's registers leave; the rows': HBM.  The rate is HBM's either way
+    roofline = {"bound": "latency" if elem else "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                 "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                 "traffic": traffic,
                 "kernel": (f"element_kernel<double, {w['p']}> and element_node_kernel<double, SPMV_CHEB_STEP>"
@@ -706,11 +707,9 @@ def main():
 
 def serving(torch, Server, Options, size, slots=8, chunk=2, hold_ms=None):
     """The serving trace of the chosen size (small: 200 requests, n <= 8,
-    p <= 4; medium: 2000 requests, n <= 16, p <= 6, ~78 GB of hierarchies;
-    large: 2000 requests, n <= 20, p <= 6, ~187 GB, the largest n range
-    whose hierarchies all fit one MI355X's HBM; full: n <= 24, ~381 GB of
-    hierarchies in mixed precision, so the full trace runs in FP64 without
-    staged-gather tables, ~15 B per fine nonzero, within a 270 GB budget)."""
+    p <= 4; medium: 2000 requests, n <= 16, p <= 6, ~15 GB of hierarchies;
+    large: 2000 requests, n <= 20, p <= 6, ~36 GB; full: n <= 24, in FP64
+    without staged-gather tables, ~83 GB)."""
     if hold_ms is None:   # admission in batches, held at most one solve's time (or 10 s)
         hold_ms = 10000
     try:

@@ -30,12 +30,18 @@
  *     results to the host synchronise that stream before returning.
  *   - A handle is not thread-safe: calls on one handle must not overlap.
  *     Distinct handles are independent.
- *   - The fine operator's products in giamg_solve, giamg_solve_noalloc and
- *     giamg_apply run over the elements (sum factorisation, same operator to
- *     rounding) where it is large enough (at least 4 M and 0.15 M p^2
- *     nonzeros, p >= 2), over its CSR rows otherwise; from a million entries
- *     of P on its transfers do so too.  direct_gathers,
- *     row_groups and lean_max_nnz choose the form of the CSR products.
+ *   - The fine operator's products run over the elements instead of its CSR
+ *     rows (same operator to rounding) for 2 <= p <= 10: in giamg_solve,
+ *     giamg_solve_noalloc and giamg_apply from 4 M and 0.15 M p^2 nonzeros on
+ *     (with the nodal basis, keep_boundary = 0 and a million entries of P the
+ *     transfers next to it too), in giamg_solve_batch, sessions and the
+ *     server at every size.  Not in mixed precision with one pinned node or
+ *     on elements whose geometry FP32 does not serve (sheared 1000 times or
+ *     stretched 10^6 times), and not in batches of a handle for whose element
+ *     matrices or results the device had no memory (p <= 4: 8 bytes, mixed
+ *     12, per entry of every element's matrix).  direct_gathers, row_groups,
+ *     lean_max_nnz and batch_kernel choose among the forms of the CSR
+ *     products, here and on the other levels.
  */
 #ifndef GIAMG_H
 #define GIAMG_H
@@ -108,7 +114,8 @@ typedef struct giamg_opts {
                               coarse node by the fine node at the nearest lattice
                               position and interpolates from the order-q GLL points */
     int32_t  batch_kernel; /* GIAMG_BATCH_*: kernel shape of the block products in
-                              giamg_solve_batch.  AUTO (the default) times every shape on
+                              giamg_solve_batch, for the operators that it multiplies by
+                              rows.  AUTO (the default) times every shape on
                               an operator's first batched product and keeps the fastest;
                               LANES, WAVE and GROUP force one.  All give the same results,
                               bit for bit */
@@ -357,6 +364,8 @@ typedef struct giamg_level_desc {
     int64_t nnz_A, nnz_P, nnz_R;   /* P/R are 0 on the coarsest level */
     double  lam_hat;     /* lambda_max(D^-1 A) estimate (0 on the coarsest level) */
     int64_t nnz_AP;      /* 0 on the coarsest level */
+    /* the form of A's rows (where its products run over the elements: the form
+       they would have) */
     int64_t staged_nnz_A;  /* nonzeros of A in row blocks with staged gathers (0: all direct,
                               or A runs in the grouped form) */
     int64_t runs_A;        /* column runs those blocks stage */
@@ -546,6 +555,9 @@ void giamg_session_free(giamg_session s);
  * on its own stream, so different hierarchies overlap on the device);
  * hierarchies stay cached on the device and are set up on a worker thread
  * when the HBM budget allows, evicting idle ones least recently used first.
+ * A resident hierarchy holds what its sessions' products read: with the fine
+ * products over the elements not the fine operator's rows, which its setup
+ * needs; the budget keeps room for the setup under way.
  * Latency runs from giamg_server_submit to the solution being in x. */
 typedef struct giamg_server_s* giamg_server;
 

@@ -1006,7 +1006,7 @@ Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 // every k or for none (a column's bits do not depend on the batch): by matrix
 // instructions on the elements' matrices up to p = 4, by sum factorisation from
 // p = 5, where an element's matrix outgrows what it saves.  Measured (whole
-// batched solves, element form / CSR block products, mixed precision): 20^3 p = 3
+// batched solves, element form / CSR block products, mixed precision, Dirichlet): 20^3 p = 3
 // k = 64 15.6 / 19.1 ms, k = 8 6.6 / 14.8, k = 1 5.5 / 13; 16^3 p = 4 k = 64 20.5 / 26.9,
 // 11^3 p = 4 k = 8 4.8 / 12.2; 16^3 p = 2 k = 64 4.4 / 4.6, k = 16 3.1 / 3.7; 10^3 p = 5
 // k = 64 30 / 34, k = 8 9.9 / 46; 8^3 p = 6 k = 48 13 / 23.  Sum factorisation at p = 4
