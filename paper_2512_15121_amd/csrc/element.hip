@@ -49,6 +49,8 @@ __host__ __device__ constexpr int element_tile(int nlp, int i, int j) {
     return ((t * (nlp / 16) + i / 16) * 64 + g * 16 + i % 16) * kb + b;
 }
 
+// 120 bytes: the launch's own arguments (the grid's size) follow in the same 64 bytes as
+// the last ones; eight bytes more cost 0.2 us a launch (a third line of arguments).
 template <typename T>
 struct ElemArgs {
     int64_t ne = 0;
@@ -59,13 +61,15 @@ struct ElemArgs {
     const T* tabs = nullptr;         // 1-D tables (element_tables)
     T lambda = 0, ps = 1, pt = -1;   // pair transform of the inner positions (element_tables)
     int k = 1;                       // columns of v ([n][k]) and ev ([ne][nl][k])
+    int e0 = 0;                      // UNIT: first element of this launch
     const int* stop = nullptr;
     const int* run = nullptr;        // when set and zero, nothing to do
     const double* vnz = nullptr;     // when set and zero, v is +0: nothing to do
     double* mat = nullptr;           // UNIT: element matrices in tiles
     float* mat32 = nullptr;
-    int64_t pair0 = 0;               // UNIT: first (element, column) pair of this launch
 };
+
+static_assert(sizeof(ElemArgs<double>) <= 120, "kernel arguments of element_kernel");
 
 // Every multiply-add is written out, so each instance of the kernel gives the
 // same bits (see the contract pragma at each function).
@@ -235,7 +239,7 @@ __global__ void __launch_bounds__(NT) element_kernel(ElemArgs<T> a) {
     __shared__ T sh[V * 3 * N * Q2];
     const int tid = threadIdx.x;
     const int v = tid % V, line = tid / V;
-    const int64_t first = (UNIT ? a.pair0 : 0) + xcd_block(blockIdx.x, gridDim.x) * V;   // element, or pair
+    const int64_t first = (UNIT ? (int64_t)a.e0 * a.k : 0) + xcd_block(blockIdx.x, gridDim.x) * V;   // element, or pair
     const int64_t total = COLS ? a.ne * a.k : a.ne;
     const int64_t mine = min(first + v, total - 1);
     const int64_t e = COLS ? (total <= (int64_t)UINT32_MAX ? (uint32_t)mine / (uint32_t)a.k : mine / a.k) : mine;
@@ -814,9 +818,10 @@ constexpr int64_t UNIT_BLOCKS = 1 << 16;
 template <int P>
 void launch_unit(ElemArgs<double> a, hipStream_t s) {
     constexpr int NT = 256, V = NT / ((P + 2) * (P + 2));
-    const int64_t pairs = a.ne * a.k;
-    for (a.pair0 = 0; a.pair0 < pairs; a.pair0 += UNIT_BLOCKS * V) {
-        const int64_t blocks = std::min(UNIT_BLOCKS, (pairs - a.pair0 + V - 1) / V);
+    const int64_t step = UNIT_BLOCKS * V / a.k;   // elements
+    for (int64_t e = 0; e < a.ne; e += step) {
+        a.e0 = (int)e;   // a last block that runs on into the next launch's pairs writes the same values
+        const int64_t blocks = (std::min(step, a.ne - e) * a.k + V - 1) / V;
         element_kernel<double, P, NT, V, true, true><<<(unsigned)blocks, NT, 0, s>>>(a);
     }
 }
@@ -1328,14 +1333,30 @@ bool fp32_geometry(const std::vector<double>& corners, int64_t ne, int p, double
     gauss_points(p + 2, g, w);
     const double at[3] = {g.front(), 0.0, g.back()};
     std::atomic<bool> ok{true};
-    parallel_for(ne, 1 << 12, [&](int64_t b, int64_t en) {
+    parallel_for(ne, 1 << 14, [&](int64_t b, int64_t en) {   // 50 ns an element; threads cost 50 us
         bool good = true;
         for (int64_t e = b; e < en && good; ++e) {
             double c[ELEM_COEF];
             trilinear_coefs(corners.data() + (size_t)e * 24, c);
             const int ex = element_exponent(c);
             good = std::abs(ex) <= 64 && std::ldexp(lambda, 3 * ex) <= 0x1p100;
-            for (double& v : c) v = std::ldexp(v, -ex);
+            if (!good) break;
+            const double scale = std::ldexp(1.0, -ex);
+            for (double& v : c) v *= scale;
+            auto norm = [&](int m) { return std::sqrt(c[m] * c[m] + c[m + 1] * c[m + 1] + c[m + 2] * c[m + 2]); };
+            auto det = [](const double* x, const double* y, const double* z) {
+                return x[0] * (y[1] * z[2] - y[2] * z[1]) + x[1] * (y[2] * z[0] - y[0] * z[2]) +
+                       x[2] * (y[0] * z[1] - y[1] * z[0]);
+            };
+            // Bounds from the middle, which most elements pass: the columns change by at most
+            // v, so the determinant by at most the product of l + v less that of l.
+            const double xy = norm(9), xz = norm(12), yz = norm(15), xyz = norm(18);
+            const double l[3] = {norm(0), norm(3), norm(6)};
+            const double v[3] = {xy + xz + xyz, xy + yz + xyz, xz + yz + xyz};
+            const double most = (l[0] + v[0]) * (l[1] + v[1]) * (l[2] + v[2]);
+            if (std::min({l[0] - v[0], l[1] - v[1], l[2] - v[2]}) >= 0x1p-20 &&
+                det(c, c + 3, c + 6) - (most - l[0] * l[1] * l[2]) >= 0x1p-10 * most)
+                continue;
             for (int q = 0; q < 27 && good; ++q) {
                 const double xi = at[q / 9], eta = at[q / 3 % 3], zeta = at[q % 3];
                 double J[3][3], len[3];   // columns dx/dxi, dx/deta, dx/dzeta
@@ -1346,10 +1367,8 @@ bool fp32_geometry(const std::vector<double>& corners, int64_t ne, int p, double
                 }
                 for (int d = 0; d < 3; ++d)
                     len[d] = std::sqrt(J[d][0] * J[d][0] + J[d][1] * J[d][1] + J[d][2] * J[d][2]);
-                const double det = J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) +
-                                   J[0][1] * (J[1][2] * J[2][0] - J[1][0] * J[2][2]) +
-                                   J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]);
-                good = std::min({len[0], len[1], len[2]}) >= 0x1p-20 && det >= 0x1p-10 * len[0] * len[1] * len[2];
+                good = std::min({len[0], len[1], len[2]}) >= 0x1p-20 &&
+                       det(J[0], J[1], J[2]) >= 0x1p-10 * len[0] * len[1] * len[2];
             }
         }
         if (!good) ok = false;
@@ -1404,7 +1423,8 @@ void build_element_form(ElementForm& E, const std::vector<double>& corners, cons
             for (int m = 0; m < ELEM_COEF; ++m) coef[(size_t)m * ne + e] = c[m];
             if (!mixed) continue;
             const int ex = element_exponent(c);
-            for (int m = 0; m < ELEM_COEF; ++m) coef32[(size_t)m * ne + e] = (float)std::ldexp(c[m], -ex);
+            const double scale = std::ldexp(1.0, -ex);
+            for (int m = 0; m < ELEM_COEF; ++m) coef32[(size_t)m * ne + e] = (float)(c[m] * scale);
             coef32[(size_t)ELEM_COEF * ne + e] = (float)std::ldexp(1.0, ex);
             coef32[(size_t)(ELEM_COEF + 1) * ne + e] = (float)std::ldexp(lambda, 3 * ex);
         }

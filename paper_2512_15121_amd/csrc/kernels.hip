@@ -1088,6 +1088,10 @@ __global__ void __launch_bounds__(256) coarse_kernel(int64_t n, const double* __
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE;
     if (row >= n) return;
+    // Waits for the flag where reading the inverse takes longer than that: 9261 rows hold
+    // 0.7 GB, which a stopped solve (20^3 p = 1) would read for 0.13 ms of its 0.40.  Small
+    // ones only look at it in the end (a look in the loop costs 1 us of 512 columns).
+    if (n > 2048 && done) return;
     double acc = 0.0;
     const double* a = inv + row * n;
     for (int64_t j = lane; j < n; j += U * WAVE) {
@@ -1102,7 +1106,6 @@ __global__ void __launch_bounds__(256) coarse_kernel(int64_t n, const double* __
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (j + u * WAVE < n) acc = __builtin_fma(m[u], (double)g[u], acc);
-        if (done) break;   // after the first loads, under way with the flag's: 9261 rows hold 0.7 GB
     }
     acc = wave_sum(acc);
     if (lane == 0 && !done) x[row] = (T)acc;
@@ -1266,6 +1269,7 @@ __global__ void __launch_bounds__(RED_THREADS) reduce_kernel(int64_t m, const do
                                                              int* ctl, const int* stop) {
     constexpr int U = 8;
     const int done = stop != nullptr ? *stop : 0;
+    if (m > 16 * RED_THREADS && done) return;   // as in coarse_kernel
     __shared__ double sh[RED_THREADS / WAVE];
     for (int c = 0; c < ncomp; ++c) {
         double s = 0.0;
@@ -1276,7 +1280,6 @@ __global__ void __launch_bounds__(RED_THREADS) reduce_kernel(int64_t m, const do
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (i + u * RED_THREADS < m) s += v[u];
-            if (done) break;
         }
         s = block_sum<RED_THREADS>(s, sh);
         if (threadIdx.x == 0 && !done) out[c] = s;
