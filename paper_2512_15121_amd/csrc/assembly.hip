@@ -305,7 +305,7 @@ int lds_limit() {
 
 void assemble_fine_device(const std::vector<double>& corners, const int32_t* l2g, int64_t ne, int p,
                           int64_t n, double lambda, const std::vector<uint8_t>& cons, int basis, DevCSR& d,
-                          hipStream_t s) {
+                          std::vector<int64_t>& rp, hipStream_t s) {
     const int n1 = p + 1, nq = p + 2, nl = n1 * n1 * n1, Q = nq * nq * nq;
     GIAMG_REQUIRE(n < (int64_t(1) << 31), "too many nodes for 32-bit column ids");
     // one wavefront per row: a launch covers at most 2^32 - 1 work-items
@@ -373,7 +373,7 @@ void assemble_fine_device(const std::vector<double>& corners, const int32_t* l2g
     GIAMG_HIP(hipMemcpyAsync(hflags, flags.get(), 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     GIAMG_HIP(hipStreamSynchronize(s));
     if (hflags[0]) throw Error(GIAMG_EINVAL, "non-positive Jacobian determinant in an element");
-    std::vector<int64_t> rp(n + 1, 0);
+    rp.assign(n + 1, 0);
     int umax = 1;
     for (int64_t i = 0; i < n; ++i) {
         rp[i + 1] = rp[i] + hc[i];
@@ -398,7 +398,6 @@ void assemble_fine_device(const std::vector<double>& corners, const int32_t* l2g
     GIAMG_HIP(hipMemcpyAsync(hflags, flags.get(), 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     GIAMG_HIP(hipStreamSynchronize(s));
     if (hflags[1]) throw Error(GIAMG_EHIP, "device assembly: row counts differ between passes");
-    setup_row_blocks(d, rp, s);
 }
 
 }  // namespace giamg

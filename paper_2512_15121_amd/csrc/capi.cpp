@@ -319,6 +319,7 @@ int giamg_level_describe(giamg_handle h, int32_t level, giamg_level_desc* out) {
         bind_device(h);
         GIAMG_REQUIRE(out != nullptr, "out is null");
         GIAMG_REQUIRE(level >= 0 && level < (int)h->h.levels.size(), "level out of range");
+        if (level == 0) giamg::describe_rows(h->h);
         const giamg::Level& L = h->h.levels[level];
         out->kind = L.kind;
         out->order = L.order;

@@ -269,6 +269,7 @@ struct Level {
     bool elem_products = false;    // the single-vector products run in the element form: of A only
                                    // the FP64 rows are kept, of A P nothing but its size
     int64_t nnz_AP = 0;            // entries of an A P that is not kept
+    bool rows_described = false;   // with elem_products: A's counts are there (describe_rows)
     TransferForm X;                // and with them, where q > 0, the transfers to the next level
     DevBuf<double> dinv;
     DevBuf<float> dinv32;
@@ -338,6 +339,9 @@ struct Handle {
 
 // Build the fine level's element form if it is not there (solver.hip).
 void ensure_element_form(Handle& H);
+// Where the fine products run over the elements: the counts of the form that A's rows
+// would have, from its tables, which are built for that and given back.
+void describe_rows(Handle& H);
 // Whether products of the fine operator may run in the element form.  Not in
 // mixed precision with one pinned node: there the constant is held by that node
 // alone, and the rounding of the FP32 cycle, not its convergence, decides how far
@@ -383,11 +387,12 @@ void p_transfer_device(const std::vector<int32_t>& l2g, int64_t n_elem, int p, i
                        int64_t& n_coarse, int basis, DevCSR& P, DevCSR& R, bool make32, hipStream_t s);
 // The same operator as assemble_fine (same pattern and entries, each entry
 // summed over its elements in ascending order), built on the device into d
-// (rows, columns, values and the FP64 row blocks).  Throws GIAMG_ENOTSUP when
-// a row's elements hold more candidate columns than the kernels' LDS lists.
+// (rows, columns and values; rp receives the row pointers, no row blocks yet).
+// Throws GIAMG_ENOTSUP when a row's elements hold more candidate columns than the
+// kernels' LDS lists.
 void assemble_fine_device(const std::vector<double>& corners, const int32_t* l2g, int64_t n_elem, int p,
                           int64_t n_nodes, double lambda, const std::vector<uint8_t>& constrained, int basis,
-                          DevCSR& d, hipStream_t s);
+                          DevCSR& d, std::vector<int64_t>& rp, hipStream_t s);
 void quadrature_points(const std::vector<double>& corners, int64_t n_elem, int p, double* xq);
 void load_vector(const std::vector<double>& corners, const int32_t* l2g, int64_t n_elem,
                  int p, int64_t n_nodes, const std::vector<uint8_t>& constrained,
@@ -423,7 +428,7 @@ std::mutex& capture_mutex();
 void parallel_for(int64_t n, int64_t grain, const std::function<void(int64_t, int64_t)>& fn);
 
 // ---- device helpers (kernels_*.hip) ----------------------------------------
-void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32);
+void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32, bool tables = true);
 void download_csr(const DevCSR& d, HostCSR& h, hipStream_t s);
 void make_fp32_values(DevCSR& d, hipStream_t s);
 // C = A * B with the full symbolic structure (device SpGEMM).

@@ -94,7 +94,7 @@ void setup_row_blocks32(DevCSR& d, const std::vector<int64_t>& rp, hipStream_t s
     build_row_blocks(d, d.blk32, spmv_cap<float>(), spmv_threads<float>(), rp, s, nullptr);
 }
 
-void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32) {
+void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32, bool tables) {
     d.nrows = h.nrows;
     d.ncols = h.ncols;
     d.nnz = h.nnz();
@@ -107,7 +107,8 @@ void upload_csr(const HostCSR& h, DevCSR& d, hipStream_t s, bool make32) {
         GIAMG_HIP(hipMemcpyAsync(d.ci.get(), h.ci.data(), d.nnz * sizeof(int32_t), hipMemcpyHostToDevice, s));
         GIAMG_HIP(hipMemcpyAsync(d.val.get(), h.val.data(), d.nnz * sizeof(double), hipMemcpyHostToDevice, s));
     }
-    setup_row_blocks(d, h.rp, s);
+    if (!tables) GIAMG_HIP(hipStreamSynchronize(s));   // the host arrays may go
+    if (tables) setup_row_blocks(d, h.rp, s);
     if (make32) {
         make_fp32_values(d, s);
         setup_row_blocks32(d, h.rp, s);
@@ -180,51 +181,45 @@ int64_t product_blocks(const Level& L) {
     return L.elem_products ? element_blocks(M.nrows) : M.lean ? M.lean_nblk : M.gnblk > 0 ? M.gnblk : M.blk.nblk;
 }
 
-// Lean form for the operators with at most max_nnz nonzeros and no row longer
-// than spmv_cap<double>() (their staging tables are released).
-void assign_lean_forms(Handle& H, int64_t max_nnz) {
-    for (Level& L : H.levels)
-        for (DevCSR* M : {&L.A, &L.AP, &L.P, &L.R}) {
-            M->lean = false;
-            M->lean_nblk = 0;
-            if (M->nrows <= 0 || M->nnz > max_nnz) continue;
-            std::vector<int64_t> rp((size_t)M->nrows + 1);
-            GIAMG_HIP(hipMemcpyAsync(rp.data(), M->rp.get(), rp.size() * sizeof(int64_t),
-                                     hipMemcpyDeviceToHost, H.stream));
-            GIAMG_HIP(hipStreamSynchronize(H.stream));
-            int64_t maxlen = 0;
-            for (int64_t r = 0; r < M->nrows; ++r) maxlen = std::max(maxlen, rp[r + 1] - rp[r]);
-            if (maxlen > spmv_cap<double>()) continue;
-            const int64_t rpb = LEAN_THREADS / M->lanes;
-            M->lean = true;
-            M->lean_nblk = (M->nrows + rpb - 1) / rpb;
-            M->blk.release_staging();
-            M->blk32.release_staging();
-        }
+// Lean form for an operator with at most max_nnz nonzeros and no row longer
+// than spmv_cap<double>() (its staging tables are released).
+void assign_lean_form(DevCSR& M, int64_t max_nnz, hipStream_t s) {
+    M.lean = false;
+    M.lean_nblk = 0;
+    if (M.nrows <= 0 || M.nnz > max_nnz) return;
+    std::vector<int64_t> rp((size_t)M.nrows + 1);
+    GIAMG_HIP(hipMemcpyAsync(rp.data(), M.rp.get(), rp.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GIAMG_HIP(hipStreamSynchronize(s));
+    int64_t maxlen = 0;
+    for (int64_t r = 0; r < M.nrows; ++r) maxlen = std::max(maxlen, rp[r + 1] - rp[r]);
+    if (maxlen > spmv_cap<double>()) return;
+    const int64_t rpb = LEAN_THREADS / M.lanes;
+    M.lean = true;
+    M.lean_nblk = (M.nrows + rpb - 1) / rpb;
+    M.blk.release_staging();
+    M.blk32.release_staging();
 }
 
-// Grouped forms (groups.cpp) of the operators whose rows share column lists;
-// an operator that gets one drops its CSR staging tables (its products then
-// always run grouped).
-void build_grouped_forms(Handle& H, bool mixed) {
-    for (size_t l = 0; l + 1 < H.levels.size(); ++l) {
-        Level& L = H.levels[l];
-        for (DevCSR* M : {&L.A, &L.AP, &L.P, &L.R}) {
-            if (M->nnz <= 0 || M->lean) continue;
-            std::vector<int64_t> rp((size_t)M->nrows + 1);
-            std::vector<int32_t> ci((size_t)M->nnz);
-            GIAMG_HIP(hipMemcpyAsync(rp.data(), M->rp.get(), rp.size() * sizeof(int64_t),
-                                     hipMemcpyDeviceToHost, H.stream));
-            GIAMG_HIP(hipMemcpyAsync(ci.data(), M->ci.get(), ci.size() * sizeof(int32_t),
-                                     hipMemcpyDeviceToHost, H.stream));
-            GIAMG_HIP(hipStreamSynchronize(H.stream));
-            if (!build_grouping(*M, rp, ci, H.stream)) continue;
-            if (mixed) make_fp32_group_values(*M, H.stream);
-            M->blk.release_staging();
-            M->blk32.release_staging();
-        }
-    }
-    GIAMG_HIP(hipStreamSynchronize(H.stream));
+// Grouped form (groups.cpp) of an operator whose rows share column lists; it then
+// drops its CSR staging tables (its products always run grouped).
+void build_grouped_form(DevCSR& M, bool mixed, hipStream_t s) {
+    if (M.nnz <= 0 || M.lean) return;
+    std::vector<int64_t> rp((size_t)M.nrows + 1);
+    std::vector<int32_t> ci((size_t)M.nnz);
+    GIAMG_HIP(hipMemcpyAsync(rp.data(), M.rp.get(), rp.size() * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    GIAMG_HIP(hipMemcpyAsync(ci.data(), M.ci.get(), ci.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    GIAMG_HIP(hipStreamSynchronize(s));
+    if (!build_grouping(M, rp, ci, s)) return;
+    if (mixed) make_fp32_group_values(M, s);
+    M.blk.release_staging();
+    M.blk32.release_staging();
+    GIAMG_HIP(hipStreamSynchronize(s));
+}
+
+// The operators of a level that single-vector products read as rows.
+std::vector<DevCSR*> row_operators(Level& L) {
+    if (L.elem_products) return {&L.P, &L.R};
+    return {&L.A, &L.AP, &L.P, &L.R};
 }
 
 void make_fp32_values(DevCSR& d, hipStream_t s) {
@@ -327,6 +322,23 @@ void ensure_element_form(Handle& H) {
     L.E = std::move(E);
 }
 
+void describe_rows(Handle& H) {
+    Level& L = H.levels[0];
+    if (!L.elem_products || L.rows_described) return;
+    AllocStreamScope alloc_scope(H.stream);
+    DevCSR& A = L.A;
+    std::vector<int64_t> rp((size_t)A.nrows + 1);
+    GIAMG_HIP(hipMemcpyAsync(rp.data(), A.rp.get(), rp.size() * sizeof(int64_t), hipMemcpyDeviceToHost, H.stream));
+    GIAMG_HIP(hipStreamSynchronize(H.stream));
+    setup_row_blocks(A, rp, H.stream);
+    const giamg_opts& o = H.opts;
+    if (o.lean_max_nnz > 0) assign_lean_form(A, o.lean_max_nnz, H.stream);
+    if (o.row_groups && !o.direct_gathers && H.levels.size() > 1) build_grouped_form(A, false, H.stream);
+    if (o.direct_gathers) A.blk.release_staging();
+    A.release_product_arrays();
+    L.rows_described = true;
+}
+
 void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     noalloc_scratch_init();
     AllocStreamScope alloc_scope(H.stream);
@@ -356,10 +368,11 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         L.order = H.porder;
         L.n = n;
         L.l2g = H.l2g;
+        std::vector<int64_t> rp;
         if (o.assembly != GIAMG_ASSEMBLY_HOST) {
             try {
                 assemble_fine_device(H.corners, l2g, ne, H.porder, n, H.lambda, H.constrained, o.basis, L.A,
-                                     H.stream);
+                                     rp, H.stream);
                 L.device_assembled = true;
             } catch (const Error& e) {
                 // AUTO: meshes whose rows outgrow the kernels' LDS lists go to the host
@@ -369,14 +382,16 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         }
         if (!L.device_assembled) {
             HostCSR A0 = assemble_fine(H.corners, l2g, ne, H.porder, n, H.lambda, H.constrained, o.basis);
-            upload_csr(A0, L.A, H.stream, false);
+            upload_csr(A0, L.A, H.stream, false, false);
+            rp = std::move(A0.rp);
         }
-    }
-    if (use_element_form(H)) {
-        Level& L = H.levels.back();
-        ensure_element_form(H);
-        L.E.ev.alloc(L.E.map.n);
-        L.elem_products = true;
+        if (use_element_form(H)) {
+            ensure_element_form(H);
+            L.E.ev.alloc(L.E.map.n);
+            L.elem_products = true;
+        } else {
+            setup_row_blocks(L.A, rp, H.stream);
+        }
     }
     H.setup_ms[0] = ms_since(t0);
     // p-levels
@@ -436,10 +451,6 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         C.n = nc;
         C.l2g = std::move(l2g_next);
         spgemm(F.R, F.AP, C.A, H.stream);
-        if (F.elem_products) {   // no product reads it (vcycle, bsmooth)
-            F.nnz_AP = F.AP.nnz;
-            F.AP = DevCSR();
-        }
         H.setup_ms[3] += ms_since(t0);
         H.levels.push_back(std::move(C));
         // Transfers by the element form from a million entries of P on.  Whole solves with and
@@ -510,14 +521,12 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     }
     H.setup_ms[4] = ms_since(t0);
     t0 = clock_t_::now();
-    if (o.lean_max_nnz > 0) assign_lean_forms(H, o.lean_max_nnz);
-    if (o.row_groups && !o.direct_gathers) build_grouped_forms(H, mixed);
-    // (built so that a level's description tells what its rows' products would use)
-    if (H.levels[0].elem_products) H.levels[0].A.release_product_arrays();
-    if (H.levels[0].X.q > 0) {
-        H.levels[0].P.release_product_arrays();
-        H.levels[0].R.release_product_arrays();
-    }
+    if (o.lean_max_nnz > 0)
+        for (Level& L : H.levels)
+            for (DevCSR* M : row_operators(L)) assign_lean_form(*M, o.lean_max_nnz, H.stream);
+    if (o.row_groups && !o.direct_gathers)
+        for (size_t l = 0; l + 1 < H.levels.size(); ++l)
+            for (DevCSR* M : row_operators(H.levels[l])) build_grouped_form(*M, mixed, H.stream);
     const double grouping_ms = ms_since(t0);
     // work buffers
     int64_t maxn = 1, maxblk = 1;
@@ -541,7 +550,7 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
         alloc_level_vectors(L, mixed);
         if (mixed && !L.elem_products) make_fp32_operator(L.A, H.stream);
         if (l + 1 == H.levels.size() && !jacobi) break;
-        if (mixed && L.AP.nrows > 0) make_fp32_operator(L.AP, H.stream);
+        if (mixed && !L.elem_products) make_fp32_operator(L.AP, H.stream);
         L.dinv.alloc(L.n);
         DevBuf<int> bad(1);
         GIAMG_HIP(hipMemsetAsync(bad.get(), 0, sizeof(int), H.stream));
@@ -576,6 +585,17 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     if (!H.ev_join) GIAMG_HIP(hipEventCreateWithFlags(&H.ev_join, hipEventDisableTiming));
     if (!H.gstream) GIAMG_HIP(hipStreamCreateWithFlags(&H.gstream, hipStreamNonBlocking));
     GIAMG_HIP(hipStreamSynchronize(H.stream));
+    // What no product reads (vcycle, bsmooth, args_transfer).  Here and not before: what
+    // is allocated after large blocks have been freed comes 1 to 2 ms later (12^3 p = 4).
+    Level& F = H.levels[0];
+    if (F.elem_products) {
+        F.nnz_AP = F.AP.nnz;
+        F.AP = DevCSR();
+    }
+    if (F.X.q > 0) {
+        F.P.release_product_arrays();
+        F.R.release_product_arrays();
+    }
     H.setup_ms[6] = ms_since(t_all);
 }
 

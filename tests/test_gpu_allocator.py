@@ -70,7 +70,7 @@ def test_failing_allocator_is_an_allocation_error():
 
 # (in mixed precision the tuning of the rows' products at p = 5 needs more than the element form)
 @pytest.mark.parametrize("n,p,k,session,precision", [(6, 4, 8, False, "fp64"), (6, 4, 8, False, "mixed"),
-                                                     (9, 4, 3, False, "fp64"), (9, 4, 3, False, "mixed"),
+                                                     (9, 4, 4, False, "fp64"), (9, 4, 4, False, "mixed"),
                                                      (5, 3, 64, True, "fp64"), (5, 3, 64, True, "mixed"),
                                                      (4, 5, 64, False, "fp64")])
 def test_batches_without_memory_for_the_element_form(n, p, k, session, precision):
