@@ -35,11 +35,12 @@
  *     giamg_solve_noalloc and giamg_apply from 4 M and 0.15 M p^2 nonzeros on
  *     (with the nodal basis, keep_boundary = 0 and a million entries of P the
  *     transfers next to it too), in giamg_solve_batch, sessions and the
- *     server at every size.  Not in mixed precision with one pinned node or
- *     on elements whose geometry FP32 does not serve (sheared 1000 times or
- *     stretched 10^6 times), and not in batches of a handle for whose element
- *     matrices or results the device had no memory (p <= 4: 8 bytes, mixed
- *     12, per entry of every element's matrix).  direct_gathers, row_groups,
+ *     server at every size.  Not in mixed precision with one pinned node, nor
+ *     (but for batches of p <= 4) on elements whose geometry FP32 does not
+ *     serve (sheared 1000 times or stretched 10^6 times), and not in batches
+ *     of a handle for whose element matrices or results the device had no
+ *     memory (p <= 4: 8 bytes, mixed 12, per entry of every element's
+ *     matrix).  direct_gathers, row_groups,
  *     lean_max_nnz and batch_kernel choose among the forms of the CSR
  *     products, here and on the other levels.
  */

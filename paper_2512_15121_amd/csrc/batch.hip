@@ -1014,10 +1014,11 @@ Tile tile_for(BatchCtx& c, const DevCSR& M, const std::string& key);
 // do not; where the device has none left, the handle's batches take the rows
 // (tuned_state).  The dense form launches 256 threads per element, of which a launch
 // holds less than 2^32.
-bool block_element_form(const Handle& H) {
+bool block_element_form(Handle& H) {
     const int64_t nl = (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1);
     return element_form_allowed(H) && !H.block_rows && H.porder >= 2 && H.porder <= 10 &&
-           H.n_elem * nl < (int64_t(1) << 31) && (H.porder > 4 || H.n_elem < (int64_t(1) << 24));
+           H.n_elem * nl < (int64_t(1) << 31) &&
+           (H.porder > 4 ? fp32_elements_ok(H) : H.n_elem < (int64_t(1) << 24));
 }
 
 template <typename T>

@@ -292,7 +292,7 @@ struct Handle {
     std::vector<uint8_t> constrained;
     // geometry kept for the load-vector helpers
     std::vector<double> corners;      // [n_elem][8][3]
-    bool fp32_elements = true;        // fp32_geometry of the mesh (mixed precision)
+    int fp32_elements = -1;           // fp32_geometry of the mesh, -1 before it is asked for
     std::vector<int32_t> l2g;         // fine element map
     // coarsest level: dense inverse (FP64), rows nc
     int64_t nc = 0;
@@ -347,11 +347,13 @@ void describe_rows(Handle& H);
 // alone, and the rounding of the FP32 cycle, not its convergence, decides how far
 // the solution is shifted (any other rounding, of the FP64 products too, moves
 // it by 1e-10 to 2e-8 of itself at a tolerance of 1e-10).  These handles keep the
-// assembled rows, and with them their solutions to the last bit.  Nor in mixed
-// precision on elements whose geometry FP32 does not serve (fp32_geometry).
+// assembled rows, and with them their solutions to the last bit.
 inline bool element_form_allowed(const Handle& H) {
-    return H.opts.precision != GIAMG_PREC_MIXED || (H.opts.bc != GIAMG_BC_PIN && H.fp32_elements);
+    return !(H.opts.precision == GIAMG_PREC_MIXED && H.opts.bc == GIAMG_BC_PIN);
 }
+// Whether sum factorisation over the elements serves the handle's precisions: in mixed
+// precision their geometry is FP32's then (element matrices are formed in FP64).
+bool fp32_elements_ok(Handle& H);
 
 // ---- host setup (setup_host.cpp) -------------------------------------------
 void gll_points(int p, std::vector<double>& x, std::vector<double>& w);

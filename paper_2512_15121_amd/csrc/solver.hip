@@ -307,10 +307,16 @@ void noalloc_scratch_init();
 // p = 2 to 18 us at p = 10, a CSR step of 4 M nonzeros takes about 13 us.  The
 // rule looks at the operator alone, so the product forms of the CSR arrays
 // (staged, direct, lean, grouped) all leave the same results behind.
-static bool use_element_form(const Handle& H) {
+static bool use_element_form(Handle& H) {
     const int64_t p = H.porder, nl = (p + 1) * (p + 1) * (p + 1);
     return element_form_allowed(H) && p >= 2 && p <= 10 && H.levels[0].A.nnz >= std::max<int64_t>(4000000, 150000 * p * p) &&
-           H.n_elem * nl < (int64_t(1) << 31);
+           H.n_elem * nl < (int64_t(1) << 31) && fp32_elements_ok(H);
+}
+
+bool fp32_elements_ok(Handle& H) {
+    if (H.opts.precision != GIAMG_PREC_MIXED) return true;
+    if (H.fp32_elements < 0) H.fp32_elements = fp32_geometry(H.corners, H.n_elem, H.porder, H.lambda);
+    return H.fp32_elements == 1;
 }
 
 void ensure_element_form(Handle& H) {
@@ -358,7 +364,6 @@ void build_hierarchy(Handle& H, const double* coords, const int32_t* l2g) {
     for (auto c : H.constrained) ncons += c;
     GIAMG_REQUIRE(H.lambda > 0.0 || ncons > 0, "lambda = 0 needs at least one constrained node");
     element_corners(coords, l2g, ne, H.porder, H.corners, o.basis);
-    H.fp32_elements = !mixed || fp32_geometry(H.corners, ne, H.porder, H.lambda);
     H.l2g.assign(l2g, l2g + ne * (int64_t)(H.porder + 1) * (H.porder + 1) * (H.porder + 1));
     H.levels.clear();
     H.levels.emplace_back();
